@@ -12,13 +12,13 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liblma.so")
-SOURCES = ["engine.hip", "kernels_misc.hip", "vecsolve.hip", "grad.hip", "kvec.hip", "lma.hip", "lma_grad.hip", "ds.hip",
+SOURCES = ["engine.hip", "diag.hip", "kernels_misc.hip", "vecsolve.hip", "grad.hip", "kvec.hip", "lma.hip", "lma_grad.hip", "ds.hip",
            "kmeans.hip", "partition.hip"]
 ARCH = os.environ.get("LMA_OFFLOAD_ARCH", "gfx950")
 # Per-source flags.  kvec.hip: its MFMA accumulators feed vector arithmetic
 # right after every short k loop; in the accumulator-register form the compiler
 # copies them between register files on every iteration, the VGPR form does not.
-SOURCE_FLAGS = {"kvec.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+SOURCE_FLAGS = {"kvec.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "diag.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def hipcc():

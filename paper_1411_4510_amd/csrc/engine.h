@@ -28,7 +28,6 @@ namespace lma {
 
 constexpr int TB = 128;     // tile edge
 constexpr int NT = 256;     // threads per workgroup (4 wave64)
-constexpr int DIAG_LD = TB + 1;
 
 // SRC_IDENT: the right-hand-side rows are rows kbeg*TB .. kbeg*TB+127 of the
 // identity, so the solve produces the matching rows of L^-T (an explicit
@@ -97,6 +96,7 @@ struct StepArgs {
   // (u, x) at band[brow[u] + x]; null when no row of the run uses one
   const T* band;
   const int64_t* brow;
+  int32_t mixed_fit;  // 1: Sigma_SS of a mixed-precision fit (which diagonal kernel runs, see diag.hip)
 };
 
 // Residual band: for training point p in block a, the entries
@@ -141,6 +141,7 @@ template <typename T>
 void launch_diag(const StepArgs<T>& a, const int32_t* plist, int np, hipStream_t st);
 template <typename T>
 void launch_trsm(const StepArgs<T>& a, hipStream_t st);
+hipError_t diag_init();
 
 // Batched float64-accumulating GEMM over tiles: output tile o computes
 //   acc = sum_{t in [tneg, t1)} A_t B_t^T - sum_{t in [t0, tneg)} A_t B_t^T

@@ -170,199 +170,6 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
 }
 
 // ---------------------------------------------------------------------------
-// diag: Cholesky of the diagonal tile (j, j) in LDS, its log-diagonal, and the
-// inverse of the factor for the triangular solves of the tiles below.
-// ---------------------------------------------------------------------------
-// The tile is factored and inverted in float64 for every storage type (the
-// float32 window factors of the mixed mode included): the diagonal tiles of
-// late column steps hold Schur complements near the noise level, and their
-// factor and inverse feed every later tile.
-//
-// Both run on 32 x 32 blocks.  Factor, for each block column kb: one wave
-// factors the diagonal block in lock step (no workgroup barrier per column),
-// the rows below are solved against it one row per thread, and the trailing
-// block update is spread over the workgroup.  Inverse (in place, X = L^-1):
-// the four diagonal blocks are inverted by the four waves at once, then block
-// columns right to left: T_ib = sum_{k=jb+1..ib} X_ib,k L_k,jb for every block
-// row ib below jb, and X_ib,jb = -T_ib X_jb,jb.  About twenty workgroup
-// barriers per tile instead of two per column.
-constexpr int DB = 32;          // block size of the diagonal-tile algorithms
-constexpr int DNB = TB / DB;    // blocks per tile side
-constexpr int DT_LD = DB + 1;   // row stride of the block products' scratch
-
-__device__ inline void wave_sync_lds() {
-  // LDS writes of this wave are visible to its other lanes after this point
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <typename T>
-__global__ __launch_bounds__(NT) void k_diag(StepArgs<T> a, const int32_t* __restrict__ plist) {
-  typedef double TA;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  TA* A = reinterpret_cast<TA*>(smem_raw);  // [TB][DIAG_LD]
-  TA* Tt = A + TB * DIAG_LD;                // [DNB-1][DB][DT_LD] block products
-  __shared__ int bad;
-  __shared__ double lsum[NT / 64];
-  const int p = plist[blockIdx.x];
-  const ProbDesc pd = a.pd[p];
-  const RowTile<T> rj = a.rt[pd.first + a.j];
-  T* src = rj.panel + (int64_t)a.j * TB;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid == 0) bad = 0;
-  for (int idx = tid; idx < TB * TB; idx += NT) {
-    const int r = idx >> 7, c = idx & (TB - 1);
-    A[r * DIAG_LD + c] = c <= r ? (TA)src[(int64_t)r * rj.ld + c] : TA(0);
-  }
-  __syncthreads();
-
-  // ---- factor
-  for (int kb = 0; kb < DNB; ++kb) {
-    const int b0 = kb * DB;
-    if (w == 0) {  // diagonal block, right-looking, one wave in lock step
-      const int rl = lane & 31, h = lane >> 5, r = b0 + rl;
-      for (int k = 0; k < DB; ++k) {
-        const int kk = b0 + k;
-        TA dkk = A[kk * DIAG_LD + kk];
-        const bool ok = dkk > TA(0);
-        if (!ok) dkk = TA(1);
-        const TA piv = k_sqrt(dkk), ip = TA(1) / piv;
-        wave_sync_lds();  // every lane has read the pivot
-        if (h == 0) {
-          if (rl > k) {
-            A[r * DIAG_LD + kk] *= ip;
-          } else if (rl == k) {
-            A[kk * DIAG_LD + kk] = piv;
-            if (!ok) bad = 1;
-          }
-        }
-        wave_sync_lds();  // column kk scaled
-        if (rl > k) {
-          const TA lrk = A[r * DIAG_LD + kk];
-          for (int c = kk + 1 + h; c <= r; c += 2) A[r * DIAG_LD + c] -= lrk * A[c * DIAG_LD + kk];
-        }
-        wave_sync_lds();
-      }
-    }
-    __syncthreads();
-    const int m = TB - b0 - DB;  // rows below the block
-    if (m == 0) break;
-    if (tid < m) {  // rows below: solve x L_kb^T = a, one row per thread
-      const int r = b0 + DB + tid;
-      TA x[DB];
-#pragma unroll
-      for (int c = 0; c < DB; ++c) x[c] = A[r * DIAG_LD + b0 + c];
-#pragma unroll
-      for (int c = 0; c < DB; ++c) {
-        TA sacc = x[c];
-#pragma unroll
-        for (int k = 0; k < c; ++k) sacc -= x[k] * A[(b0 + c) * DIAG_LD + b0 + k];
-        x[c] = sacc / A[(b0 + c) * DIAG_LD + b0 + c];
-      }
-#pragma unroll
-      for (int c = 0; c < DB; ++c) A[r * DIAG_LD + b0 + c] = x[c];
-    }
-    __syncthreads();
-    // trailing update of the lower triangle below and right of the block, 4 x 4 per thread
-    const int m4 = m >> 2;
-    for (int t = tid; t < m4 * m4; t += NT) {
-      const int bi = t / m4, bj = t - bi * m4;
-      if (bj > bi) continue;
-      const int r0 = b0 + DB + 4 * bi, c0 = b0 + DB + 4 * bj;
-      TA acc[4][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = TA(0);
-      for (int k = 0; k < DB; ++k) {
-        TA ar[4], ac[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          ar[u] = A[(r0 + u) * DIAG_LD + b0 + k];
-          ac[u] = A[(c0 + u) * DIAG_LD + b0 + k];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[u][v] += ar[u] * ac[v];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (c0 + v <= r0 + u) A[(r0 + u) * DIAG_LD + c0 + v] -= acc[u][v];
-    }
-    __syncthreads();
-  }
-  if (bad && tid == 0) a.status[p] = 1;
-  // store L_jj and its log-diagonal
-  for (int idx = tid; idx < TB * TB; idx += NT) {
-    const int r = idx >> 7, c = idx & (TB - 1);
-    src[(int64_t)r * rj.ld + c] = c <= r ? (T)A[r * DIAG_LD + c] : T(0);
-  }
-  {
-    double ls = 0.0;
-    if (tid < TB && tid < rj.nvalid) ls = log((double)A[tid * DIAG_LD + tid]);
-    for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o);
-    if ((tid & 63) == 0) lsum[tid >> 6] = ls;
-  }
-  __syncthreads();  // the factor is stored and read before the inverse overwrites it
-  if (tid == 0) {
-    const double tot = lsum[0] + lsum[1] + lsum[2] + lsum[3];
-    a.logdiag[(int64_t)p * a.maxT + a.j] = (a.j >= pd.ld_from) ? tot : 0.0;
-  }
-
-  // ---- inverse, diagonal blocks: wave w inverts block w, last column first:
-  //   X_jj = 1/L_jj,  X_ij = -X_jj sum_{k=j+1..i} X_ik L_kj
-  {
-    const int b0 = w * DB, il = lane & 31, h = lane >> 5;
-    for (int jj = DB - 1; jj >= 0; --jj) {
-      const TA xjj = TA(1) / A[(b0 + jj) * DIAG_LD + b0 + jj];
-      TA sacc = TA(0);
-      if (il > jj)
-        for (int k = jj + 1 + h; k <= il; k += 2) sacc += A[(b0 + il) * DIAG_LD + b0 + k] * A[(b0 + k) * DIAG_LD + b0 + jj];
-      sacc += __shfl_xor(sacc, 32);
-      wave_sync_lds();  // column jj of L read by every lane
-      if (h == 0 && il > jj) A[(b0 + il) * DIAG_LD + b0 + jj] = -xjj * sacc;
-      if (lane == 0) A[(b0 + jj) * DIAG_LD + b0 + jj] = xjj;
-      wave_sync_lds();
-    }
-  }
-  __syncthreads();
-  // ---- inverse, block columns right to left
-  for (int jb = DNB - 2; jb >= 0; --jb) {
-    const int nb = DNB - 1 - jb;
-    for (int e = tid; e < nb * DB * DB; e += NT) {
-      const int q = e / (DB * DB), rem = e - q * (DB * DB), i = rem / DB, jc = rem - i * DB;
-      const int ib = jb + 1 + q;
-      TA sacc = TA(0);
-      for (int kb2 = jb + 1; kb2 <= ib; ++kb2) {
-        const TA* xr = A + (ib * DB + i) * DIAG_LD + kb2 * DB;
-        const TA* lc = A + (kb2 * DB) * DIAG_LD + jb * DB + jc;
-#pragma unroll 8
-        for (int kk = 0; kk < DB; ++kk) sacc += xr[kk] * lc[kk * DIAG_LD];
-      }
-      Tt[(q * DB + i) * DT_LD + jc] = sacc;
-    }
-    __syncthreads();
-    for (int e = tid; e < nb * DB * DB; e += NT) {
-      const int q = e / (DB * DB), rem = e - q * (DB * DB), i = rem / DB, jc = rem - i * DB;
-      const int ib = jb + 1 + q;
-      TA sacc = TA(0);
-      for (int kk = jc; kk < DB; ++kk) sacc += Tt[(q * DB + i) * DT_LD + kk] * A[(jb * DB + kk) * DIAG_LD + jb * DB + jc];
-      A[(ib * DB + i) * DIAG_LD + jb * DB + jc] = -sacc;
-    }
-    __syncthreads();
-  }
-  T* inv = a.invdiag + pd.invdiag_off + (int64_t)a.j * TB * TB;
-  for (int idx = tid; idx < TB * TB; idx += NT) {
-    const int r = idx >> 7, c = idx & (TB - 1);
-    inv[idx] = c <= r ? (T)A[r * DIAG_LD + c] : T(0);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // trsm: L_ij = C_ij L_jj^-T (in place) for every item (p, i), i != j
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -509,11 +316,6 @@ __global__ __launch_bounds__(NT) void k_band(BandArgs<T> a) {
 static inline int pad8(int n) { return ((n + 7) / 8) * 8; }
 
 template <typename T>
-size_t diag_lds_bytes() {
-  return sizeof(T) * (size_t)(TB * DIAG_LD + (DNB - 1) * DB * DT_LD);
-}
-
-template <typename T>
 void launch_update(const StepArgs<T>& a, bool mixed, hipStream_t st) {
   if (a.nitems <= 0) return;
   if constexpr (std::is_same<T, float>::value) {
@@ -527,12 +329,6 @@ void launch_update(const StepArgs<T>& a, bool mixed, hipStream_t st) {
     const size_t lds = 2 * (size_t)a.d * TB * sizeof(T);
     hipLaunchKernelGGL((k_update<T, false>), dim3(pad8(a.nitems)), dim3(NT), lds, st, a);
   }
-}
-
-template <typename T>
-void launch_diag(const StepArgs<T>& a, const int32_t* plist, int np, hipStream_t st) {
-  if (np <= 0) return;
-  hipLaunchKernelGGL(k_diag<T>, dim3(np), dim3(NT), diag_lds_bytes<double>(), st, a, plist);
 }
 
 template <typename T>
@@ -555,11 +351,7 @@ void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, h
 
 // Raise the dynamic-LDS limit of the kernels that need more than the default.
 hipError_t engine_init() {
-  hipError_t e = hipFuncSetAttribute((const void*)k_diag<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)diag_lds_bytes<double>());
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)k_diag<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)diag_lds_bytes<double>());
+  hipError_t e = diag_init();
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)k_update<double, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(double)));
@@ -579,8 +371,6 @@ hipError_t engine_init() {
 
 template void launch_update<double>(const StepArgs<double>&, bool, hipStream_t);
 template void launch_update<float>(const StepArgs<float>&, bool, hipStream_t);
-template void launch_diag<double>(const StepArgs<double>&, const int32_t*, int, hipStream_t);
-template void launch_diag<float>(const StepArgs<float>&, const int32_t*, int, hipStream_t);
 template void launch_trsm<double>(const StepArgs<double>&, hipStream_t);
 template void launch_trsm<float>(const StepArgs<float>&, hipStream_t);
 template void launch_band<double>(const BandArgs<double>&, hipStream_t);

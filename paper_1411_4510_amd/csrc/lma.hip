@@ -725,6 +725,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     a.logdiag = logdiag + (int64_t)slot * maxTld;
     a.status = status + slot;
     a.maxT = maxTld;
+    a.mixed_fit = mixed && slot == (int)M ? 1 : 0;
     for (int j = 0; j < realT; ++j) {
       a.j = j;
       a.items = run.d_items + run.upd_off[j];
