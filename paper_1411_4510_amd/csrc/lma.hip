@@ -146,7 +146,6 @@ void ensure_init() {
   if (g_inited) return;
   HIPCHK(engine_init());
   HIPCHK(misc_init());
-  HIPCHK(vecsolve_init());
   HIPCHK(grad_init());
   HIPCHK(kvec_init());
   g_inited = true;
@@ -927,14 +926,14 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
       auto va = winvec(panels, invs, xJ, xW, c);
       using TT = typename std::remove_const<typename std::remove_pointer<decltype(panels)>::type>::type;
       prof::timed(prof::OTHER, 0.0, st, [&] { launch_ycp<TT>(va, nwin(c), maxTw, st); });
-      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, nwin(c), st); });
+      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, nwin(c), maxTw, st); });
       HIPCHK(hipGetLastError());
     };
     auto full_solve = [&](auto* panels, auto* invs, double* vJ, double* vW, int c) {
       auto va = winvec(panels, invs, vJ, vW, c);
       using TT = typename std::remove_const<typename std::remove_pointer<decltype(panels)>::type>::type;
       prof::timed(prof::OTHER, 0.0, st, [&] { launch_fwd<TT>(va, nwin(c), maxTw, st); });
-      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, nwin(c), st); });
+      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, nwin(c), maxTw, st); });
       HIPCHK(hipGetLastError());
     };
     // x += alpha t over the vector entries of chunk c's windows

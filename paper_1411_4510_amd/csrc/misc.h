@@ -75,7 +75,6 @@ void launch_pred_var(const PredArgs& a, hipStream_t st);
 template <typename T>
 void launch_pred_xi(const XiArgs<T>& a, hipStream_t st);
 hipError_t misc_init();
-hipError_t vecsolve_init();
 hipError_t engine_init();
 
 }  // namespace lma
@@ -139,7 +138,7 @@ void launch_ycp(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st);
 template <typename TW>
 void launch_fwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st);
 template <typename TW>
-void launch_bwd(const WinVecArgs<TW>& a, int M, hipStream_t st);
+void launch_bwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st);
 void launch_gres(const GresArgs& a, hipStream_t st);
 // g += dg and t = L_SS^T dg (one workgroup)
 void launch_gupdate(const double* L, const double* dg, double* g, double* t, int sp, hipStream_t st);

@@ -46,147 +46,145 @@ __device__ inline double wave_sum(double v) {
 }
 
 // ---------------------------------------------------------------------------
-// triangular solves of one vector per window (one workgroup of 8 waves per
-// window; the panels are streamed once per solve with 16-byte loads)
+// triangular solves of one vector per window and separator
 // ---------------------------------------------------------------------------
+// Right-looking over the tiles, all windows in lock step, one launch per column
+// tile: launch i subtracts the products with the tile solved before from every
+// tile that is left (one workgroup per 128 x 128 factor tile), and the workgroup
+// whose tile is next solves it at once with the inverted diagonal tile.  It alone
+// touches that tile of the vector, so the solution replaces the vector in place.
+// W_m's factor is the leading block of J_m's, so both vectors take part in one
+// read of a tile.  Bound: one read of the factors (HBM), and for few or narrow
+// windows the launches.  Measured against one workgroup per window walking its
+// factor once for each vector: backward at n=16384, M=16, B=15 (6.3 GB of factors)
+// 44.2 -> 2.6 ms, n=2048 92 -> 20 us (4 launches); forward and backward of a mixed
+// fit (n=50021, B=3) 26.7 -> about 4 ms.
 constexpr int SOLVE_NT = 512;
-constexpr size_t FWD_LDS_MAX = 150 * 1024;  // solved prefix of windows up to 19200 rows in LDS
+constexpr int SOLVE_W = SOLVE_NT / 64;
+constexpr int SOLVE_R = TB / SOLVE_W;  // tile rows of a wave
 
 template <typename TW>
-struct Vec16;
+struct Vec2;
 template <>
-struct Vec16<float> {
-  typedef float type __attribute__((ext_vector_type(4)));
-  static constexpr int n = 4;
-};
+struct Vec2<float> { typedef float type __attribute__((ext_vector_type(2))); };
 template <>
-struct Vec16<double> {
-  typedef double type __attribute__((ext_vector_type(2)));
-  static constexpr int n = 2;
-};
+struct Vec2<double> { typedef double type __attribute__((ext_vector_type(2))); };
 
-// forward, left-looking: t_i = v_i - L_{i,<i} x_{<i}, x_i = L_ii^-1 t_i, x in v.
-// xs holds the solved prefix (LDS when it fits, else v itself).
+// The rows of this wave (SOLVE_R of them from row SOLVE_R * wave on) of a 128 x 128
+// tile; each lane holds columns 2 lane and 2 lane + 1.
 template <typename TW>
-__device__ void fwd_solve(const TW* base, const TW* inv, double* v, int nt, double* xs, double* t) {
-  typedef typename Vec16<TW>::type VT;
-  constexpr int NV = Vec16<TW>::n, STEP = 64 * NV;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int i = 0; i < nt; ++i) {
-    const TW* P = base + jp_off(i);
-    const int64_t ld = (int64_t)(i + 1) * TB;
-    const int K = i * TB;
-    for (int r = wv; r < TB; r += SOLVE_NT / 64) {
-      const TW* row = P + (int64_t)r * ld;
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-      int k = lane * NV;
-      for (; k + 3 * STEP < K; k += 4 * STEP) {
-        const VT a0 = *(const VT*)(row + k), a1 = *(const VT*)(row + k + STEP);
-        const VT a2 = *(const VT*)(row + k + 2 * STEP), a3 = *(const VT*)(row + k + 3 * STEP);
+__device__ inline void load_rows(const TW* tile, int64_t ld, typename Vec2<TW>::type (&a)[SOLVE_R]) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-        for (int e = 0; e < NV; ++e) {
-          s0 += (double)a0[e] * xs[k + e];
-          s1 += (double)a1[e] * xs[k + STEP + e];
-          s2 += (double)a2[e] * xs[k + 2 * STEP + e];
-          s3 += (double)a3[e] * xs[k + 3 * STEP + e];
-        }
-      }
-      for (; k < K; k += STEP) {
-        const VT a0 = *(const VT*)(row + k);
-#pragma unroll
-        for (int e = 0; e < NV; ++e) s0 += (double)a0[e] * xs[k + e];
-      }
-      const double s = wave_sum((s0 + s1) + (s2 + s3));
-      if (lane == 0) t[r] = v[K + r] - s;
-    }
-    __syncthreads();
-    const TW* Li = inv + (int64_t)i * TB * TB;
-    for (int r = wv; r < TB; r += SOLVE_NT / 64) {
-      double s = 0.0;
-      for (int c = lane; c <= r; c += 64) s += (double)Li[(int64_t)r * TB + c] * t[c];
-      s = wave_sum(s);
-      if (lane == 0) {
-        v[K + r] = s;
-        xs[K + r] = s;
-      }
-    }
-    __syncthreads();
-  }
+  for (int r = 0; r < SOLVE_R; ++r)
+    a[r] = *(const typename Vec2<TW>::type*)(tile + (int64_t)(wv * SOLVE_R + r) * ld + 2 * lane);
 }
 
-// backward, right-looking: x_i = L_ii^-T v_i, then v_{<i} -= L_{i,<i}^T x_i
-// (row panel i; each thread owns NV consecutive columns, rows streamed in order).
+// out[c] = sum_r a[r][c] x[r] over the 128 rows of the tile, for the threads c < 128
 template <typename TW>
-__device__ void bwd_solve(const TW* base, const TW* inv, double* v, int nt, double* xi, double* t) {
-  typedef typename Vec16<TW>::type VT;
-  constexpr int NV = Vec16<TW>::n;
-  const int tid = threadIdx.x;
-  for (int i = nt - 1; i >= 0; --i) {
-    if (tid < TB) t[tid] = v[i * TB + tid];
+__device__ inline double mul_t(const typename Vec2<TW>::type (&a)[SOLVE_R], const double* x, double* red) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+  for (int r = 0; r < SOLVE_R; ++r) {
+    const double xr = x[wv * SOLVE_R + r];
+    s0 += (double)a[r][0] * xr;
+    s1 += (double)a[r][1] * xr;
+  }
+  __syncthreads();
+  red[wv * TB + 2 * lane] = s0;
+  red[wv * TB + 2 * lane + 1] = s1;
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x < TB)
+#pragma unroll
+    for (int q = 0; q < SOLVE_W; ++q) s += red[q * TB + threadIdx.x];
+  return s;
+}
+
+// out[r] = sum_c a[r][c] x[c], for the threads r < 128
+template <typename TW>
+__device__ inline double mul_n(const typename Vec2<TW>::type (&a)[SOLVE_R], const double* x, double* red) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const double x0 = x[2 * lane], x1 = x[2 * lane + 1];
+  double v[SOLVE_R];
+#pragma unroll
+  for (int r = 0; r < SOLVE_R; ++r) v[r] = (double)a[r][0] * x0 + (double)a[r][1] * x1;
+  // halve the rows held per lane with each exchange: lane bit b keeps the rows with that bit
+#pragma unroll
+  for (int n = SOLVE_R / 2, o = 32; n >= 1; n >>= 1, o >>= 1) {
+    const bool hi = lane & o;
+#pragma unroll
+    for (int r = 0; r < n; ++r) {
+      const double give = hi ? v[r] : v[r + n], keep = hi ? v[r + n] : v[r];
+      v[r] = keep + __shfl_xor(give, o);
+    }
+  }
+  double s = v[0];
+#pragma unroll
+  for (int o = 64 / SOLVE_R / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  __syncthreads();
+  if ((lane & (64 / SOLVE_R - 1)) == 0) red[wv * SOLVE_R + lane / (64 / SOLVE_R)] = s;
+  __syncthreads();
+  return threadIdx.x < TB ? red[threadIdx.x] : 0.0;
+}
+
+// Step i of the solves with L^T (BWD, i = maxT .. 1: tile i is solved, tile i - 1
+// comes next) or with L (i = 0 .. maxT - 1: tile i - 1 is solved, tile i comes next).
+template <typename TW, bool BWD>
+__global__ __launch_bounds__(SOLVE_NT) void k_solve_step(WinVecArgs<TW> a, int i) {
+  __shared__ double xJ[TB], xW[TB];
+  __shared__ double red[SOLVE_W * TB];
+  typedef typename Vec2<TW>::type V2;
+  const int m = blockIdx.x, tid = threadIdx.x;
+  const WinTab& w = a.w;
+  const int T = w.T[m], tw = w.tw[m];
+  // the tile of the vector this workgroup updates, and whether there is a solved tile to subtract
+  const int tv = BWD ? i - 1 - (int)blockIdx.y : i + (int)blockIdx.y;
+  const int ts = BWD ? i : i - 1;
+  if (tv < 0 || tv >= T) return;
+  const bool upd = BWD ? i < T : i > 0, next = blockIdx.y == 0;
+  if (BWD && i > T) return;
+  if (!upd && !next) return;
+  const bool inW = tv < tw, updW = inW && (BWD ? i < tw : i > 0);
+  const TW* base = a.panels + w.panel[m];
+  double* vJ = a.vJ + w.vec[m] + (int64_t)tv * TB;
+  double* vW = a.vW + w.vec[m] + (int64_t)tv * TB;
+  V2 lt[SOLVE_R], li[SOLVE_R];
+  if (upd) {
+    const int tr = BWD ? ts : tv, tc = BWD ? tv : ts;
+    load_rows<TW>(base + jp_off(tr) + (int64_t)tc * TB, (int64_t)(tr + 1) * TB, lt);
+  }
+  if (next) load_rows<TW>(a.invs + w.inv[m] + (int64_t)tv * TB * TB, TB, li);
+  double rJ = 0.0, rW = 0.0;
+  if (tid < TB) {
+    rJ = vJ[tid];
+    if (inW) rW = vW[tid];
+  }
+  if (upd) {
+    const int64_t so = w.vec[m] + (int64_t)ts * TB;
+    if (tid < TB) {
+      xJ[tid] = a.vJ[so + tid];
+      if (updW) xW[tid] = a.vW[so + tid];
+    }
+    __syncthreads();
+    rJ -= BWD ? mul_t<TW>(lt, xJ, red) : mul_n<TW>(lt, xJ, red);
+    if (updW) rW -= BWD ? mul_t<TW>(lt, xW, red) : mul_n<TW>(lt, xW, red);
+  }
+  if (next) {
     __syncthreads();
     if (tid < TB) {
-      const TW* Li = inv + (int64_t)i * TB * TB;
-      double s0 = 0.0, s1 = 0.0;
-      int c = tid;
-      for (; c + 1 < TB; c += 2) {
-        s0 += (double)Li[(int64_t)c * TB + tid] * t[c];
-        s1 += (double)Li[(int64_t)(c + 1) * TB + tid] * t[c + 1];
-      }
-      for (; c < TB; ++c) s0 += (double)Li[(int64_t)c * TB + tid] * t[c];
-      xi[tid] = s0 + s1;
-      v[i * TB + tid] = s0 + s1;
+      xJ[tid] = rJ;
+      xW[tid] = rW;
     }
     __syncthreads();
-    const TW* P = base + jp_off(i);
-    const int64_t ld = (int64_t)(i + 1) * TB;
-    for (int col = tid * NV; col < i * TB; col += SOLVE_NT * NV) {
-      double acc[NV];
-#pragma unroll
-      for (int e = 0; e < NV; ++e) acc[e] = 0.0;
-#pragma unroll 4
-      for (int r = 0; r < TB; ++r) {
-        const VT a = *(const VT*)(P + (int64_t)r * ld + col);
-        const double x = xi[r];
-#pragma unroll
-        for (int e = 0; e < NV; ++e) acc[e] += (double)a[e] * x;
-      }
-#pragma unroll
-      for (int e = 0; e < NV; ++e) v[col + e] -= acc[e];
-    }
-    __syncthreads();
+    rJ = BWD ? mul_t<TW>(li, xJ, red) : mul_n<TW>(li, xJ, red);
+    if (inW) rW = BWD ? mul_t<TW>(li, xW, red) : mul_n<TW>(li, xW, red);
   }
-}
-
-template <typename TW, bool XS_LDS>
-__global__ __launch_bounds__(SOLVE_NT) void k_fwd(WinVecArgs<TW> a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double t[TB];
-  const int m = blockIdx.x;
-  const WinTab& w = a.w;
-  const int T = w.T[m], tw = w.tw[m];
-  const int64_t vo = w.vec[m];
-  const TW* base = a.panels + w.panel[m];
-  const TW* inv = a.invs + w.inv[m];
-  double* xsJ = XS_LDS ? reinterpret_cast<double*>(smem_raw) : a.vJ + vo;
-  fwd_solve<TW>(base, inv, a.vJ + vo, T, xsJ, t);
-  if (tw > 0) {
-    double* xsW = XS_LDS ? reinterpret_cast<double*>(smem_raw) : a.vW + vo;
-    fwd_solve<TW>(base, inv, a.vW + vo, tw, xsW, t);
+  if (tid < TB) {
+    vJ[tid] = rJ;
+    if (inW) vW[tid] = rW;
   }
-}
-
-template <typename TW>
-__global__ __launch_bounds__(SOLVE_NT) void k_bwd(WinVecArgs<TW> a) {
-  __shared__ double xi[TB];
-  __shared__ double t[TB];
-  const int m = blockIdx.x;
-  const WinTab& w = a.w;
-  const int T = w.T[m], tw = w.tw[m];
-  const int64_t vo = w.vec[m];
-  const TW* base = a.panels + w.panel[m];
-  const TW* inv = a.invs + w.inv[m];
-  bwd_solve<TW>(base, inv, a.vJ + vo, T, xi, t);
-  if (tw > 0) bwd_solve<TW>(base, inv, a.vW + vo, tw, xi, t);
 }
 
 // L_J^-1 (c_J - K_JS g) from the stored whitened right-hand sides:
@@ -281,37 +279,38 @@ __global__ __launch_bounds__(256) void k_axpy2(double* vJ, double* vW, const dou
   }
 }
 
-// h = V_X x: block (m, s-tile), thread k sums over the window's rows.
-__global__ __launch_bounds__(128) void k_h(HArgs a) {
-  const int m = blockIdx.x, kt = blockIdx.y, k = kt * TB + threadIdx.x;
+// h = V_X x, one workgroup per window and 64 columns of V: its 16 waves take every
+// 16th row and the partial sums are added in wave order.  Bound: one read of the
+// window's V rows.  With one thread walking all rows of a column the loads were a
+// serial chain: 68 -> 13 us at n=2048, 2.5 ms -> 0.36 ms at n=16384 with B=15.
+constexpr int H_W = 16;
+__global__ __launch_bounds__(64 * H_W) void k_h(HArgs a) {
+  __shared__ double red[2][H_W][64];
+  const int m = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int k = blockIdx.y * 64 + lane;
   const WinTab& w = a.w;
-  const int tw = w.tw[m];
-  const int64_t vo = w.vec[m];
-  const int64_t wl = w.wlen[m], dl = w.dlen[m];
-  const double* Vw = a.Vt + w.wstart[m] * a.sp + k;
-  const double* Vd = a.Vt + w.dstart[m] * a.sp + k;
-  double hj0 = 0.0, hj1 = 0.0, hw0 = 0.0, hw1 = 0.0;
-  int64_t r = 0;
-  for (; r + 1 < wl; r += 2) {
-    const double v0 = Vw[r * a.sp], v1 = Vw[(r + 1) * a.sp];
-    hj0 += v0 * a.xJ[vo + r];
-    hj1 += v1 * a.xJ[vo + r + 1];
-    hw0 += v0 * a.xW[vo + r];
-    hw1 += v1 * a.xW[vo + r + 1];
+  const int64_t vo = w.vec[m], wl = w.wlen[m], dl = w.dlen[m];
+  double hj = 0.0, hw = 0.0;
+  const double* V = a.Vt + w.wstart[m] * a.sp + k;
+#pragma unroll 4
+  for (int64_t r = wv; r < wl; r += H_W) {
+    const double v = V[r * a.sp];
+    hj += v * a.xJ[vo + r];
+    hw += v * a.xW[vo + r];
   }
-  for (; r < wl; ++r) {
-    const double v0 = Vw[r * a.sp];
-    hj0 += v0 * a.xJ[vo + r];
-    hw0 += v0 * a.xW[vo + r];
+  V = a.Vt + w.dstart[m] * a.sp + k;
+  const double* x = a.xJ + vo + (int64_t)w.tw[m] * TB;
+#pragma unroll 4
+  for (int64_t r = wv; r < dl; r += H_W) hj += V[r * a.sp] * x[r];
+  red[0][wv][lane] = hj;
+  red[1][wv][lane] = hw;
+  __syncthreads();
+  if (wv < 2) {
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < H_W; ++q) s += red[wv][q][lane];
+    (wv == 0 ? a.hJ : a.hW)[(int64_t)m * a.sp + k] = s;
   }
-  const int64_t o = vo + (int64_t)tw * TB;
-  for (r = 0; r + 1 < dl; r += 2) {
-    hj0 += Vd[r * a.sp] * a.xJ[o + r];
-    hj1 += Vd[(r + 1) * a.sp] * a.xJ[o + r + 1];
-  }
-  for (; r < dl; ++r) hj0 += Vd[r * a.sp] * a.xJ[o + r];
-  a.hJ[(int64_t)m * a.sp + k] = hj0 + hj1;
-  a.hW[(int64_t)m * a.sp + k] = hw0 + hw1;
 }
 
 template <typename TW>
@@ -320,15 +319,13 @@ void launch_ycp(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st) {
 }
 template <typename TW>
 void launch_fwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st) {
-  const size_t lds = sizeof(double) * (size_t)maxT * TB;
-  if (lds <= FWD_LDS_MAX)
-    hipLaunchKernelGGL((k_fwd<TW, true>), dim3(M), dim3(SOLVE_NT), lds, st, a);
-  else
-    hipLaunchKernelGGL((k_fwd<TW, false>), dim3(M), dim3(SOLVE_NT), 0, st, a);
+  for (int i = 0; i < maxT; ++i)
+    hipLaunchKernelGGL((k_solve_step<TW, false>), dim3(M, i > 0 ? maxT - i : 1), dim3(SOLVE_NT), 0, st, a, i);
 }
 template <typename TW>
-void launch_bwd(const WinVecArgs<TW>& a, int M, hipStream_t st) {
-  hipLaunchKernelGGL(k_bwd<TW>, dim3(M), dim3(SOLVE_NT), 0, st, a);
+void launch_bwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st) {
+  for (int i = maxT; i > 0; --i)
+    hipLaunchKernelGGL((k_solve_step<TW, true>), dim3(M, i < maxT ? i : 1), dim3(SOLVE_NT), 0, st, a, i);
 }
 void launch_gres(const GresArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(k_gres, dim3(1), dim3(256), sizeof(double) * (size_t)a.sp, st, a);
@@ -349,21 +346,13 @@ void launch_axpy2(double* vJ, double* vW, const double* xJ, const double* xW, do
   hipLaunchKernelGGL(k_axpy2, dim3(nb), dim3(256), 0, st, vJ, vW, xJ, xW, alpha, nvec);
 }
 void launch_h(const HArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_h, dim3(a.M, a.sp / TB), dim3(TB), 0, st, a);
+  hipLaunchKernelGGL(k_h, dim3(a.M, a.sp / 64), dim3(64 * H_W), 0, st, a);
 }
-hipError_t vecsolve_init() {
-  for (const void* f : {(const void*)k_fwd<double, true>, (const void*)k_fwd<float, true>}) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FWD_LDS_MAX);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
 template void launch_ycp<double>(const WinVecArgs<double>&, int, int, hipStream_t);
 template void launch_ycp<float>(const WinVecArgs<float>&, int, int, hipStream_t);
 template void launch_fwd<double>(const WinVecArgs<double>&, int, int, hipStream_t);
 template void launch_fwd<float>(const WinVecArgs<float>&, int, int, hipStream_t);
-template void launch_bwd<double>(const WinVecArgs<double>&, int, hipStream_t);
-template void launch_bwd<float>(const WinVecArgs<float>&, int, hipStream_t);
+template void launch_bwd<double>(const WinVecArgs<double>&, int, int, hipStream_t);
+template void launch_bwd<float>(const WinVecArgs<float>&, int, int, hipStream_t);
 
 }  // namespace lma

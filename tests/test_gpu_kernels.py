@@ -44,3 +44,12 @@ def test_diagonal_tile_block_edges(lib, n, s):
     s = min(s, n)
     p = synth.make_random(seed=100 + n, n=n, d=2, M=1, s=s, n_u=9, B=0, uneven=(n, n), sn2=0.05)
     check_fit(lib, p)
+
+
+# windows from one to a dozen tiles in one launch of the vector solves, some with an
+# empty separator; forward and backward (the mixed path runs both; its bar is 1e-4)
+@pytest.mark.parametrize("precision,bar", [("fp64", BAR), ("mixed", 1e-4)])
+@pytest.mark.parametrize("B", [0, 1, 4])
+def test_vector_solves_of_unequal_windows(lib, B, precision, bar):
+    p = synth.make_random(seed=61, n=1500, d=3, M=5, s=70, n_u=60, B=B, uneven=(20, 700), sn2=0.05)
+    check_fit(lib, p, bar=bar, precision=precision)
