@@ -10,21 +10,30 @@ namespace lma {
 // ---------------------------------------------------------------------------
 // update: C_ij = K_ij - V_i V_j^T - sum_{k<j} L_ik L_jk^T for every item (p, i)
 // ---------------------------------------------------------------------------
-template <typename T, bool MIXED>
+// SUB: MFMA sub-tiles per wave and side.  4: a workgroup computes the whole 128 x 128
+// tile; 2 and 1: one of its 4 (16) pieces of 64 x 64 (32 x 32).
+template <typename T, bool MIXED, int SUB>
 __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
+  constexpr int WS = 16 * SUB, QS = 2 * WS, NQ = TB / QS;  // rows of a wave, of a piece; pieces per side
   // covariance tile and V-part precision: float64 when T is double or MIXED
   typedef typename std::conditional<MIXED, double, T>::type TK;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
-  if (logical >= a.nitems) return;
-  const WorkItem it = a.items[logical];
+  if (logical >= a.nitems * NQ * NQ) return;
+  const WorkItem it = a.items[logical / (NQ * NQ)];
   const ProbDesc pd = a.pd[it.p];
   const RowTile<T> ri = a.rt[pd.first + it.tile];
   const RowTile<T> rj = a.rt[pd.first + a.j];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wr = w >> 1, wc = w & 1;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int q0r = (logical / NQ) % NQ * QS, q0c = logical % NQ * QS;  // the piece's first row and column
+  const bool diag = ri.is_j && (it.tile == a.j);
+  if (q0r >= ri.nstore) return;         // no row of the piece is stored
+  if (diag && q0c > q0r) return;        // above the diagonal: not read by the diagonal tile's kernel
+  const int r0 = q0r + (w >> 1) * WS, c0 = q0c + (w & 1) * WS;  // the wave's
+  const bool real = q0r < ri.nvalid && q0c < rj.nvalid;         // else padding only
 
-  typename Mfma<TK>::acc accv[4][4];   // V_i V_j^T
-  typename Mfma<T>::acc accl[4][4];    // sum_k L_ik L_jk^T (aliases accv when not MIXED)
+  typename Mfma<TK>::acc accv[SUB][SUB];   // V_i V_j^T
+  typename Mfma<T>::acc accl[SUB][SUB];    // sum_k L_ik L_jk^T (aliases accv when not MIXED)
   const bool band = ri.src == SRC_BAND;    // V part already inside the band entries
   const bool tband = ri.src == SRC_TBAND;  // likewise for test rows
   if (band || tband) {
@@ -35,36 +44,36 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
     // are masked to zero), and the accumulators are started through an MFMA, as
     // in zero_acc, so that they stay in their register file.
     const int nvr = ri.nvalid, nvc = rj.nvalid;
-    int64_t rowp[4][4], rowb[4][4], colq[4], colb[4];
+    int64_t rowp[SUB][4], rowb[SUB][4], colq[SUB], colb[SUB];
 #pragma unroll
-    for (int cs = 0; cs < 4; ++cs) {
-      const int col = wc * 64 + cs * 16 + (lane & 15);
+    for (int cs = 0; cs < SUB; ++cs) {
+      const int col = c0 + cs * 16 + (lane & 15);
       colq[cs] = rj.pt0 + (col < nvc ? col : nvc - 1);
       colb[cs] = tband ? 0 : a.brow[colq[cs]];
     }
 #pragma unroll
-    for (int rs = 0; rs < 4; ++rs)
+    for (int rs = 0; rs < SUB; ++rs)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = wr * 64 + rs * 16 + Mfma<TK>::row(lane, v);
+        const int row = r0 + rs * 16 + Mfma<TK>::row(lane, v);
         rowp[rs][v] = ri.pt0 + (row < nvr ? row : nvr - 1);
         rowb[rs][v] = a.brow[rowp[rs][v]];
       }
 #pragma unroll
-    for (int rs = 0; rs < 4; ++rs)
+    for (int rs = 0; rs < SUB; ++rs)
 #pragma unroll
-      for (int cs = 0; cs < 4; ++cs) {
-        typename Mfma<TK>::acc r0;
+      for (int cs = 0; cs < SUB; ++cs) {
+        typename Mfma<TK>::acc start;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int row = wr * 64 + rs * 16 + Mfma<TK>::row(lane, v);
-          const int col = wc * 64 + cs * 16 + (lane & 15);
+          const int row = r0 + rs * 16 + Mfma<TK>::row(lane, v);
+          const int col = c0 + cs * 16 + (lane & 15);
           const int64_t p = rowp[rs][v], q = colq[cs];
           const int64_t e = (tband || q <= p) ? rowb[rs][v] + q : colb[cs] + p;
           const TK kv = (TK)a.band[e];
-          r0[v] = (row < nvr && col < nvc) ? -kv : TK(0);
+          start[v] = (row < nvr && col < nvc) ? -kv : TK(0);
         }
-        accv[rs][cs] = Mfma<TK>::op(TK(0), TK(0), r0);
+        accv[rs][cs] = Mfma<TK>::op(TK(0), TK(0), start);
       }
   } else {
     zero_acc<TK>(accv);
@@ -72,59 +81,58 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
   if constexpr (MIXED) zero_acc<T>(accl);
   const TK* vi = MIXED ? (const TK*)ri.vt64 : (const TK*)ri.vt;
   const TK* vj = MIXED ? (const TK*)rj.vt64 : (const TK*)rj.vt;
-  if (!band && !tband && vi != nullptr && vj != nullptr && a.vlen > 0)
-    wave_gemm<TK, TK>(accv, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, 0, a.vlen, wr * 64, wc * 64, lane);
+  if (real && !band && !tband && vi != nullptr && vj != nullptr && a.vlen > 0)
+    wave_gemm<TK, TK>(accv, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, 0, a.vlen, r0, c0, lane);
   // factor columns kb .. j-1 (a row is zero left of its kbeg)
   const int kb = ri.kbeg > rj.kbeg ? ri.kbeg : rj.kbeg;
-  if (a.j > kb) {
+  if (real && a.j > kb) {
     const T* pa = ri.panel + (int64_t)(kb - ri.kbeg) * TB;
     const T* pb = rj.panel + (int64_t)(kb - rj.kbeg) * TB;
     if constexpr (MIXED)  // float32 products, sums folded into the float64 accumulators
-      wave_gemm_fold(accl, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, 0, (a.j - kb) * TB, wr * 64, wc * 64, lane,
+      wave_gemm_fold(accl, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, 0, (a.j - kb) * TB, r0, c0, lane,
                      accv);
     else
-      wave_gemm<T, T>(accv, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, 0, (a.j - kb) * TB, wr * 64, wc * 64, lane);
+      wave_gemm<T, T>(accv, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, 0, (a.j - kb) * TB, r0, c0, lane);
   }
 
   const int d = a.d;
-  TK* xr = reinterpret_cast<TK*>(smem_raw);  // [d][TB] row-side coordinates
-  TK* xc = xr + d * TB;                      // [d][TB] column-side coordinates
+  TK* xr = reinterpret_cast<TK*>(smem_raw);  // [d][QS] row-side coordinates
+  TK* xc = xr + d * QS;                      // [d][QS] column-side coordinates
   const bool kern = ri.src == SRC_KERNEL;
   if (kern) {
     const TK* xsi = MIXED ? (const TK*)ri.xs64 : (const TK*)ri.xs;
     const TK* xsj = MIXED ? (const TK*)rj.xs64 : (const TK*)rj.xs;
-    for (int idx = tid; idx < TB * d; idx += NT) {
+    for (int idx = tid; idx < QS * d; idx += NT) {
       const int r = idx / d, t = idx - r * d;
-      xr[t * TB + r] = r < ri.nvalid ? xsi[(int64_t)r * d + t] : TK(0);
-      xc[t * TB + r] = r < rj.nvalid ? xsj[(int64_t)r * d + t] : TK(0);
+      xr[t * QS + r] = q0r + r < ri.nvalid ? xsi[(int64_t)(q0r + r) * d + t] : TK(0);
+      xc[t * QS + r] = q0c + r < rj.nvalid ? xsj[(int64_t)(q0c + r) * d + t] : TK(0);
     }
   }
   __syncthreads();
-  const bool diag = ri.is_j && (it.tile == a.j);
   const TK sf2 = (TK)a.sf2, sn2 = (TK)a.sn2;
   T* out = ri.panel + (int64_t)(a.j - ri.kbeg) * TB;
   const bool ident = ri.src == SRC_IDENT;
   const bool ident_here = ident && ri.kbeg == a.j;
   // squared distances of the lane's 64 entries, one coordinate at a time
-  TK sq[4][4][4];
+  TK sq[SUB][SUB][4];
 #pragma unroll
-  for (int rs = 0; rs < 4; ++rs)
+  for (int rs = 0; rs < SUB; ++rs)
 #pragma unroll
-    for (int cs = 0; cs < 4; ++cs)
+    for (int cs = 0; cs < SUB; ++cs)
 #pragma unroll
       for (int v = 0; v < 4; ++v) sq[rs][cs][v] = TK(0);
-  if (kern) {
+  if (kern && real) {
     for (int t = 0; t < d; ++t) {
-      TK cv[4];
+      TK cv[SUB];
 #pragma unroll
-      for (int cs = 0; cs < 4; ++cs) cv[cs] = xc[t * TB + wc * 64 + cs * 16 + (lane & 15)];
+      for (int cs = 0; cs < SUB; ++cs) cv[cs] = xc[t * QS + c0 - q0c + cs * 16 + (lane & 15)];
 #pragma unroll
-      for (int rs = 0; rs < 4; ++rs)
+      for (int rs = 0; rs < SUB; ++rs)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const TK rv = xr[t * TB + wr * 64 + rs * 16 + Mfma<TK>::row(lane, v)];
+          const TK rv = xr[t * QS + r0 - q0r + rs * 16 + Mfma<TK>::row(lane, v)];
 #pragma unroll
-          for (int cs = 0; cs < 4; ++cs) {
+          for (int cs = 0; cs < SUB; ++cs) {
             const TK df = rv - cv[cs];
             sq[rs][cs][v] += df * df;
           }
@@ -132,13 +140,13 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
     }
   }
 #pragma unroll
-  for (int rs = 0; rs < 4; ++rs) {
+  for (int rs = 0; rs < SUB; ++rs) {
 #pragma unroll
-    for (int cs = 0; cs < 4; ++cs) {
+    for (int cs = 0; cs < SUB; ++cs) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = wr * 64 + rs * 16 + Mfma<TK>::row(lane, v);
-        const int col = wc * 64 + cs * 16 + (lane & 15);
+        const int row = r0 + rs * 16 + Mfma<TK>::row(lane, v);
+        const int col = c0 + cs * 16 + (lane & 15);
         TK kv = TK(0);
         if (ident) {
           kv = (ident_here && row == col) ? TK(1) : TK(0);  // exact at padding too
@@ -172,28 +180,35 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
 // ---------------------------------------------------------------------------
 // trsm: L_ij = C_ij L_jj^-T (in place) for every item (p, i), i != j
 // ---------------------------------------------------------------------------
-template <typename T>
+// The inverse is lower triangular, so the sum for columns [c0, c0 + n) ends at
+// c0 + n.  WR waves stand above each other: 2, a workgroup takes the 128 x 128 tile
+// (4 x 4 sub-tiles per wave); 1, it takes 32 rows of it (2 x 2 per wave).  Rows are
+// never split between workgroups, so the tile is replaced in place.
+template <typename T, int WR>
 __global__ __launch_bounds__(NT) void k_trsm(StepArgs<T> a) {
+  constexpr int SUB = 2 * WR, WS = 16 * SUB, WC = 4 / WR, RS = WR * WS, NP = TB / RS;
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
-  if (logical >= a.nitems) return;
-  const WorkItem it = a.items[logical];
+  if (logical >= a.nitems * NP) return;
+  const WorkItem it = a.items[logical / NP];
   const ProbDesc pd = a.pd[it.p];
   const RowTile<T> ri = a.rt[pd.first + it.tile];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wr = w >> 1, wc = w & 1;
+  if (logical % NP * RS >= ri.nstore) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r0 = logical % NP * RS + w / WC * WS, c0 = w % WC * WS;
   T* C = ri.panel + (int64_t)(a.j - ri.kbeg) * TB;
   const T* Li = a.invdiag + pd.invdiag_off + (int64_t)a.j * TB * TB;
-  typename Mfma<T>::acc acc[4][4];
+  typename Mfma<T>::acc acc[SUB][SUB];
   zero_acc<T>(acc);
-  wave_gemm<T, T>(acc, C, ri.ld, ri.nstore, Li, TB, TB, 0, TB, wr * 64, wc * 64, lane);
+  wave_gemm<T, T>(acc, C, ri.ld, ri.nstore, Li, TB, TB, 0, c0 + WS, r0, c0, lane);
   __syncthreads();  // every wave has consumed its reads of C before anyone overwrites it
 #pragma unroll
-  for (int rs = 0; rs < 4; ++rs)
+  for (int rs = 0; rs < SUB; ++rs)
 #pragma unroll
-    for (int cs = 0; cs < 4; ++cs)
+    for (int cs = 0; cs < SUB; ++cs)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = wr * 64 + rs * 16 + Mfma<T>::row(lane, v);
-        const int col = wc * 64 + cs * 16 + (lane & 15);
+        const int row = r0 + rs * 16 + Mfma<T>::row(lane, v);
+        const int col = c0 + cs * 16 + (lane & 15);
         if (row < ri.nstore) C[(int64_t)row * ri.ld + col] = acc[rs][cs][v];
       }
 }
@@ -201,40 +216,43 @@ __global__ __launch_bounds__(NT) void k_trsm(StepArgs<T> a) {
 // ---------------------------------------------------------------------------
 // batched float64-accumulating tile GEMM
 // ---------------------------------------------------------------------------
-template <typename T>
+template <typename T, int SUB>
 __global__ __launch_bounds__(NT) void k_tile_gemm(const GemmTerm<T>* __restrict__ terms,
                                                   const GemmOut* __restrict__ outs, int nout) {
+  constexpr int WS = 16 * SUB, QS = 2 * WS, NQ = TB / QS;  // as in k_update
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
-  if (logical >= nout) return;
-  const GemmOut o = outs[logical];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wr = w >> 1, wc = w & 1;
-  typename Mfma<double>::acc acc[4][4];
+  if (logical >= nout * NQ * NQ) return;
+  const GemmOut o = outs[logical / (NQ * NQ)];
+  const int q0r = (logical / NQ) % NQ * QS, q0c = logical % NQ * QS;
+  if (q0r >= o.rows || q0c >= o.cols) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r0 = q0r + (w >> 1) * WS, c0 = q0c + (w & 1) * WS;
+  typename Mfma<double>::acc acc[SUB][SUB];
   zero_acc<double>(acc);
   for (int t = o.t0; t < o.t1; ++t) {
     if (t == o.tneg && t > o.t0) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < SUB; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = -acc[a][b];
+        for (int b = 0; b < SUB; ++b) acc[a][b] = -acc[a][b];
     }
     const GemmTerm<T> tm = terms[t];
-    wave_gemm<T, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, wr * 64, wc * 64,
-                         lane);
+    wave_gemm<T, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, r0, c0, lane);
   }
   if (o.tneg == o.t1 && o.t1 > o.t0) {  // only subtracted terms
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < SUB; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = -acc[a][b];
+      for (int b = 0; b < SUB; ++b) acc[a][b] = -acc[a][b];
   }
 #pragma unroll
-  for (int rs = 0; rs < 4; ++rs)
+  for (int rs = 0; rs < SUB; ++rs)
 #pragma unroll
-    for (int cs = 0; cs < 4; ++cs)
+    for (int cs = 0; cs < SUB; ++cs)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = wr * 64 + rs * 16 + Mfma<double>::row(lane, v);
-        const int col = wc * 64 + cs * 16 + (lane & 15);
+        const int row = r0 + rs * 16 + Mfma<double>::row(lane, v);
+        const int col = c0 + cs * 16 + (lane & 15);
         if (row < o.rows && col < o.cols) {
           double* q = o.out + (int64_t)row * o.ld + col;
           double r = o.alpha * acc[rs][cs][v];
@@ -313,28 +331,70 @@ __global__ __launch_bounds__(NT) void k_band(BandArgs<T> a) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+constexpr int NCU = 256;  // compute units
 static inline int pad8(int n) { return ((n + 7) / 8) * 8; }
+
+// Pieces per tile side (1, 2 or 4) of a launch of n whole tiles with products of
+// length k.  A whole tile gives its products the most reuse but only one workgroup
+// fits on a CU, so n tiles take ceil(n / 256) turns.  Measured (k_update, float64, in
+// units of one turn): 4 pieces per tile take 0.48 per turn of 256 of them (two fit
+// on a CU, each at a lower rate), 16 pieces 0.245.  So cutting pays while the pieces
+// fit in one (n <= 16, 32 .. 64) or two (n <= 128) turns: n = 8 1763 / 864 / 432 us for
+// 1 / 4 / 16 pieces at k = 16000, n = 56 1576 / 751 / 1469, n = 120 1474 / 1406 / 2770,
+// n = 136 1289 / 1853 / 2731.  With k <= 256 the covariance and the stores are most of
+// a tile's time and more workgroups on a CU overlap them: n = 1032, k = 0 150 / 80 / 81 us,
+// k = 128 235 / 195 / 266, k = 256 324 / 310 / 470, k = 384 397 / 427 / 686.
+static inline int split_of(int64_t n, int64_t k) {
+  if (n <= 16 || (k == 0 && n <= NCU)) return 4;
+  return n <= NCU / 2 || k <= 256 ? 2 : 1;
+}
+
+template <typename T, bool MIXED>
+static void update_pieces(StepArgs<T> a, int64_t i0, int64_t n, int split, hipStream_t st) {
+  if (n <= 0) return;
+  a.items += i0;
+  a.nitems = (int32_t)n;
+  const size_t lds = 2 * (size_t)a.d * (TB / split) * (MIXED ? sizeof(double) : sizeof(T));
+  const dim3 grid(pad8(a.nitems * split * split));
+  switch (split) {
+    case 1: hipLaunchKernelGGL((k_update<T, MIXED, 4>), grid, dim3(NT), lds, st, a); break;
+    case 2: hipLaunchKernelGGL((k_update<T, MIXED, 2>), grid, dim3(NT), lds, st, a); break;
+    default: hipLaunchKernelGGL((k_update<T, MIXED, 1>), grid, dim3(NT), lds, st, a);
+  }
+}
+
+template <typename T, bool MIXED>
+static void update_launches(const StepArgs<T>& a, hipStream_t st) {
+  const int64_t n = a.nitems, k = (int64_t)a.j * TB + (a.band ? 0 : a.vlen);
+  const int split = split_of(n, k);
+  // up to 64 tiles left over from full turns: a launch of their own, in pieces that fit
+  // in half a turn
+  const int64_t rest = split == 1 && n % NCU <= NCU / 4 ? n % NCU : 0;
+  update_pieces<T, MIXED>(a, 0, n - rest, split, st);
+  update_pieces<T, MIXED>(a, n - rest, rest, split_of(rest, k), st);
+}
 
 template <typename T>
 void launch_update(const StepArgs<T>& a, bool mixed, hipStream_t st) {
   if (a.nitems <= 0) return;
-  if constexpr (std::is_same<T, float>::value) {
+  if constexpr (std::is_same<T, float>::value)
     if (mixed) {
-      const size_t lds = 2 * (size_t)a.d * TB * sizeof(double);
-      hipLaunchKernelGGL((k_update<T, true>), dim3(pad8(a.nitems)), dim3(NT), lds, st, a);
+      update_launches<T, true>(a, st);
       return;
     }
-  }
-  {
-    const size_t lds = 2 * (size_t)a.d * TB * sizeof(T);
-    hipLaunchKernelGGL((k_update<T, false>), dim3(pad8(a.nitems)), dim3(NT), lds, st, a);
-  }
+  update_launches<T, false>(a, st);
 }
 
 template <typename T>
 void launch_trsm(const StepArgs<T>& a, hipStream_t st) {
   if (a.nitems <= 0) return;
-  hipLaunchKernelGGL(k_trsm<T>, dim3(pad8(a.nitems)), dim3(NT), 0, st, a);
+  // 32 rows per workgroup: measured 22 -> 10 us for n <= 64 tiles, 25 -> 17 at n = 128;
+  // from there on it is slower in float64 (26 -> 32 us at n = 224), and faster in
+  // float32 while its lower occupancy shows (n = 544 39 -> 37, n = 1680 97 -> 92, n = 2000 109 -> 123)
+  if (a.nitems > (std::is_same<T, float>::value ? 1200 : NCU / 2))
+    hipLaunchKernelGGL((k_trsm<T, 2>), dim3(pad8(a.nitems)), dim3(NT), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_trsm<T, 1>), dim3(pad8(4 * a.nitems)), dim3(NT), 0, st, a);
 }
 
 template <typename T>
@@ -346,20 +406,28 @@ void launch_band(const BandArgs<T>& a, hipStream_t st) {
 template <typename T>
 void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, hipStream_t st) {
   if (nout <= 0) return;
-  hipLaunchKernelGGL(k_tile_gemm<T>, dim3(pad8(nout)), dim3(NT), 0, st, terms, outs, nout);
+  // measured, whole / 4 / 16 pieces: float64 n = 48 204 / 75 / 110 us, n = 112 178 / 128 / 204,
+  // n = 176 80 / 94 / 129; float32 operands leave the registers for three workgroups of
+  // pieces on a CU: n = 240 863 / 755 / 893, n = 14240 8071 / 6637 / 11110
+  if (nout <= 16)
+    hipLaunchKernelGGL((k_tile_gemm<T, 1>), dim3(pad8(16 * nout)), dim3(NT), 0, st, terms, outs, nout);
+  else if (nout <= NCU / 2 || std::is_same<T, float>::value)
+    hipLaunchKernelGGL((k_tile_gemm<T, 2>), dim3(pad8(4 * nout)), dim3(NT), 0, st, terms, outs, nout);
+  else
+    hipLaunchKernelGGL((k_tile_gemm<T, 4>), dim3(pad8(nout)), dim3(NT), 0, st, terms, outs, nout);
 }
 
 // Raise the dynamic-LDS limit of the kernels that need more than the default.
 hipError_t engine_init() {
   hipError_t e = diag_init();
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)k_update<double, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  e = hipFuncSetAttribute((const void*)k_update<double, false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(double)));
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)k_update<float, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  e = hipFuncSetAttribute((const void*)k_update<float, true, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(double)));
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)k_update<float, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  e = hipFuncSetAttribute((const void*)k_update<float, false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(float)));
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)k_band<double>, hipFuncAttributeMaxDynamicSharedMemorySize,

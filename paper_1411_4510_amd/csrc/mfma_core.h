@@ -2,7 +2,10 @@
 // contraction kernels (gfx950, wave64).
 //
 // A workgroup of 4 wave64 computes one 128x128 output tile; wave (wr, wc)
-// owns the 64x64 quadrant (wr, wc) as 4x4 MFMA 16x16 sub-tiles.  Operand
+// owns the 64x64 quadrant (wr, wc) as 4x4 MFMA 16x16 sub-tiles.  Where a launch
+// has too few tiles to fill the chip the tile is cut into 64x64 or 32x32 pieces, a
+// workgroup each, and a wave owns 2x2 sub-tiles or one.  Every element sums its
+// products in the same order in all forms.  Operand
 // fragments are read straight from HBM/L2 in the MFMA 16x16x4 input layout
 // (lane l supplies row l%16 and four consecutive k values starting at
 // 4*(l/16)); the four MFMA k-steps of a 16-wide k chunk consume those four
@@ -75,43 +78,46 @@ __device__ inline int xcd_logical(int bid, int nb) {
 // the thousands of k of a late column step loses accuracy linearly in k (about 10x a
 // blocked float32 Cholesky at k ~ 3000); chains of 144 are more accurate than one.
 constexpr int FOLD_ITERS = 3;
-template <typename Tin, typename Tc, bool PERMA, int PF, bool FOLD>
-__device__ __forceinline__ void wave_gemm_impl(typename Mfma<Tc>::acc (&acc)[4][4],
+template <typename Tin, typename Tc, bool PERMA, int PF, bool FOLD, int RA, int RB>
+__device__ __forceinline__ void wave_gemm_impl(typename Mfma<Tc>::acc (&acc)[RA][RB],
                                                const Tin* __restrict__ A, int64_t lda, int anr,
                                                const Tin* __restrict__ Bm, int64_t ldb, int bnr,
                                                int k0, int k1, int arow0, int brow0, int lane,
-                                               dv4 (&fold)[4][4]) {
+                                               dv4 (&fold)[RA][RB]) {
   static_assert(!FOLD || (PERMA && std::is_same<Tc, float>::value), "folding needs the float64 output layout");
   typedef typename V4<Tin>::type vin;
   const int r16 = lane & 15, kq = (lane >> 4) << 2;
-  const Tin* pa[4];
-  const Tin* pb[4];
+  const Tin* pa[RA];
+  const Tin* pb[RB];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < RA; ++t) {
     const int ra = arow0 + t * 16 + (PERMA ? ((r16 >> 2) | ((r16 & 3) << 2)) : r16);
     pa[t] = A + (int64_t)(ra < anr ? ra : 0) * lda + k0 + kq;
+  }
+#pragma unroll
+  for (int t = 0; t < RB; ++t) {
     const int rb = brow0 + t * 16 + r16;
     pb[t] = Bm + (int64_t)(rb < bnr ? rb : 0) * ldb + k0 + kq;
   }
   const int nc = (k1 - k0) >> 4;
   if (nc <= 0) return;
-  vin sa[PF + 1][4], sb[PF + 1][4];
+  vin sa[PF + 1][RA], sb[PF + 1][RB];
   // chunk x lives in slot x % (PF+1)
 #define LMA_LOAD_CHUNK(X, SLOT)                                \
   {                                                            \
     const int off_ = (X) << 4;                                 \
     const int slot_ = (SLOT);                                  \
-    _Pragma("unroll") for (int u_ = 0; u_ < 4; ++u_) {         \
+    _Pragma("unroll") for (int u_ = 0; u_ < RA; ++u_)          \
       sa[slot_][u_] = *(const vin*)(pa[u_] + off_);            \
+    _Pragma("unroll") for (int u_ = 0; u_ < RB; ++u_)          \
       sb[slot_][u_] = *(const vin*)(pb[u_] + off_);            \
-    }                                                          \
   }
 #define LMA_MMA_SLOT(SLOT)                                                                 \
   {                                                                                        \
     const int slot_ = (SLOT);                                                              \
     _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                        \
-      _Pragma("unroll") for (int ra = 0; ra < 4; ++ra) {                                   \
-        _Pragma("unroll") for (int rb = 0; rb < 4; ++rb) {                                 \
+      _Pragma("unroll") for (int ra = 0; ra < RA; ++ra) {                                  \
+        _Pragma("unroll") for (int rb = 0; rb < RB; ++rb) {                                \
           acc[ra][rb] = Mfma<Tc>::op((Tc)sa[slot_][ra][e], (Tc)sb[slot_][rb][e], acc[ra][rb]); \
         }                                                                                  \
       }                                                                                    \
@@ -119,8 +125,8 @@ __device__ __forceinline__ void wave_gemm_impl(typename Mfma<Tc>::acc (&acc)[4][
   }
 #define LMA_FOLD()                                                                    \
   if constexpr (FOLD) {                                                              \
-    _Pragma("unroll") for (int a_ = 0; a_ < 4; ++a_) {                               \
-      _Pragma("unroll") for (int b_ = 0; b_ < 4; ++b_) {                             \
+    _Pragma("unroll") for (int a_ = 0; a_ < RA; ++a_) {                              \
+      _Pragma("unroll") for (int b_ = 0; b_ < RB; ++b_) {                            \
         _Pragma("unroll") for (int v_ = 0; v_ < 4; ++v_) {                           \
           fold[a_][b_][v_] += (double)acc[a_][b_][v_];                               \
           acc[a_][b_][v_] = Tc(0);                                                   \
@@ -161,33 +167,38 @@ __device__ __forceinline__ void wave_gemm_impl(typename Mfma<Tc>::acc (&acc)[4][
 #undef LMA_FOLD
 }
 
-template <typename Tin, typename Tc, bool PERMA = false, int PF = 2>
-__device__ __forceinline__ void wave_gemm(typename Mfma<Tc>::acc (&acc)[4][4],
+// chunks in flight: a wave of fewer sub-tiles has fewer products per chunk to cover
+// the latency of the next ones, and registers to spare
+constexpr int pf_of(int sub) { return sub >= 4 ? 2 : sub == 2 ? 3 : 5; }
+
+template <typename Tin, typename Tc, int RA, int RB>
+__device__ __forceinline__ void wave_gemm(typename Mfma<Tc>::acc (&acc)[RA][RB],
                                           const Tin* __restrict__ A, int64_t lda, int anr,
                                           const Tin* __restrict__ Bm, int64_t ldb, int bnr,
                                           int k0, int k1, int arow0, int brow0, int lane) {
-  dv4 unused[4][4];
-  wave_gemm_impl<Tin, Tc, PERMA, PF, false>(acc, A, lda, anr, Bm, ldb, bnr, k0, k1, arow0, brow0, lane, unused);
+  dv4 unused[RA][RB];
+  wave_gemm_impl<Tin, Tc, false, pf_of(RA > RB ? RA : RB), false>(acc, A, lda, anr, Bm, ldb, bnr, k0, k1, arow0, brow0,
+                                                                 lane, unused);
 }
 
 // float32 products (PERMA layout) with the sums folded into the float64 accumulators fold
-template <int PF = 2>
-__device__ __forceinline__ void wave_gemm_fold(fv4 (&acc)[4][4], const float* __restrict__ A, int64_t lda, int anr,
+template <int RA, int RB>
+__device__ __forceinline__ void wave_gemm_fold(fv4 (&acc)[RA][RB], const float* __restrict__ A, int64_t lda, int anr,
                                                const float* __restrict__ Bm, int64_t ldb, int bnr, int k0, int k1,
-                                               int arow0, int brow0, int lane, dv4 (&fold)[4][4]) {
-  wave_gemm_impl<float, float, true, PF, true>(acc, A, lda, anr, Bm, ldb, bnr, k0, k1, arow0, brow0, lane, fold);
+                                               int arow0, int brow0, int lane, dv4 (&fold)[RA][RB]) {
+  wave_gemm_impl<float, float, true, 2, true>(acc, A, lda, anr, Bm, ldb, bnr, k0, k1, arow0, brow0, lane, fold);
 }
 
 // Accumulators start as the result of an MFMA of zero operands (exactly +0):
 // started from constant zeros, the compiler keeps the loop-carried accumulators
 // of a k loop in vector registers and copies all of them into the accumulation
 // registers and back on every iteration; an MFMA result stays in place.
-template <typename Tc>
-__device__ inline void zero_acc(typename Mfma<Tc>::acc (&acc)[4][4]) {
+template <typename Tc, int RA, int RB>
+__device__ inline void zero_acc(typename Mfma<Tc>::acc (&acc)[RA][RB]) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < RA; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = Mfma<Tc>::op(Tc(0), Tc(0), (typename Mfma<Tc>::acc){Tc(0), Tc(0), Tc(0), Tc(0)});
+    for (int b = 0; b < RB; ++b) acc[a][b] = Mfma<Tc>::op(Tc(0), Tc(0), (typename Mfma<Tc>::acc){Tc(0), Tc(0), Tc(0), Tc(0)});
 }
 
 

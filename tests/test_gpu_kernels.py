@@ -53,3 +53,14 @@ def test_diagonal_tile_block_edges(lib, n, s):
 def test_vector_solves_of_unequal_windows(lib, B, precision, bar):
     p = synth.make_random(seed=61, n=1500, d=3, M=5, s=70, n_u=60, B=B, uneven=(20, 700), sn2=0.05)
     check_fit(lib, p, bar=bar, precision=precision)
+
+
+# launches of few tiles run in pieces of 64 x 64 and 32 x 32: windows of 1 to 16 tiles
+# (16 and fewer tiles per launch, up to 128, more), pieces of padding only (blocks of
+# 130 and 33 points), test tiles of a few rows
+@pytest.mark.parametrize("precision,bar", [("fp64", BAR), ("mixed", 1e-4)])
+@pytest.mark.parametrize("n,M,B,s,n_u", [(33, 1, 0, 7, 3), (130, 1, 0, 33, 200), (520, 4, 3, 130, 70),
+                                         (1600, 8, 2, 260, 333), (4200, 25, 4, 97, 31)])
+def test_pieces_of_tiles(lib, n, M, B, s, n_u, precision, bar):
+    p = synth.make_random(seed=n, n=n, d=4, M=M, s=s, n_u=n_u, B=B, uneven=(max(1, n // M - 15), n // M + 15), sn2=0.05)
+    check_fit(lib, p, bar=bar, precision=precision)
