@@ -6,15 +6,17 @@
 // each of its point's coordinates once per pass.  Each distance is summed over
 // the coordinates in increasing order with separately rounded products and
 // sums (contraction into fused multiply-adds is switched off), so the result
-// is the same bit for bit as any plain evaluation in that order.
+// is the same bit for bit as any plain evaluation in that order.  With few points
+// (SPLIT_N) that is less than a workgroup per CU or a few, so the four waves of a
+// workgroup take the same 64 points and a quarter of the passes each, and the
+// smallest (distance, index) of the four wins.
 //
 // Centre update: the points are cut into chunks of 4096 consecutive indices.
-// One thread per (chunk, centre, coordinate) walks its chunk in increasing
-// index and adds the coordinate of the points with its label (the label read
-// is wave-uniform); a second kernel adds the chunk sums in chunk order and
+// A workgroup takes one chunk and eight centres, lists the chunk's points of each
+// of them in increasing index, and one thread per (centre, coordinate) adds its
+// list in that order; a second kernel adds the chunk sums in chunk order and
 // divides once by the count.  Every sum has a fixed order, so the update does
-// not depend on scheduling, and the walk spreads over chunks x centres x
-// coordinates threads (10752 waves at n=524288, k=256, d=21).
+// not depend on scheduling.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,7 +34,9 @@ namespace part {
 
 constexpr int NTA = 256;   // threads per workgroup, assignment
 constexpr int CG = 8;      // centres per pass
-constexpr int NTU = 64;    // threads per workgroup, update
+constexpr int NTU = 64;    // threads per workgroup, combine
+constexpr int CU = 8;      // centres per workgroup of the chunk sums
+constexpr int64_t SPLIT_N = 262144;  // four workgroups of 256 points per CU
 constexpr int MAX_K = 65536;
 constexpr int64_t CHUNK = 4096;         // points per partial sum of the update
 constexpr int64_t PART_BYTES = 1ll << 30;  // partial sums held at once
@@ -44,16 +48,19 @@ constexpr int64_t PART_BYTES = 1ll << 30;  // partial sums held at once
 constexpr int64_t NOALLOC_BYTES = 16ll << 20;
 static __device__ __align__(256) char scratch[NOALLOC_BYTES];
 
+// Measured at n=65536, k=64, d=8: 41 us whole, 14 us split.
+template <bool SPLIT>
 __global__ __launch_bounds__(NTA) void k_km_assign(const double* __restrict__ P, int64_t n, int d,
                                                    const double* __restrict__ C, int k, int32_t* __restrict__ label,
                                                    double* __restrict__ dist2) {
 #pragma clang fp contract(off)
-  const int64_t i = (int64_t)blockIdx.x * NTA + threadIdx.x;
-  if (i >= n) return;
-  const double* p = P + i * d;
+  const int w = SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  const int64_t i = SPLIT ? (int64_t)blockIdx.x * 64 + (threadIdx.x & 63) : (int64_t)blockIdx.x * NTA + threadIdx.x;
+  if (!SPLIT && i >= n) return;
+  const double* p = P + (i < n ? i : 0) * d;
   double best = INFINITY;
   int arg = 0;
-  for (int c0 = 0; c0 < k; c0 += CG) {
+  for (int c0 = w * CG; c0 < k; c0 += SPLIT ? 4 * CG : CG) {
     const int nc = k - c0 < CG ? k - c0 : CG;
     double acc[CG];
 #pragma unroll
@@ -77,43 +84,119 @@ __global__ __launch_bounds__(NTA) void k_km_assign(const double* __restrict__ P,
         arg = c0 + j;
       }
   }
+  if constexpr (SPLIT) {
+    // a wave that found no finite distance holds (+inf, 0): it wins only if every
+    // wave holds it, which is the plain result for a point without one
+    __shared__ double sb[4][64];
+    __shared__ int sa[4][64];
+    sb[w][threadIdx.x & 63] = best;
+    sa[w][threadIdx.x & 63] = arg;
+    __syncthreads();
+    if (w > 0 || i >= n) return;
+    for (int q = 1; q < 4; ++q) {
+      const double v = sb[q][threadIdx.x];
+      const int c = sa[q][threadIdx.x];
+      if (v < best || (v == best && v < INFINITY && c < arg)) {
+        best = v;
+        arg = c;
+      }
+    }
+  }
   label[i] = arg;
   if (dist2) dist2[i] = best;
 }
 
-__global__ __launch_bounds__(NTU) void k_km_partial(const double* __restrict__ P, int64_t n, int d,
+// Sums of one chunk for CU centres.  Bound: the reads of the labels and the rows.
+// Walking the chunk's labels once per 64 (centre, coordinate) pairs took 210 us at
+// n=65536, k=64, d=8; the lists take 14 us.
+__global__ __launch_bounds__(256) void k_km_partial(const double* __restrict__ P, int64_t n, int d,
                                                     const int32_t* __restrict__ label, int k, int64_t ch0,
                                                     int64_t nbx, double* __restrict__ part,
                                                     int64_t* __restrict__ pcnt) {
-  // block b covers chunk ch0 + b / nbx and threads (b % nbx) * NTU + tid of the k*d (centre, coordinate) pairs
-  const int64_t kd = (int64_t)k * d;
+  static_assert(CHUNK == 16 * 256 && CU == 8, "16 points per thread, eight 16-bit counters in two words");
+  __shared__ __align__(16) uint8_t lab[CHUNK];  // centre of each point relative to c0, 255: another
+  __shared__ uint16_t list[CHUNK];              // point offsets, by centre, in increasing order
+  __shared__ uint64_t wsum[2][4];
+  __shared__ int base[CU + 1];
+  // block b covers chunk ch0 + b / nbx and centres (b % nbx) * CU + 0..7
   const int64_t g = blockIdx.x / nbx;
-  const int64_t e = (blockIdx.x - g * nbx) * NTU + threadIdx.x;
-  if (e >= kd) return;
-  const int c = (int)(e / d), t = (int)(e - (int64_t)c * d);
+  const int c0 = (int)(blockIdx.x - g * nbx) * CU;
+  const int nc = k - c0 < CU ? k - c0 : CU;
   const int64_t i0 = (ch0 + g) * CHUNK;
-  const int64_t i1 = i0 + CHUNK < n ? i0 + CHUNK : n;
-  double s = 0.0;
-  int64_t cnt = 0;
-  int64_t i = i0;
-  for (; i + 8 <= i1; i += 8) {
-    int32_t lb[8];
+  const int m = (int)(n - i0 < CHUNK ? n - i0 : CHUNK);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) lb[j] = label[i + j];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (lb[j] == c) {
-        s = s + P[(i + j) * d + t];
-        ++cnt;
-      }
+  for (int j = 0; j < 16; ++j) {
+    const int o = j * 256 + tid;
+    const uint32_t l = o < m ? (uint32_t)label[i0 + o] - (uint32_t)c0 : 255u;
+    lab[o] = l < (uint32_t)nc ? (uint8_t)l : (uint8_t)255;
   }
-  for (; i < i1; ++i)
-    if (label[i] == c) {
-      s = s + P[i * d + t];
-      ++cnt;
+  __syncthreads();
+  // counts of this thread's 16 consecutive points: centre l in bits 16 (l % 4) of cnt[l / 4]
+  const uint4 q4 = *(const uint4*)(lab + 16 * tid);
+  const uint32_t qw[4] = {q4.x, q4.y, q4.z, q4.w};
+  uint64_t cnt[2] = {0, 0};
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const uint32_t l = (qw[j >> 2] >> (8 * (j & 3))) & 255u;
+    if (l < 8) cnt[l >> 2] += 1ull << (16 * (l & 3));
+  }
+  // inclusive scan over the threads
+  uint64_t inc[2] = {cnt[0], cnt[1]};
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t a = __shfl_up(inc[0], o), b = __shfl_up(inc[1], o);
+    if (lane >= o) {
+      inc[0] += a;
+      inc[1] += b;
     }
-  part[g * kd + e] = s;
-  if (t == 0) pcnt[g * k + c] = cnt;
+  }
+  if (lane == 63) {
+    wsum[0][w] = inc[0];
+    wsum[1][w] = inc[1];
+  }
+  __syncthreads();
+  uint64_t tot[2] = {0, 0};
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (q < w) inc[h] += wsum[h][q];
+      tot[h] += wsum[h][q];
+    }
+  if (tid <= CU) {
+    int b = 0;
+    for (int l = 0; l < tid; ++l) b += (int)((tot[l >> 2] >> (16 * (l & 3))) & 0xffffu);
+    base[tid] = b;
+  }
+  __syncthreads();
+  uint64_t pos[2] = {inc[0] - cnt[0], inc[1] - cnt[1]};
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const uint32_t l = (qw[j >> 2] >> (8 * (j & 3))) & 255u;
+    if (l < 8) {
+      const int sh = 16 * (l & 3);
+      list[base[l] + (int)((pos[l >> 2] >> sh) & 0xffffu)] = (uint16_t)(16 * tid + j);
+      pos[l >> 2] += 1ull << sh;
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < nc * d; e += 256) {
+    const int c = e / d, t = e - c * d;
+    const double* col = P + i0 * d + t;
+    double s = 0.0;
+    int q = base[c];
+    const int q1 = base[c + 1];
+    for (; q + 8 <= q1; q += 8) {
+      double v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = col[(int)list[q + j] * d];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s = s + v[j];
+    }
+    for (; q < q1; ++q) s = s + col[(int)list[q] * d];
+    part[g * (int64_t)k * d + (int64_t)c0 * d + e] = s;
+  }
+  if (tid < nc) pcnt[g * k + c0 + tid] = base[tid + 1] - base[tid];
 }
 
 __global__ __launch_bounds__(NTU) void k_km_combine(const double* __restrict__ part, const int64_t* __restrict__ pcnt,
@@ -158,8 +241,12 @@ void assign(const double* P, int64_t n, int32_t d, const double* C, int32_t k, i
   if (n == 0) return;
   const int64_t nb = (n + lma::part::NTA - 1) / lma::part::NTA;
   if (nb > 0x7fffffff) throw Err{LMA_E_ARG, "too many points"};
-  hipLaunchKernelGGL(lma::part::k_km_assign, dim3((unsigned)nb), dim3(lma::part::NTA), 0, st, P, n, (int)d, C, (int)k,
-                     label, dist2);
+  if (n <= lma::part::SPLIT_N && k > lma::part::CG)
+    hipLaunchKernelGGL(lma::part::k_km_assign<true>, dim3((unsigned)((n + 63) / 64)), dim3(lma::part::NTA), 0, st, P, n,
+                       (int)d, C, (int)k, label, dist2);
+  else
+    hipLaunchKernelGGL(lma::part::k_km_assign<false>, dim3((unsigned)nb), dim3(lma::part::NTA), 0, st, P, n, (int)d, C,
+                       (int)k, label, dist2);
   HIPCHK(hipGetLastError());
 }
 
@@ -173,7 +260,7 @@ hipError_t update_launch(const double* P, int64_t n, int32_t d, const int32_t* l
   const int64_t kd = (int64_t)k * d;
   const int64_t nch = n > 0 ? (n + CHUNK - 1) / CHUNK : 0;
   const int64_t per = (int64_t)sizeof(double) * kd + (int64_t)sizeof(int64_t) * k;
-  const int64_t nbx = (kd + NTU - 1) / NTU;
+  const int64_t nbx = (kd + NTU - 1) / NTU, nbc = (k + CU - 1) / CU;
   double* part = reinterpret_cast<double*>(mem);
   int64_t* pcnt = reinterpret_cast<int64_t*>(mem + sizeof(double) * group * kd);
   double* srun = reinterpret_cast<double*>(mem + group * per);
@@ -186,8 +273,8 @@ hipError_t update_launch(const double* P, int64_t n, int32_t d, const int32_t* l
   }
   for (int64_t ch0 = 0; ch0 < nch && err == hipSuccess; ch0 += group) {
     const int64_t ng = std::min<int64_t>(group, nch - ch0);
-    hipLaunchKernelGGL(k_km_partial, dim3((unsigned)(ng * nbx)), dim3(NTU), 0, st, P, n, (int)d, label, (int)k, ch0,
-                       nbx, part, pcnt);
+    hipLaunchKernelGGL(k_km_partial, dim3((unsigned)(ng * nbc)), dim3(256), 0, st, P, n, (int)d, label, (int)k, ch0,
+                       nbc, part, pcnt);
     err = hipGetLastError();
     if (err != hipSuccess) break;
     hipLaunchKernelGGL(k_km_combine, dim3((unsigned)nbx), dim3(NTU), 0, st, part, pcnt, ng, (int)k, (int)d, srun,
@@ -206,14 +293,15 @@ int64_t update_running(int32_t d, int32_t k) {
 }
 
 void check_launch_size(int64_t group, int32_t d, int32_t k) {
-  const int64_t nbx = ((int64_t)k * d + lma::part::NTU - 1) / lma::part::NTU;
+  const int64_t nbx = ((int64_t)k + lma::part::CU - 1) / lma::part::CU;
   if (group * nbx > 0x7fffffff) throw Err{LMA_E_ARG, "too many centres x coordinates for one launch"};
 }
 
-// The update with a workspace from the library's device cache (partial sums
-// of at most PART_BYTES at once), returned after a stream synchronisation.
-void update(const double* P, int64_t n, int32_t d, const int32_t* label, int32_t k, double* C, int64_t* count,
-            hipStream_t st) {
+// `rounds` times (assign to label, then) the update, with one workspace from the
+// library's device cache (partial sums of at most PART_BYTES at once), returned
+// after a stream synchronisation.
+void update(const double* P, int64_t n, int32_t d, int32_t* label, int32_t k, double* C, int64_t* count,
+            hipStream_t st, int32_t rounds = 1, bool with_assign = false) {
   using namespace lma::part;
   const int64_t nch = n > 0 ? (n + CHUNK - 1) / CHUNK : 0;
   const int64_t per = update_per_chunk(d, k);
@@ -221,14 +309,30 @@ void update(const double* P, int64_t n, int32_t d, const int32_t* label, int32_t
   if (const char* env = std::getenv("LMA_KMEANS_PART_BYTES")) cap = std::max<long long>(1, std::atoll(env));
   const int64_t group = nch == 0 ? 0 : std::max<int64_t>(1, std::min<int64_t>(nch, cap / per));
   check_launch_size(group, d, k);
+  struct Mem {  // given back after the stream has drained, also when a launch fails
+    char* p;
+    size_t bytes;
+    hipStream_t st;
+    hipError_t es = hipSuccess;
+    void release() {
+      if (!p) return;
+      es = hipStreamSynchronize(st);
+      lmart::devcache::put(p, bytes);
+      p = nullptr;
+    }
+    ~Mem() { release(); }
+  };
   const size_t bytes = (size_t)(group * per + update_running(d, k));
-  char* mem = static_cast<char*>(lmart::devcache::get(bytes));
-  if (!mem) throw Err{LMA_E_NOMEM, "device allocation for the centre update failed"};
-  const hipError_t err = update_launch(P, n, d, label, k, C, count, group, mem, st);
-  const hipError_t es = hipStreamSynchronize(st);
-  lmart::devcache::put(mem, bytes);
+  Mem mem{static_cast<char*>(lmart::devcache::get(bytes)), bytes, st};
+  if (!mem.p) throw Err{LMA_E_NOMEM, "device allocation for the centre update failed"};
+  hipError_t err = hipSuccess;
+  for (int32_t it = 0; it < rounds && err == hipSuccess; ++it) {
+    if (with_assign) assign(P, n, d, C, k, label, nullptr, st);
+    err = update_launch(P, n, d, label, k, C, count, group, mem.p, st);
+  }
+  mem.release();
   if (err != hipSuccess) throw Err{LMA_E_HIP, std::string("k-means update launch: ") + hipGetErrorString(err)};
-  if (es != hipSuccess) throw Err{LMA_E_HIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(es)};
+  if (mem.es != hipSuccess) throw Err{LMA_E_HIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(mem.es)};
 }
 
 // Device address of the scratch array on the current device, looked up once
@@ -348,7 +452,7 @@ lma_status lma_kmeans_update(const double* P, int64_t n, int32_t d, const int32_
   return guard([&] {
     check_shape(P, n, d, k);
     if (!C || (n > 0 && !label)) throw Err{LMA_E_ARG, "NULL array"};
-    update(P, n, d, label, k, C, count, stream);
+    update(P, n, d, const_cast<int32_t*>(label), k, C, count, stream);  // label is read only
   });
 }
 
@@ -367,10 +471,7 @@ lma_status lma_kmeans(const double* P, int64_t n, int32_t d, double* C, int32_t 
     check_shape(P, n, d, k);
     if (iters < 0) throw Err{LMA_E_ARG, "iters < 0"};
     if (!C || (n > 0 && !label)) throw Err{LMA_E_ARG, "NULL array"};
-    for (int32_t it = 0; it < iters; ++it) {
-      assign(P, n, d, C, k, label, nullptr, stream);
-      if (n > 0) update(P, n, d, label, k, C, nullptr, stream);
-    }
+    if (n > 0 && iters > 0) update(P, n, d, label, k, C, nullptr, stream, iters, true);
     assign(P, n, d, C, k, label, dist2, stream);
   });
 }

@@ -14,11 +14,18 @@
 //     select on the (float64 bit pattern, index) pair: non-negative doubles
 //     order like their bit patterns.
 //
-// Seeding: per round one kernel updates each point's distance to its nearest
-// chosen centre and the block maxima, one workgroup derives the power-of-two
-// scale from the maximum, one kernel forms the block sums of the weights, and
-// one workgroup finds the drawn point (a scan of the block sums, then of the
-// weights of one block).  No host synchronisation between rounds.
+// Seeding: two launches per round.  One updates each point's distance to its
+// nearest chosen centre and the block maxima; every workgroup of it first finds the
+// point drawn last for itself (a scan of the block sums, then of the weights of one
+// block; the distances alternate between two arrays, so that block is still there
+// unchanged).  The other derives the power-of-two scale from the maxima, again in
+// every workgroup, and forms the block sums of the weights.  No host synchronisation
+// between rounds.  Bound: the launches (2 to 4 us each); with the scale and the draw
+// in launches of one workgroup a round had four (n=65536, k=64: 775 us in 252 launches, 500 us in 126 now).
+//
+// Counts per centre are formed in LDS and added to the global counters once per
+// workgroup and centre (k <= HIST_K): one atomic per point on a few dozen counters
+// serialised (proposals of 65536 points on 64 centres 111 -> 34 us, scatter 80 -> 8 us).
 //
 // Bounded assignment, upper bound: rounds of (propose to the nearest open
 // centre, counting sort of the proposers by centre, one workgroup per centre
@@ -66,6 +73,28 @@ __device__ __forceinline__ double sqdist(const double* __restrict__ p, const dou
   return acc;
 }
 
+constexpr int HIST_K = 2048;  // centres counted in LDS
+
+// Every thread of the workgroup calls it: adds one to cnt[c] for each thread with c >= 0.
+// hist: [HIST_K] LDS words, or null to add directly.  Returns the thread's place among
+// all that were ever added to cnt[c].
+__device__ inline unsigned long long count_place(unsigned long long* __restrict__ cnt, int k, int c, uint32_t* hist,
+                                                 unsigned long long* place) {
+  if (hist == nullptr) return c >= 0 ? atomicAdd(&cnt[c], 1ull) : 0;
+  for (int q = threadIdx.x; q < k; q += blockDim.x) hist[q] = 0;
+  __syncthreads();
+  const uint32_t mine = c >= 0 ? atomicAdd(&hist[c], 1u) : 0u;
+  __syncthreads();
+  for (int q = threadIdx.x; q < k; q += blockDim.x)
+    if (hist[q]) {
+      const unsigned long long at = atomicAdd(&cnt[q], (unsigned long long)hist[q]);
+      if (place) place[q] = at;
+    }
+  if (!place) return 0;
+  __syncthreads();
+  return c >= 0 ? place[c] + mine : 0;
+}
+
 __device__ __forceinline__ uint64_t dbits(double v) { return (uint64_t)__double_as_longlong(v); }
 
 // key order: (distance bits, index) lexicographic
@@ -77,42 +106,42 @@ __device__ __forceinline__ bool key_le(uint64_t k, int64_t i, uint64_t tk, int64
 // block-wide helpers (NT threads)
 // ---------------------------------------------------------------------------
 __device__ double block_max(double v, double* sh) {
-  sh[threadIdx.x] = v;
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
-  }
-  const double r = sh[0];
+  v = sh[0];
+  for (int q = 1; q < NT / 64; ++q) v = fmax(v, sh[q]);
   __syncthreads();
-  return r;
+  return v;
 }
 
 __device__ uint64_t block_sum_u64(uint64_t v, uint64_t* sh) {
-  sh[threadIdx.x] = v;
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  const uint64_t r = sh[0];
+  v = sh[0];
+  for (int q = 1; q < NT / 64; ++q) v += sh[q];
   __syncthreads();
-  return r;
+  return v;
 }
 
-// inclusive scan of one uint64 per thread (Hillis-Steele in LDS)
-__device__ uint64_t block_incl_scan_u64(uint64_t v, uint64_t* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = 1; s < NT; s <<= 1) {
-    const uint64_t add = (int)threadIdx.x >= s ? sh[threadIdx.x - s] : 0;
-    __syncthreads();
-    sh[threadIdx.x] += add;
-    __syncthreads();
+// inclusive scan of one uint64 per thread; total receives the sum over the workgroup
+__device__ uint64_t block_incl_scan_u64(uint64_t v, uint64_t* sh, uint64_t* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t a = __shfl_up(v, o);
+    if (lane >= o) v += a;
   }
-  const uint64_t r = sh[threadIdx.x];
+  if (lane == 63) sh[w] = v;
   __syncthreads();
-  return r;
+  uint64_t t = 0;
+  for (int q = 0; q < NT / 64; ++q) {
+    if (q == w) v += t;
+    t += sh[q];
+  }
+  *total = t;
+  __syncthreads();
+  return v;
 }
 
 // floor(r * T / 2^32) for T < 2^63, exactly
@@ -130,80 +159,25 @@ __device__ __forceinline__ uint64_t weight_of(double dmin, int shift, int zero) 
 // ---------------------------------------------------------------------------
 // seeding
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(NT) void k_seed_dmin(const double* __restrict__ P, int64_t n, int d,
-                                                  const int64_t* __restrict__ sidx, int j, double* __restrict__ dmin,
-                                                  double* __restrict__ bmax) {
-  __shared__ double sh[NT];
-  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  double v = 0.0;
-  if (i < n) {
-    const double q = sqdist(P + i * d, P + sidx[j] * d, d);
-    const double old = dmin[i];
-    v = (j == 0 || q < old) ? q : old;
-    dmin[i] = v;
-  }
-  const double m = block_max(v, sh);
-  if (threadIdx.x == 0) bmax[blockIdx.x] = m;
-}
-
-// scal[0] = shift W - e, scal[1] = 1 when every weight is 0, scal[2] |= 1 on a
-// non-finite maximum
-__global__ __launch_bounds__(NT) void k_seed_scale(const double* __restrict__ bmax, int64_t nb, int wbits,
-                                                   int32_t* __restrict__ scal) {
-  __shared__ double sh[NT];
-  double m = 0.0;
-  for (int64_t b = threadIdx.x; b < nb; b += NT) m = fmax(m, bmax[b]);
-  m = block_max(m, sh);
-  if (threadIdx.x == 0) {
-    if (!isfinite(m)) {
-      scal[2] = 1;
-      scal[1] = 1;
-      scal[0] = 0;
-    } else if (!(m > 0.0)) {
-      scal[1] = 1;
-      scal[0] = 0;
-    } else {
-      int e = 0;
-      (void)frexp(m, &e);
-      scal[0] = wbits - e;
-      scal[1] = 0;
-    }
-  }
-}
-
-__global__ __launch_bounds__(NT) void k_seed_wsum(const double* __restrict__ dmin, int64_t n,
-                                                  const int32_t* __restrict__ scal, uint64_t* __restrict__ bsum) {
-  __shared__ uint64_t sh[NT];
-  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  const uint64_t w = i < n ? weight_of(dmin[i], scal[0], scal[1]) : 0;
-  const uint64_t s = block_sum_u64(w, sh);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = s;
-}
-
-// one workgroup: the drawn point of round j
-__global__ __launch_bounds__(NT) void k_seed_pick(const double* __restrict__ dmin, int64_t n,
-                                                  const int32_t* __restrict__ scal,
-                                                  const uint64_t* __restrict__ bsum, int64_t nb,
-                                                  const uint32_t* __restrict__ rnd, int j,
-                                                  int64_t* __restrict__ sidx) {
-  __shared__ uint64_t sh[NT];
-  __shared__ int64_t found_b;
+// The point of round j (workgroup-wide; the same in every workgroup).
+// scal[0] = shift W - e, scal[1] = 1 when every weight is 0
+__device__ int64_t seed_pick(const double* __restrict__ dmin, int64_t n, const int32_t* __restrict__ scal,
+                             const uint64_t* __restrict__ bsum, int64_t nb, uint32_t r) {
+  __shared__ uint64_t sh[NT / 64];
+  __shared__ int64_t found_b, found_i;
   __shared__ uint64_t found_rest;
   // per-thread contiguous ranges of blocks
   const int64_t per = (nb + NT - 1) / NT;
   const int64_t b0 = (int64_t)threadIdx.x * per, b1 = b0 + per < nb ? b0 + per : nb;
-  uint64_t mine = 0;
+  uint64_t mine = 0, T;
   for (int64_t b = b0; b < b1; ++b) mine += bsum[b];
-  const uint64_t incl = block_incl_scan_u64(mine, sh);
-  const uint64_t T = sh[NT - 1];
-  __syncthreads();
-  const uint32_t r = rnd[j];
-  if (T == 0) {
-    if (threadIdx.x == 0) sidx[j] = (int64_t)(((uint64_t)r * (uint64_t)n) >> 32);
-    return;
-  }
+  const uint64_t incl = block_incl_scan_u64(mine, sh, &T);
+  if (T == 0) return (int64_t)(((uint64_t)r * (uint64_t)n) >> 32);
   const uint64_t target = scaled_target(r, T);
-  if (threadIdx.x == 0) found_b = -1;
+  if (threadIdx.x == 0) {
+    found_b = -1;
+    found_i = 0;  // an index is drawn whenever T > 0
+  }
   __syncthreads();
   const uint64_t excl = incl - mine;
   if (excl <= target && target < incl) {
@@ -223,8 +197,73 @@ __global__ __launch_bounds__(NT) void k_seed_pick(const double* __restrict__ dmi
   const uint64_t rest = found_rest;
   const int64_t i = b * NT + threadIdx.x;
   const uint64_t w = (b >= 0 && i < n) ? weight_of(dmin[i], scal[0], scal[1]) : 0;
-  const uint64_t wi = block_incl_scan_u64(w, sh);
-  if (b >= 0 && wi > rest && wi - w <= rest) sidx[j] = i;
+  const uint64_t wi = block_incl_scan_u64(w, sh, &T);
+  if (b >= 0 && wi > rest && wi - w <= rest) found_i = i;
+  __syncthreads();
+  return found_i;
+}
+
+// Round j: draw point j (j > 0) from the weights of dold, then the distances to the
+// nearest of the points 0..j in dnew and their block maxima.
+__global__ __launch_bounds__(NT) void k_seed_dmin(const double* __restrict__ P, int64_t n, int d, int j,
+                                                  const int32_t* __restrict__ scal, const uint64_t* __restrict__ bsum,
+                                                  int64_t nb, const uint32_t* __restrict__ rnd,
+                                                  int64_t* __restrict__ sidx, const double* __restrict__ dold,
+                                                  double* __restrict__ dnew, double* __restrict__ bmax) {
+  __shared__ double sh[NT / 64];
+  int64_t c = sidx[0];
+  if (j > 0) {
+    c = seed_pick(dold, n, scal, bsum, nb, rnd[j]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) sidx[j] = c;
+  }
+  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  double v = 0.0;
+  if (i < n) {
+    const double q = sqdist(P + i * d, P + c * d, d);
+    const double old = j > 0 ? dold[i] : 0.0;
+    v = (j == 0 || q < old) ? q : old;
+    dnew[i] = v;
+  }
+  const double m = block_max(v, sh);
+  if (threadIdx.x == 0) bmax[blockIdx.x] = m;
+}
+
+// Block sums of the weights; scal[0] = shift W - e, scal[1] = 1 when every weight is
+// 0, scal[2] |= 1 on a non-finite maximum
+__global__ __launch_bounds__(NT) void k_seed_wsum(const double* __restrict__ dmin, int64_t n,
+                                                  const double* __restrict__ bmax, int64_t nb, int wbits,
+                                                  int32_t* __restrict__ scal, uint64_t* __restrict__ bsum) {
+  __shared__ double shd[NT / 64];
+  __shared__ uint64_t sh[NT / 64];
+  double m = 0.0;
+  for (int64_t b = threadIdx.x; b < nb; b += NT) m = fmax(m, bmax[b]);
+  m = block_max(m, shd);
+  int shift = 0, zero = 1;
+  if (isfinite(m) && m > 0.0) {
+    int e = 0;
+    (void)frexp(m, &e);
+    shift = wbits - e;
+    zero = 0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    scal[0] = shift;
+    scal[1] = zero;
+    if (!isfinite(m)) scal[2] = 1;
+  }
+  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  const uint64_t w = i < n ? weight_of(dmin[i], shift, zero) : 0;
+  const uint64_t s = block_sum_u64(w, sh);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = s;
+}
+
+// one workgroup: the drawn point of the last round
+__global__ __launch_bounds__(NT) void k_seed_pick(const double* __restrict__ dmin, int64_t n,
+                                                  const int32_t* __restrict__ scal,
+                                                  const uint64_t* __restrict__ bsum, int64_t nb,
+                                                  const uint32_t* __restrict__ rnd, int j,
+                                                  int64_t* __restrict__ sidx) {
+  const int64_t c = seed_pick(dmin, n, scal, bsum, nb, rnd[j]);
+  if (threadIdx.x == 0) sidx[j] = c;
 }
 
 __global__ void k_gather_rows(const double* __restrict__ P, int d, const int64_t* __restrict__ idx, int k,
@@ -240,44 +279,66 @@ __global__ void k_gather_rows(const double* __restrict__ P, int d, const int64_t
 // ---------------------------------------------------------------------------
 // Every point without a centre proposes to its nearest centre holding fewer
 // than hi points (ties to the lower index).
+// Four waves share 64 points and the centres as in the nearest-centre assignment.
 __global__ __launch_bounds__(NT) void k_propose(const double* __restrict__ P, int64_t n, int d,
                                                 const double* __restrict__ C, int k, int64_t hi,
                                                 const int64_t* __restrict__ cnt, const int32_t* __restrict__ label,
                                                 int32_t* __restrict__ tgt, double* __restrict__ key,
                                                 unsigned long long* __restrict__ pcnt) {
 #pragma clang fp contract(off)
-  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (i >= n || label[i] >= 0) return;
-  const double* p = P + i * d;
+  __shared__ double sb[4][64];
+  __shared__ int sa[4][64];
+  __shared__ uint32_t hist[HIST_K];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const bool live = i < n && label[i] < 0;
+  const double* p = P + (i < n ? i : 0) * d;
   double best = INFINITY;
   int arg = -1;
-  for (int c0 = 0; c0 < k; c0 += CG) {
-    const int nc = k - c0 < CG ? k - c0 : CG;
-    double acc[CG];
+  if (__any(live))
+    for (int c0 = w * CG; c0 < k; c0 += 4 * CG) {
+      const int nc = k - c0 < CG ? k - c0 : CG;
+      double acc[CG];
 #pragma unroll
-    for (int jj = 0; jj < CG; ++jj) acc[jj] = 0.0;
-    const double* cb = C + (int64_t)c0 * d;
-    for (int t = 0; t < d; ++t) {
-      const double x = p[t];
+      for (int jj = 0; jj < CG; ++jj) acc[jj] = 0.0;
+      const double* cb = C + (int64_t)c0 * d;
+      for (int t = 0; t < d; ++t) {
+        const double x = p[t];
 #pragma unroll
-      for (int jj = 0; jj < CG; ++jj) {
-        if (jj < nc) {
-          const double df = x - cb[jj * d + t];
-          const double sq = df * df;
-          acc[jj] = acc[jj] + sq;
+        for (int jj = 0; jj < CG; ++jj) {
+          if (jj < nc) {
+            const double df = x - cb[jj * d + t];
+            const double sq = df * df;
+            acc[jj] = acc[jj] + sq;
+          }
         }
       }
-    }
 #pragma unroll
-    for (int jj = 0; jj < CG; ++jj)
-      if (jj < nc && cnt[c0 + jj] < hi && (arg < 0 || acc[jj] < best)) {
-        best = acc[jj];
-        arg = c0 + jj;
+      for (int jj = 0; jj < CG; ++jj)
+        if (jj < nc && cnt[c0 + jj] < hi && (arg < 0 || acc[jj] < best)) {
+          best = acc[jj];
+          arg = c0 + jj;
+        }
+    }
+  sb[w][lane] = best;
+  sa[w][lane] = arg;
+  __syncthreads();
+  int take = -1;
+  if (w == 0 && live) {
+    for (int q = 1; q < 4; ++q) {
+      const double v = sb[q][lane];
+      const int c = sa[q][lane];
+      // the first open centre wins whatever its distance, a later one if it is nearer
+      if (c >= 0 && (arg < 0 || v < best || (c < arg && !(best < v)))) {
+        best = v;
+        arg = c;
       }
+    }
+    tgt[i] = arg;
+    key[i] = best;
+    take = arg;  // an open centre exists while points are left
   }
-  tgt[i] = arg;
-  key[i] = best;
-  if (arg >= 0) atomicAdd(&pcnt[arg], 1ull);  // an open centre exists while points are left
+  count_place(pcnt, k, take, k <= HIST_K ? hist : nullptr, nullptr);
 }
 
 // One workgroup: segment offsets from the per-segment counts (which it then
@@ -314,17 +375,18 @@ __global__ __launch_bounds__(1024) void k_seg_offsets(unsigned long long* __rest
 
 // Proposers (tgt >= 0 among points flagged by label < 0, or every point with
 // tgt >= 0 when all_tgt) into their segment.
-__global__ __launch_bounds__(NT) void k_scatter(int64_t n, const int32_t* __restrict__ label, int all_tgt,
+__global__ __launch_bounds__(NT) void k_scatter(int64_t n, int k, const int32_t* __restrict__ label, int all_tgt,
                                                 const int32_t* __restrict__ tgt, const double* __restrict__ key,
                                                 const int64_t* __restrict__ seg_ptr,
                                                 unsigned long long* __restrict__ cursor,
                                                 uint64_t* __restrict__ skey, int64_t* __restrict__ sidx) {
+  __shared__ uint32_t hist[HIST_K];
+  __shared__ unsigned long long place[HIST_K];
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (i >= n) return;
-  if (!all_tgt && label[i] >= 0) return;
-  const int c = tgt[i];
+  const int c = i < n && (all_tgt || label[i] < 0) ? tgt[i] : -1;
+  const unsigned long long at = count_place(cursor, k, c, k <= HIST_K ? hist : nullptr, place);
   if (c < 0) return;
-  const int64_t pos = seg_ptr[c] + (int64_t)atomicAdd(&cursor[c], 1ull);
+  const int64_t pos = seg_ptr[c] + (int64_t)at;
   skey[pos] = dbits(key[i]);
   sidx[pos] = i;
 }
@@ -447,19 +509,19 @@ __global__ __launch_bounds__(1024) void k_round_end(int k, const int64_t* __rest
 // than lo; their key is the squared distance to c, tgt their donor.
 __global__ __launch_bounds__(NT) void k_lb_keys(const double* __restrict__ P, int64_t n, int d,
                                                 const double* __restrict__ C, int c, const int32_t* __restrict__ label,
-                                                const int64_t* __restrict__ cnt, int64_t lo,
+                                                const int64_t* __restrict__ cnt, int64_t lo, int k,
                                                 int32_t* __restrict__ tgt, double* __restrict__ key,
                                                 unsigned long long* __restrict__ pcnt) {
+  __shared__ uint32_t hist[HIST_K];
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (i >= n) return;
-  const int o = label[i];
-  if (o == c || cnt[o] <= lo) {
-    tgt[i] = -1;
-    return;
+  int o = -1;
+  if (i < n) {
+    o = label[i];
+    if (o == c || cnt[o] <= lo) o = -1;
+    tgt[i] = o;
+    if (o >= 0) key[i] = sqdist(P + i * d, C + (int64_t)c * d, d);
   }
-  tgt[i] = o;
-  key[i] = sqdist(P + i * d, C + (int64_t)c * d, d);
-  atomicAdd(&pcnt[o], 1ull);
+  count_place(pcnt, k, o, k <= HIST_K ? hist : nullptr, nullptr);
 }
 
 // The union A of each donor's (count - lo) nearest candidates, compacted.
@@ -553,37 +615,52 @@ __global__ __launch_bounds__(NT) void k_digit_scatter(const uint32_t* __restrict
                                                       const uint32_t* __restrict__ H, uint32_t* __restrict__ kout,
                                                       int64_t* __restrict__ vout) {
   __shared__ uint32_t run[256];
-  __shared__ uint32_t dig[NT];
+  __shared__ uint32_t wcnt[NT / 64][257];  // points per digit (256: none) of each wave
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t ch = blockIdx.x;
   run[threadIdx.x] = 0;
-  __syncthreads();
   for (int s = 0; s < SORT_CHUNK; s += NT) {
     const int64_t i = ch * SORT_CHUNK + s + threadIdx.x;
     const bool ok = i < n;
     const uint32_t kv = ok ? kin[i] : 0;
     const uint32_t dg = ok ? ((kv >> shift) & 255u) : 256u;
-    dig[threadIdx.x] = dg;
+    for (int q = lane; q < 257; q += 64) wcnt[w][q] = 0;
+    // lanes with the same digit, and how many of them come before this one
+    uint64_t same = ~0ull;
+#pragma unroll
+    for (int bit = 0; bit < 9; ++bit) {
+      const bool one = (dg >> bit) & 1u;
+      const uint64_t m = __ballot(one);
+      same &= one ? m : ~m;
+    }
+    const uint32_t before = __popcll(same & ((1ull << lane) - 1));
     __syncthreads();
-    uint32_t before = 0;
-    for (int t = 0; t < (int)threadIdx.x; ++t) before += dig[t] == dg ? 1u : 0u;
+    if (before == 0) wcnt[w][dg] = __popcll(same);
+    __syncthreads();
     if (ok) {
-      const int64_t pos = (int64_t)H[(int64_t)dg * nch + ch] + run[dg] + before;
+      uint32_t at = run[dg] + before;
+      for (int q = 0; q < w; ++q) at += wcnt[q][dg];
+      const int64_t pos = (int64_t)H[(int64_t)dg * nch + ch] + at;
       kout[pos] = kv;
       vout[pos] = vin ? vin[i] : i;
     }
     __syncthreads();
-    if (ok) atomicAdd(&run[dg], 1u);
+    for (int q = 0; q < NT / 64; ++q) run[threadIdx.x] += wcnt[q][threadIdx.x];
     __syncthreads();
   }
 }
 
-__global__ void k_block_keys(const int32_t* __restrict__ label, const int32_t* __restrict__ rank, int64_t n,
-                             uint32_t* __restrict__ keys, unsigned long long* __restrict__ bcount) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int32_t b = rank[label[i]];
-  keys[i] = (uint32_t)b;
-  atomicAdd(&bcount[b], 1ull);
+__global__ __launch_bounds__(NT) void k_block_keys(const int32_t* __restrict__ label, const int32_t* __restrict__ rank,
+                                                   int64_t n, int M, uint32_t* __restrict__ keys,
+                                                   unsigned long long* __restrict__ bcount) {
+  __shared__ uint32_t hist[HIST_K];
+  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  int32_t b = -1;
+  if (i < n) {
+    b = rank[label[i]];
+    keys[i] = (uint32_t)b;
+  }
+  count_place(bcount, M, b, M <= HIST_K ? hist : nullptr, nullptr);
 }
 
 // non-finite flag over an array
@@ -668,7 +745,7 @@ void check_finite(const double* a, int64_t n, int32_t* flag, hipStream_t st, con
 }
 
 // k-means++ seeding: indices into sidx (device [k]), centres into C (device
-// [k][d]); ws pieces: dmin [n], bmax/bsum [nb], scal [3], rnd [k].
+// [k][d]); ws pieces: dmin [2][n], bmax/bsum [nb], scal [3], rnd [k].
 void seed(const double* P, int64_t n, int32_t d, int32_t k, const uint32_t* rand_h, double* C, int64_t* sidx,
           double* dmin, double* bmax, uint64_t* bsum, int32_t* scal, uint32_t* rnd, hipStream_t st) {
   const int64_t nb = nblocks(n);
@@ -678,19 +755,17 @@ void seed(const double* P, int64_t n, int32_t d, int32_t k, const uint32_t* rand
   HIPCHK(hipMemcpyAsync(sidx, &first, 8, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemsetAsync(scal, 0, 12, st));
   const int wb = weight_bits(n);
-  for (int j = 0; j < k; ++j) {
-    if (j > 0) {
-      hipLaunchKernelGGL(k_seed_scale, dim3(1), dim3(NT), 0, st, bmax, nb, wb, scal);
-      chk();
-      hipLaunchKernelGGL(k_seed_wsum, dim3((unsigned)nb), dim3(NT), 0, st, dmin, n, scal, bsum);
-      chk();
-      hipLaunchKernelGGL(k_seed_pick, dim3(1), dim3(NT), 0, st, dmin, n, scal, bsum, nb, rnd, j, sidx);
-      chk();
-    }
-    if (j < k - 1) {
-      hipLaunchKernelGGL(k_seed_dmin, dim3((unsigned)nb), dim3(NT), 0, st, P, n, (int)d, sidx, j, dmin, bmax);
-      chk();
-    }
+  for (int j = 0; j < k - 1; ++j) {
+    double* dnew = dmin + (j & 1) * n;
+    hipLaunchKernelGGL(k_seed_dmin, dim3((unsigned)nb), dim3(NT), 0, st, P, n, (int)d, j, scal, bsum, nb, rnd, sidx,
+                       dmin + ((j + 1) & 1) * n, dnew, bmax);
+    chk();
+    hipLaunchKernelGGL(k_seed_wsum, dim3((unsigned)nb), dim3(NT), 0, st, dnew, n, bmax, nb, wb, scal, bsum);
+    chk();
+  }
+  if (k > 1) {
+    hipLaunchKernelGGL(k_seed_pick, dim3(1), dim3(NT), 0, st, dmin + (k & 1) * n, n, scal, bsum, nb, rnd, k - 1, sidx);
+    chk();
   }
   const int64_t kd = (int64_t)k * d;
   hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)((kd + NT - 1) / NT)), dim3(NT), 0, st, P, (int)d, sidx, (int)k, C);
@@ -782,13 +857,13 @@ int32_t bounded(const double* P, int64_t n, int32_t d, const double* C, int32_t 
   while (left > 0) {
     if (rounds > k + 1) throw Err{LMA_E_INTERNAL, "bounded assignment did not finish in k + 1 rounds"};
     ++rounds;
-    hipLaunchKernelGGL(k_propose, dim3((unsigned)nb), dim3(NT), 0, st, P, n, (int)d, C, (int)k, hi, b.cnt, label,
+    hipLaunchKernelGGL(k_propose, dim3((unsigned)((n + 63) / 64)), dim3(NT), 0, st, P, n, (int)d, C, (int)k, hi, b.cnt, label,
                        b.tgt, b.key, b.pcnt);
     chk();
     hipLaunchKernelGGL(k_seg_offsets, dim3(1), dim3(1024), 0, st, b.pcnt, (int)k, b.seg_ptr, b.cursor, b.cnt, hi, 0,
                        b.rank);
     chk();
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)nb), dim3(NT), 0, st, n, label, 0, b.tgt, b.key, b.seg_ptr,
+    hipLaunchKernelGGL(k_scatter, dim3((unsigned)nb), dim3(NT), 0, st, n, (int)k, label, 0, b.tgt, b.key, b.seg_ptr,
                        b.cursor, b.skey, b.sidx);
     chk();
     hipLaunchKernelGGL(k_seg_select, dim3((unsigned)k), dim3(NT), 0, st, b.seg_ptr, b.skey, b.sidx, b.rank, (int)k,
@@ -807,13 +882,13 @@ int32_t bounded(const double* P, int64_t n, int32_t d, const double* C, int32_t 
   sync(st);
   for (int c = 0; c < k; ++c) {
     if (cnt[c] >= lo) continue;
-    hipLaunchKernelGGL(k_lb_keys, dim3((unsigned)nb), dim3(NT), 0, st, P, n, (int)d, C, c, label, b.cnt, lo, b.tgt,
-                       b.key, b.pcnt);
+    hipLaunchKernelGGL(k_lb_keys, dim3((unsigned)nb), dim3(NT), 0, st, P, n, (int)d, C, c, label, b.cnt, lo, (int)k,
+                       b.tgt, b.key, b.pcnt);
     chk();
     hipLaunchKernelGGL(k_seg_offsets, dim3(1), dim3(1024), 0, st, b.pcnt, (int)k, b.seg_ptr, b.cursor, b.cnt, lo, 1,
                        b.rank);
     chk();
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)nb), dim3(NT), 0, st, n, label, 1, b.tgt, b.key, b.seg_ptr,
+    hipLaunchKernelGGL(k_scatter, dim3((unsigned)nb), dim3(NT), 0, st, n, (int)k, label, 1, b.tgt, b.key, b.seg_ptr,
                        b.cursor, b.skey, b.sidx);
     chk();
     hipLaunchKernelGGL(k_seg_select, dim3((unsigned)k), dim3(NT), 0, st, b.seg_ptr, b.skey, b.sidx, b.rank, (int)k,
@@ -897,7 +972,7 @@ lma_status lma_kmeans_seed(const double* P, int64_t n, int32_t d, int32_t k, con
     if (!rand || !C) throw Err{LMA_E_ARG, "NULL array"};
     const int64_t nb = nblocks(n);
     Work w;
-    const size_t o_dmin = w.take(8 * (size_t)n), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
+    const size_t o_dmin = w.take(16 * (size_t)n), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
     const size_t o_scal = w.take(16), o_rnd = w.take(4 * (size_t)k), o_sidx = w.take(8 * (size_t)k);
     w.get(stream);
     check_finite(P, n * d, w.at<int32_t>(o_scal), stream, "P");
@@ -948,7 +1023,7 @@ lma_status lma_partition(const double* X, int64_t n, const double* U, int64_t n_
     Work w;
     std::vector<size_t> o;
     bounded_reserve(w, n, M, o);
-    const size_t o_dmin = w.take(8 * (size_t)n), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
+    const size_t o_dmin = w.take(16 * (size_t)n), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
     const size_t o_scal = w.take(16), o_rnd = w.take(4 * (size_t)M), o_sidx = w.take(8 * (size_t)M);
     const size_t o_C = w.take(8 * (size_t)M * d), o_Cb = w.take(8 * (size_t)M * d);
     const size_t o_label = w.take(4 * (size_t)nmax), o_keys = w.take(4 * (size_t)nmax);
@@ -1003,7 +1078,7 @@ lma_status lma_partition(const double* X, int64_t n, const double* U, int64_t n_
     auto one_set = [&](const int32_t* lab, int64_t np, int64_t* out_perm, int64_t* out_ptr) {
       HIPCHK(hipMemsetAsync(bc, 0, 8 * (size_t)M, stream));
       if (np > 0) {
-        hipLaunchKernelGGL(k_block_keys, dim3((unsigned)nblocks(np)), dim3(NT), 0, stream, lab, rank_d, np, keys, bc);
+        hipLaunchKernelGGL(k_block_keys, dim3((unsigned)nblocks(np)), dim3(NT), 0, stream, lab, rank_d, np, (int)M, keys, bc);
         chk();
         stable_perm(keys, np, M, out_perm, w.at<uint32_t>(o_kbuf), w.at<int64_t>(o_vbuf), w.at<uint32_t>(o_H),
                     stream);

@@ -64,3 +64,41 @@ def test_vector_solves_of_unequal_windows(lib, B, precision, bar):
 def test_pieces_of_tiles(lib, n, M, B, s, n_u, precision, bar):
     p = synth.make_random(seed=n, n=n, d=4, M=M, s=s, n_u=n_u, B=B, uneven=(max(1, n // M - 15), n // M + 15), sn2=0.05)
     check_fit(lib, p, bar=bar, precision=precision)
+
+
+# partition kernels: sums in the documented order bit for bit (chunks of 4096 points,
+# groups of eight centres), counts in LDS up to 2048 centres and global beyond, the
+# sort's ranks over chunk and wave edges
+@pytest.mark.parametrize("n,k,d", [(1, 1, 1), (63, 7, 3), (65, 8, 2), (4096, 9, 64), (4097, 17, 1), (12300, 300, 5),
+                                   (262145, 33, 2)])
+def test_centre_update_bit_for_bit(lib, n, k, d):
+    rng = np.random.default_rng(n + k)
+    P, C = rng.standard_normal((n, d)), rng.standard_normal((k, d))
+    label = rng.integers(-1, k + 1, size=n).astype(np.int32)  # labels outside 0..k-1 count for no centre
+    label[label == k // 2] = (k // 2 + 1) % k                 # a centre without points
+    sums, count = np.zeros((k, d)), np.zeros(k, dtype=np.int64)
+    for a in range(0, n, 4096):
+        lab, Q = label[a:a + 4096], P[a:a + 4096]
+        ok = (lab >= 0) & (lab < k)
+        count += np.bincount(lab[ok], minlength=k)
+        sums += np.stack([np.bincount(lab[ok], weights=Q[ok, t], minlength=k) for t in range(d)], axis=1)
+    want = np.where(count[:, None] > 0, sums / np.maximum(count, 1)[:, None], C)
+    got, cnt = lib.kmeans_update(P, label, C)
+    assert np.array_equal(cnt.cpu().numpy(), count) and np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,k,d,lo,hi", [(64, 3, 2, 0, 64), (1025, 40, 3, 10, 40), (4700, 2100, 2, 1, 3),
+                                         (70000, 20, 2, 3000, 4000)])
+def test_partition_steps_equal_the_oracle(lib, n, k, d, lo, hi):
+    from oracle import kmeans as okm
+    from oracle import partition as opart
+    rng = np.random.default_rng(n + k)
+    P = np.round(rng.uniform(size=(n, d)), 3)     # ties among distances
+    C = P[rng.choice(n, size=k, replace=False)]
+    lab, dist = lib.kmeans_assign(P, C)
+    lo_, do = okm.assign(P, C)
+    assert np.array_equal(lab.cpu().numpy(), lo_) and np.array_equal(dist.cpu().numpy(), do)
+    lab, cnt, _ = lib.bounded_assign(P, C, lo, hi)
+    want = opart.bounded_assign(P, C, lo, hi)
+    want = want[0] if isinstance(want, tuple) else want
+    assert np.array_equal(lab.cpu().numpy(), want)
