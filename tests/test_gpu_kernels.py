@@ -102,3 +102,42 @@ def test_partition_steps_equal_the_oracle(lib, n, k, d, lo, hi):
     want = opart.bounded_assign(P, C, lo, hi)
     want = want[0] if isinstance(want, tuple) else want
     assert np.array_equal(lab.cpu().numpy(), want)
+
+
+# encoder kernels: sets that end inside a 64-point piece, a 128-point tile with an empty
+# half, one point, and more pieces than workgroups; tolerances of the network's oracle
+# test (float32 accumulation and bfloat16 rounding flips); a backward pass that follows
+# a parameter update uses the activations of its own forward pass
+@pytest.mark.parametrize("sizes", [[1], [63, 64, 65], [128, 129, 1, 191], [4096] * 5 + [77]])
+def test_network_piece_edges(sizes):
+    import torch
+    from paper_1411_4510_amd import warmstart as ws
+    rng = np.random.default_rng(sum(sizes))
+    ptr, sn = ws.aligned_layout(sizes)
+    feats = rng.standard_normal((int(ptr[-1]), ws.NFEAT)).astype(np.float32)  # padding rows hold values too
+    params = ws.he_init(3)
+    labels = rng.standard_normal((len(sizes), ws.NOUT)).astype(np.float32)
+    masks = np.ones_like(labels)
+    net = ws.Network(max_rows=int(ptr[-1]), max_sets=len(sizes))
+    net.set_params(params)
+    out = net.forward(torch.as_tensor(feats, device="cuda"), ptr, sn).cpu().numpy()
+    _, grad = net.backward(labels, masks, want_grad=True)
+    net.adam(0.1)
+    net.adam(0.1)
+    _, after = net.backward(labels, masks, want_grad=True)
+    p = ws.unpack(params)
+    X = torch.as_tensor(feats, dtype=torch.float64)
+    w = {k: torch.tensor(v, dtype=torch.float64, requires_grad=True) for k, v in p.items()}
+    outs = []
+    for b, n in enumerate(sizes):
+        x = X[int(ptr[b]):int(ptr[b]) + n]
+        h = torch.relu(torch.relu(x @ w["W1"].T + w["b1"]) @ w["W2"].T + w["b2"]).mean(0)
+        outs.append(torch.relu(w["W3"] @ h + w["b3"]) @ w["W4"].T + w["b4"])
+    ref = torch.stack(outs)
+    ((ref - torch.as_tensor(labels)) ** 2).mean(1).mean().backward()
+    # against the network without bfloat16 roundings: 2^-9 per operand, five operands deep
+    assert rel(out, ref.detach().numpy()) < 5 * 2.0 ** -8
+    g = ws.unpack(grad.cpu().numpy())
+    for k in g:
+        assert rel(g[k], w[k].grad.numpy()) < 10 * 2.0 ** -8, k
+    assert np.all(np.isfinite(after.cpu().numpy()))
