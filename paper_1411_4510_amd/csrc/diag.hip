@@ -40,7 +40,6 @@ constexpr int NB = 16;          // block edge
 constexpr int NBK = TB / NB;    // blocks per tile side
 constexpr int PLD = NB + 2;     // row stride of the panel in LDS (16-byte aligned rows)
 static_assert(NBK == 8 && NT == 256, "block (i, j): slot (i, j >> 2) of wave j & 3");
-typedef double dv2 __attribute__((ext_vector_type(2)));
 
 // lane l's value of x, the same in every lane
 __device__ inline double lane_value(double x, int l) {
@@ -58,11 +57,6 @@ __device__ inline double rsqrt_pos(double d) {
   const double y = __builtin_amdgcn_rsq(d);
   const double e = __builtin_fmin(__builtin_fma(-(d * y), y, 1.0), 1.0);
   return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
-}
-
-// barrier of the workgroup that orders its LDS accesses only
-__device__ inline void barrier_lds() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 __global__ __launch_bounds__(NT) void k_diag16(StepArgs<double> a, const int32_t* __restrict__ plist) {

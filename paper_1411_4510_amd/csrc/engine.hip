@@ -3,6 +3,7 @@
 #include "engine.h"
 #include "mfma_core.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace lma {
@@ -13,7 +14,8 @@ namespace lma {
 // SUB: MFMA sub-tiles per wave and side.  4: a workgroup computes the whole 128 x 128
 // tile; 2 and 1: one of its 4 (16) pieces of 64 x 64 (32 x 32).
 template <typename T, bool MIXED, int SUB>
-__global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
+__global__ __launch_bounds__(NT, (std::is_same<T, double>::value && SUB == 4) ? 2 : 1) void k_update(StepArgs<T> a) {
+  constexpr bool WG = std::is_same<T, double>::value && SUB == 4;  // operands through LDS
   constexpr int WS = 16 * SUB, QS = 2 * WS, NQ = TB / QS;  // rows of a wave, of a piece; pieces per side
   // covariance tile and V-part precision: float64 when T is double or MIXED
   typedef typename std::conditional<MIXED, double, T>::type TK;
@@ -82,7 +84,10 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
   const TK* vi = MIXED ? (const TK*)ri.vt64 : (const TK*)ri.vt;
   const TK* vj = MIXED ? (const TK*)rj.vt64 : (const TK*)rj.vt;
   if (real && !band && !tband && vi != nullptr && vj != nullptr && a.vlen > 0)
-    wave_gemm<TK, TK>(accv, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, 0, a.vlen, r0, c0, lane);
+    if constexpr (WG)
+      wg_gemm<TK>(accv, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, 0, a.vlen, reinterpret_cast<double*>(smem_raw));
+    else
+      wave_gemm<TK, TK>(accv, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, 0, a.vlen, r0, c0, lane);
   // factor columns kb .. j-1 (a row is zero left of its kbeg)
   const int kb = ri.kbeg > rj.kbeg ? ri.kbeg : rj.kbeg;
   if (real && a.j > kb) {
@@ -91,6 +96,9 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
     if constexpr (MIXED)  // float32 products, sums folded into the float64 accumulators
       wave_gemm_fold(accl, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, 0, (a.j - kb) * TB, r0, c0, lane,
                      accv);
+    else if constexpr (WG)
+      wg_gemm<T>(accv, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, 0, (a.j - kb) * TB,
+                 reinterpret_cast<double*>(smem_raw));
     else
       wave_gemm<T, T>(accv, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, 0, (a.j - kb) * TB, r0, c0, lane);
   }
@@ -99,6 +107,7 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
   TK* xr = reinterpret_cast<TK*>(smem_raw);  // [d][QS] row-side coordinates
   TK* xc = xr + d * QS;                      // [d][QS] column-side coordinates
   const bool kern = ri.src == SRC_KERNEL;
+  if (WG && kern) __syncthreads();  // the operand stages lie where the coordinates go
   if (kern) {
     const TK* xsi = MIXED ? (const TK*)ri.xs64 : (const TK*)ri.xs;
     const TK* xsj = MIXED ? (const TK*)rj.xs64 : (const TK*)rj.xs;
@@ -113,34 +122,30 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
   T* out = ri.panel + (int64_t)(a.j - ri.kbeg) * TB;
   const bool ident = ri.src == SRC_IDENT;
   const bool ident_here = ident && ri.kbeg == a.j;
-  // squared distances of the lane's 64 entries, one coordinate at a time
-  TK sq[SUB][SUB][4];
 #pragma unroll
-  for (int rs = 0; rs < SUB; ++rs)
+  for (int rs = 0; rs < SUB; ++rs) {
+    // squared distances of a 16-row strip, one coordinate at a time
+    TK sq[SUB][4];
 #pragma unroll
     for (int cs = 0; cs < SUB; ++cs)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) sq[rs][cs][v] = TK(0);
-  if (kern && real) {
-    for (int t = 0; t < d; ++t) {
-      TK cv[SUB];
+      for (int v = 0; v < 4; ++v) sq[cs][v] = TK(0);
+    if (kern && real) {
+      for (int t = 0; t < d; ++t) {
+        TK cv[SUB];
 #pragma unroll
-      for (int cs = 0; cs < SUB; ++cs) cv[cs] = xc[t * QS + c0 - q0c + cs * 16 + (lane & 15)];
-#pragma unroll
-      for (int rs = 0; rs < SUB; ++rs)
+        for (int cs = 0; cs < SUB; ++cs) cv[cs] = xc[t * QS + c0 - q0c + cs * 16 + (lane & 15)];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const TK rv = xr[t * QS + r0 - q0r + rs * 16 + Mfma<TK>::row(lane, v)];
 #pragma unroll
           for (int cs = 0; cs < SUB; ++cs) {
             const TK df = rv - cv[cs];
-            sq[rs][cs][v] += df * df;
+            sq[cs][v] += df * df;
           }
         }
+      }
     }
-  }
-#pragma unroll
-  for (int rs = 0; rs < SUB; ++rs) {
 #pragma unroll
     for (int cs = 0; cs < SUB; ++cs) {
 #pragma unroll
@@ -152,7 +157,7 @@ __global__ __launch_bounds__(NT) void k_update(StepArgs<T> a) {
           kv = (ident_here && row == col) ? TK(1) : TK(0);  // exact at padding too
         } else if (row < ri.nvalid && col < rj.nvalid) {
           if (kern) {
-            kv = sf2 * k_exp(TK(-0.5) * sq[rs][cs][v]);
+            kv = sf2 * k_exp(TK(-0.5) * sq[cs][v]);
             if (diag && row == col) kv += sn2;
           } else if (band || tband) {
             kv = TK(0);  // the residual entry started the accumulator (negated)
@@ -217,9 +222,10 @@ __global__ __launch_bounds__(NT) void k_trsm(StepArgs<T> a) {
 // batched float64-accumulating tile GEMM
 // ---------------------------------------------------------------------------
 template <typename T, int SUB>
-__global__ __launch_bounds__(NT) void k_tile_gemm(const GemmTerm<T>* __restrict__ terms,
+__global__ __launch_bounds__(NT, SUB == 4 ? 2 : 1) void k_tile_gemm(const GemmTerm<T>* __restrict__ terms,
                                                   const GemmOut* __restrict__ outs, int nout) {
   constexpr int WS = 16 * SUB, QS = 2 * WS, NQ = TB / QS;  // as in k_update
+  extern __shared__ __align__(16) double sm[];
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
   if (logical >= nout * NQ * NQ) return;
   const GemmOut o = outs[logical / (NQ * NQ)];
@@ -237,7 +243,10 @@ __global__ __launch_bounds__(NT) void k_tile_gemm(const GemmTerm<T>* __restrict_
         for (int b = 0; b < SUB; ++b) acc[a][b] = -acc[a][b];
     }
     const GemmTerm<T> tm = terms[t];
-    wave_gemm<T, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, r0, c0, lane);
+    if constexpr (SUB == 4)
+      wg_gemm<T>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, sm);
+    else
+      wave_gemm<T, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, r0, c0, lane);
   }
   if (o.tneg == o.t1 && o.t1 > o.t0) {  // only subtracted terms
 #pragma unroll
@@ -267,12 +276,17 @@ __global__ __launch_bounds__(NT) void k_tile_gemm(const GemmTerm<T>* __restrict_
 // residual band (float64 arithmetic, one rounding to T on the store)
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(NT) void k_band(BandArgs<T> a) {
+__global__ __launch_bounds__(NT, 2) void k_band(BandArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
   if (logical >= a.nitems) return;
   const BandItem it = a.items[logical];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wr = w >> 1, wc = w & 1;
+  typename Mfma<double>::acc acc[4][4];
+  zero_acc<double>(acc);
+  wg_gemm<double>(acc, a.Vr + it.p0 * a.vld, a.vld, it.nr, a.Vt + it.q0 * a.vld, a.vld, it.nc, 0, a.vlen,
+                  reinterpret_cast<double*>(smem_raw));
+  __syncthreads();  // the operand stages lie where the coordinates go
   // coordinates of the tile's row and column points
   const int d = a.d;
   double* xr = reinterpret_cast<double*>(smem_raw);  // [d][TB]
@@ -282,38 +296,29 @@ __global__ __launch_bounds__(NT) void k_band(BandArgs<T> a) {
     xr[t * TB + r] = r < it.nr ? a.Xr[(it.p0 + r) * d + t] : 0.0;
     xc[t * TB + r] = r < it.nc ? a.Xs[(it.q0 + r) * d + t] : 0.0;
   }
-  typename Mfma<double>::acc acc[4][4];
-  zero_acc<double>(acc);
-  wave_gemm<double, double>(acc, a.Vr + it.p0 * a.vld, a.vld, it.nr, a.Vt + it.q0 * a.vld, a.vld, it.nc, 0, a.vlen,
-                            wr * 64, wc * 64, lane);
   __syncthreads();
-  // squared distances of the lane's 64 entries, one coordinate at a time (its 16
-  // row and 4 column values of a coordinate are read from LDS once)
-  double sq[4][4][4];
 #pragma unroll
-  for (int rs = 0; rs < 4; ++rs)
+  for (int rs = 0; rs < 4; ++rs) {
+    // squared distances of a 16-row strip, one coordinate at a time
+    double sq[4][4];
 #pragma unroll
     for (int cs = 0; cs < 4; ++cs)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) sq[rs][cs][v] = 0.0;
-  for (int t = 0; t < d; ++t) {
-    double cv[4];
+      for (int v = 0; v < 4; ++v) sq[cs][v] = 0.0;
+    for (int t = 0; t < d; ++t) {
+      double cv[4];
 #pragma unroll
-    for (int cs = 0; cs < 4; ++cs) cv[cs] = xc[t * TB + wc * 64 + cs * 16 + (lane & 15)];
-#pragma unroll
-    for (int rs = 0; rs < 4; ++rs)
+      for (int cs = 0; cs < 4; ++cs) cv[cs] = xc[t * TB + wc * 64 + cs * 16 + (lane & 15)];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const double rv = xr[t * TB + wr * 64 + rs * 16 + Mfma<double>::row(lane, v)];
 #pragma unroll
         for (int cs = 0; cs < 4; ++cs) {
           const double df = rv - cv[cs];
-          sq[rs][cs][v] += df * df;
+          sq[cs][v] += df * df;
         }
       }
-  }
-#pragma unroll
-  for (int rs = 0; rs < 4; ++rs)
+    }
 #pragma unroll
     for (int cs = 0; cs < 4; ++cs)
 #pragma unroll
@@ -321,11 +326,12 @@ __global__ __launch_bounds__(NT) void k_band(BandArgs<T> a) {
         const int row = wr * 64 + rs * 16 + Mfma<double>::row(lane, v);
         const int col = wc * 64 + cs * 16 + (lane & 15);
         if (row < it.nr && col < it.nc) {
-          double kv = a.sf2 * k_exp(-0.5 * sq[rs][cs][v]);
+          double kv = a.sf2 * k_exp(-0.5 * sq[cs][v]);
           if (a.noise && it.p0 + row == it.q0 + col) kv += a.sn2;
           a.band[it.off + (int64_t)row * it.ld + col] = (T)(kv - acc[rs][cs][v]);
         }
       }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -354,7 +360,8 @@ static void update_pieces(StepArgs<T> a, int64_t i0, int64_t n, int split, hipSt
   if (n <= 0) return;
   a.items += i0;
   a.nitems = (int32_t)n;
-  const size_t lds = 2 * (size_t)a.d * (TB / split) * (MIXED ? sizeof(double) : sizeof(T));
+  size_t lds = 2 * (size_t)a.d * (TB / split) * (MIXED ? sizeof(double) : sizeof(T));
+  if (std::is_same<T, double>::value && split == 1) lds = std::max(lds, WG_GEMM_LDS);
   const dim3 grid(pad8(a.nitems * split * split));
   switch (split) {
     case 1: hipLaunchKernelGGL((k_update<T, MIXED, 4>), grid, dim3(NT), lds, st, a); break;
@@ -400,7 +407,8 @@ void launch_trsm(const StepArgs<T>& a, hipStream_t st) {
 template <typename T>
 void launch_band(const BandArgs<T>& a, hipStream_t st) {
   if (a.nitems <= 0) return;
-  hipLaunchKernelGGL(k_band<T>, dim3(pad8(a.nitems)), dim3(NT), 2 * (size_t)a.d * TB * sizeof(double), st, a);
+  const size_t lds = std::max(WG_GEMM_LDS, 2 * (size_t)a.d * TB * sizeof(double));
+  hipLaunchKernelGGL(k_band<T>, dim3(pad8(a.nitems)), dim3(NT), lds, st, a);
 }
 
 template <typename T>
@@ -414,7 +422,7 @@ void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, h
   else if (nout <= NCU / 2 || std::is_same<T, float>::value)
     hipLaunchKernelGGL((k_tile_gemm<T, 2>), dim3(pad8(4 * nout)), dim3(NT), 0, st, terms, outs, nout);
   else
-    hipLaunchKernelGGL((k_tile_gemm<T, 4>), dim3(pad8(nout)), dim3(NT), 0, st, terms, outs, nout);
+    hipLaunchKernelGGL((k_tile_gemm<T, 4>), dim3(pad8(nout)), dim3(NT), WG_GEMM_LDS, st, terms, outs, nout);
 }
 
 // Raise the dynamic-LDS limit of the kernels that need more than the default.
@@ -430,6 +438,10 @@ hipError_t engine_init() {
   e = hipFuncSetAttribute((const void*)k_update<float, false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(float)));
   if (e != hipSuccess) return e;
+  for (const void* f : {(const void*)k_tile_gemm<double, 4>, (const void*)k_tile_gemm<float, 4>}) {
+    e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)WG_GEMM_LDS);
+    if (e != hipSuccess) return e;
+  }
   e = hipFuncSetAttribute((const void*)k_band<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(double)));
   if (e != hipSuccess) return e;

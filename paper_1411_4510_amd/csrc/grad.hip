@@ -3,6 +3,7 @@
 #include "mfma_core.h"
 #include "misc.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace lma {
@@ -11,7 +12,7 @@ namespace lma {
 // epilogue adds the rank-one / explicit terms, regenerates the covariance tile
 // from LDS-staged coordinates and contracts it with its d+2 derivatives.
 template <typename TX>
-__global__ __launch_bounds__(NT) void k_dcontract(DcArgs<TX> a) {
+__global__ __launch_bounds__(NT, 2) void k_dcontract(DcArgs<TX> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double red[NT / 64][MAX_D + 2];
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
@@ -20,16 +21,16 @@ __global__ __launch_bounds__(NT) void k_dcontract(DcArgs<TX> a) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wr = w >> 1, wc = w & 1;
   const int d = a.d;
 
+  double* stages = reinterpret_cast<double*>(smem_raw);
   typename Mfma<double>::acc acc[4][4];
   zero_acc<double>(acc);
   for (int t = it.x0; t < it.x1; ++t) {
     const GemmTerm<TX> tm = a.xterms[t];
-    wave_gemm<TX, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, wr * 64, wc * 64, lane);
+    wg_gemm<TX>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, stages);
   }
   for (int t = it.t0; t < it.tneg; ++t) {
     const GemmTerm<double> tm = a.terms[t];
-    wave_gemm<double, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, wr * 64, wc * 64,
-                              lane);
+    wg_gemm<double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, stages);
   }
   if (it.x1 > it.x0 || it.tneg > it.t0) {
 #pragma unroll
@@ -39,10 +40,10 @@ __global__ __launch_bounds__(NT) void k_dcontract(DcArgs<TX> a) {
   }
   for (int t = it.tneg; t < it.t1; ++t) {
     const GemmTerm<double> tm = a.terms[t];
-    wave_gemm<double, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, wr * 64, wc * 64,
-                              lane);
+    wg_gemm<double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, tm.k0, tm.k1, stages);
   }
 
+  __syncthreads();  // the operand stages lie where the coordinates go
   double* xr = reinterpret_cast<double*>(smem_raw);  // [d][TB]
   double* xc = xr + d * TB;                          // [d][TB]
   for (int idx = tid; idx < TB * d; idx += NT) {
@@ -52,36 +53,32 @@ __global__ __launch_bounds__(NT) void k_dcontract(DcArgs<TX> a) {
   }
   __syncthreads();
 
-  // squared distances of the lane's 64 entries, one length-scale at a time
-  double dist[4][4][4];
+  // pass 1: e_ij = wt * A_ij * k_ij (kept in acc), signal and noise sums, a 16-row
+  // strip at a time (its squared distances one length-scale at a time)
+  const bool same_diag = it.kind == DC_SAME && it.diag;
+  const double sf2 = a.sf2, sn2 = a.sn2;
+  double gs = 0.0, gn = 0.0;
 #pragma unroll
-  for (int rs = 0; rs < 4; ++rs)
+  for (int rs = 0; rs < 4; ++rs) {
+    double dist[4][4];
 #pragma unroll
     for (int cs = 0; cs < 4; ++cs)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dist[rs][cs][v] = 0.0;
-  for (int q = 0; q < d; ++q) {
-    double cv[4];
+      for (int v = 0; v < 4; ++v) dist[cs][v] = 0.0;
+    for (int q = 0; q < d; ++q) {
+      double cv[4];
 #pragma unroll
-    for (int cs = 0; cs < 4; ++cs) cv[cs] = xc[q * TB + wc * 64 + cs * 16 + (lane & 15)];
-#pragma unroll
-    for (int rs = 0; rs < 4; ++rs)
+      for (int cs = 0; cs < 4; ++cs) cv[cs] = xc[q * TB + wc * 64 + cs * 16 + (lane & 15)];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const double rv = xr[q * TB + wr * 64 + rs * 16 + Mfma<double>::row(lane, v)];
 #pragma unroll
         for (int cs = 0; cs < 4; ++cs) {
           const double df = rv - cv[cs];
-          dist[rs][cs][v] += df * df;
+          dist[cs][v] += df * df;
         }
       }
-  }
-  // pass 1: e_ij = wt * A_ij * k_ij (kept in acc), signal and noise sums
-  const bool same_diag = it.kind == DC_SAME && it.diag;
-  const double sf2 = a.sf2, sn2 = a.sn2;
-  double gs = 0.0, gn = 0.0;
-#pragma unroll
-  for (int rs = 0; rs < 4; ++rs)
+    }
 #pragma unroll
     for (int cs = 0; cs < 4; ++cs)
 #pragma unroll
@@ -97,12 +94,13 @@ __global__ __launch_bounds__(NT) void k_dcontract(DcArgs<TX> a) {
 #pragma unroll
           for (int x = 0; x < 2; ++x)
             if (x < it.nex) val += it.exs[x] * it.ex[x][(int64_t)row * it.exld[x] + col];
-          e = it.wt * val * (sf2 * exp(-0.5 * dist[rs][cs][v]));
+          e = it.wt * val * (sf2 * exp(-0.5 * dist[cs][v]));
           gs += e;
           if (same_diag && row == col) gn += it.wt * val * sn2;
         }
         acc[rs][cs][v] = e;
       }
+  }
 
   // pass 2: one length-scale at a time
   for (int q = 0; q < d; ++q) {
@@ -200,7 +198,7 @@ static inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 template <typename TX>
 void launch_dcontract(const DcArgs<TX>& a, hipStream_t st) {
   if (a.nitems <= 0) return;
-  const size_t lds = 2 * (size_t)a.d * TB * sizeof(double);
+  const size_t lds = std::max(WG_GEMM_LDS, 2 * (size_t)a.d * TB * sizeof(double));
   hipLaunchKernelGGL(k_dcontract<TX>, dim3(pad8(a.nitems)), dim3(NT), lds, st, a);
 }
 
