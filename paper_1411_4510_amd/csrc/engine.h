@@ -97,7 +97,15 @@ struct StepArgs {
   const T* band;
   const int64_t* brow;
   int32_t mixed_fit;  // 1: Sigma_SS of a mixed-precision fit (which diagonal kernel runs, see diag.hip)
+  // workspace for tiles whose products are split along k (launch_update): PART_TILES tiles
+  // of TB x TB, or null (no tile is split).  In use only within one launch_update.
+  double* part;
+  int32_t nsplit;     // set by launch_update: parts of every tile of a launch
 };
+constexpr int PART_TILES = 512;
+constexpr int64_t PART_BYTES = (int64_t)PART_TILES * TB * TB * sizeof(double);
+// column tiles of a run below which no split pays (products of 128 k per column tile)
+constexpr int PART_MIN_T = 8;
 
 // Residual band: for training point p in block a, the entries
 //   R_pq = sf2 exp(-|x_p - x_q|^2 / 2) + [p == q] sn2 - V_p . V_q

@@ -12,10 +12,11 @@ namespace lma {
 // update: C_ij = K_ij - V_i V_j^T - sum_{k<j} L_ik L_jk^T for every item (p, i)
 // ---------------------------------------------------------------------------
 // SUB: MFMA sub-tiles per wave and side.  4: a workgroup computes the whole 128 x 128
-// tile; 2 and 1: one of its 4 (16) pieces of 64 x 64 (32 x 32).
-template <typename T, bool MIXED, int SUB>
+// tile; 2 and 1: one of its 4 (16) pieces of 64 x 64 (32 x 32).  FIX: the products were
+// formed by k_update_part; their a.nsplit parts are added in order.
+template <typename T, bool MIXED, int SUB, bool FIX = false>
 __global__ __launch_bounds__(NT, (std::is_same<T, double>::value && SUB == 4) ? 2 : 1) void k_update(StepArgs<T> a) {
-  constexpr bool WG = std::is_same<T, double>::value && SUB == 4;  // operands through LDS
+  constexpr bool WG = std::is_same<T, double>::value && SUB == 4 && !FIX;  // operands through LDS
   constexpr int WS = 16 * SUB, QS = 2 * WS, NQ = TB / QS;  // rows of a wave, of a piece; pieces per side
   // covariance tile and V-part precision: float64 when T is double or MIXED
   typedef typename std::conditional<MIXED, double, T>::type TK;
@@ -83,14 +84,24 @@ __global__ __launch_bounds__(NT, (std::is_same<T, double>::value && SUB == 4) ? 
   if constexpr (MIXED) zero_acc<T>(accl);
   const TK* vi = MIXED ? (const TK*)ri.vt64 : (const TK*)ri.vt;
   const TK* vj = MIXED ? (const TK*)rj.vt64 : (const TK*)rj.vt;
-  if (real && !band && !tband && vi != nullptr && vj != nullptr && a.vlen > 0)
+  if (!FIX && real && !band && !tband && vi != nullptr && vj != nullptr && a.vlen > 0)
     if constexpr (WG)
       wg_gemm<TK>(accv, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, 0, a.vlen, reinterpret_cast<double*>(smem_raw));
     else
       wave_gemm<TK, TK>(accv, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, 0, a.vlen, r0, c0, lane);
   // factor columns kb .. j-1 (a row is zero left of its kbeg)
   const int kb = ri.kbeg > rj.kbeg ? ri.kbeg : rj.kbeg;
-  if (real && a.j > kb) {
+  if constexpr (FIX) {
+    const double* part = a.part + (int64_t)(logical / (NQ * NQ)) * a.nsplit * TB * TB;
+    for (int p = 0; p < a.nsplit; ++p, part += TB * TB)
+#pragma unroll
+      for (int rs = 0; rs < SUB; ++rs)
+#pragma unroll
+        for (int cs = 0; cs < SUB; ++cs)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            accv[rs][cs][v] += (TK)part[(r0 + rs * 16 + Mfma<TK>::row(lane, v)) * TB + c0 + cs * 16 + (lane & 15)];
+  } else if (real && a.j > kb) {
     const T* pa = ri.panel + (int64_t)(kb - ri.kbeg) * TB;
     const T* pb = rj.panel + (int64_t)(kb - rj.kbeg) * TB;
     if constexpr (MIXED)  // float32 products, sums folded into the float64 accumulators
@@ -180,6 +191,51 @@ __global__ __launch_bounds__(NT, (std::is_same<T, double>::value && SUB == 4) ? 
       }
     }
   }
+}
+
+// Part `piece` of a.nsplit of the sums over k of every item's tile, to the workspace.
+// Where the tiles of a launch leave the last turn of the CUs nearly empty, or are
+// fewer than the CUs, parts along k fill them at the full rate of whole tiles (64 x 64
+// pieces reach half of it); k_update with FIX adds the parts.  In mixed precision the
+// parts end where a float32 sum is folded, so only float64 sums are reordered.
+template <typename T, bool MIXED>
+__global__ __launch_bounds__(NT, (std::is_same<T, double>::value) ? 2 : 1) void k_update_part(StepArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int logical = xcd_logical(blockIdx.x, gridDim.x);
+  if (logical >= a.nitems * a.nsplit) return;
+  const int piece = logical / a.nitems, item = logical - piece * a.nitems;
+  const WorkItem it = a.items[item];
+  const ProbDesc pd = a.pd[it.p];
+  const RowTile<T> ri = a.rt[pd.first + it.tile];
+  const RowTile<T> rj = a.rt[pd.first + a.j];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r0 = (w >> 1) * 64, c0 = (w & 1) * 64;
+  dv4 acc[4][4];
+  zero_acc<double>(acc);
+  const int kb = ri.kbeg > rj.kbeg ? ri.kbeg : rj.kbeg;
+  // 16-wide chunks per indivisible step; wave_gemm_fold joins a last chunk of its own to
+  // the group before it
+  constexpr int U = MIXED ? FOLD_CHUNKS : 1;
+  const int nc = (a.j - kb) * (TB / 16), nu = U > 1 && nc % U == 1 ? nc / U : (nc + U - 1) / U;
+  const int k0 = 16 * U * (nu * piece / a.nsplit);
+  const int k1 = piece + 1 < a.nsplit ? 16 * U * (nu * (piece + 1) / a.nsplit) : 16 * nc;
+  const T* pa = ri.panel + (int64_t)(kb - ri.kbeg) * TB;
+  const T* pb = rj.panel + (int64_t)(kb - rj.kbeg) * TB;
+  if constexpr (MIXED) {
+    fv4 accl[4][4];
+    zero_acc<float>(accl);
+    if (k1 > k0) wave_gemm_fold(accl, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, k0, k1, r0, c0, lane, acc);
+  } else {
+    if (k1 > k0)
+      wg_gemm<T>(acc, pa, ri.ld, ri.nstore, pb, rj.ld, rj.nstore, k0, k1, reinterpret_cast<double*>(smem_raw));
+  }
+  double* out = a.part + ((int64_t)item * a.nsplit + piece) * TB * TB;
+#pragma unroll
+  for (int rs = 0; rs < 4; ++rs)
+#pragma unroll
+    for (int cs = 0; cs < 4; ++cs)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        out[(r0 + rs * 16 + Mfma<double>::row(lane, v)) * TB + c0 + cs * 16 + (lane & 15)] = acc[rs][cs][v];
 }
 
 // ---------------------------------------------------------------------------
@@ -370,10 +426,60 @@ static void update_pieces(StepArgs<T> a, int64_t i0, int64_t n, int split, hipSt
   }
 }
 
+// A launch of n tiles with products of length k as `whole` tiles in full turns of the
+// CUs, then the rest with its products in `parts` parts along k (1: whole).
+struct UpdatePlan {
+  int64_t whole;
+  int parts;
+  double us;
+};
+
+// Estimated times in us.  Measured for a turn of whole tiles: 1.75 us per 16 k in
+// float64 and 1.05 in mixed precision (float32 products and their folds); the
+// parts are written and read once (128 KB each, 3.5 TB/s) and need a launch more.
+// Measured over all launches (products of k_update, its parts and their sums): full GP
+// n=16384 261 -> 201 ms, n=262144 728 -> 688, n=65536 22.4 -> 21.7, mixed n=50021 36.5 -> 31.3.
+template <bool MIXED>
+static UpdatePlan plan_update(int64_t n, int64_t k, int cap) {
+  const double turn = (MIXED ? 1.05 : 1.75) * (double)(k / 16);
+  UpdatePlan best{n, 1, turn * (double)((n + NCU - 1) / NCU)};
+  for (int64_t whole = n / NCU * NCU; whole >= 0 && whole + 2 * NCU > n; whole -= NCU) {
+    const int64_t rest = n - whole;
+    for (int s = 2; s <= 32 && rest * s <= cap; ++s) {
+      const double us = turn * (double)(whole / NCU) + turn * (double)((rest * s + NCU - 1) / NCU) / s +
+                        2.0 * 131072.0 * (double)(rest * s) / 3.5e6 + (whole ? 12.0 : 8.0);
+      if (us < best.us) best = UpdatePlan{whole, s, us};
+    }
+  }
+  return best;
+}
+
 template <typename T, bool MIXED>
 static void update_launches(const StepArgs<T>& a, hipStream_t st) {
-  const int64_t n = a.nitems, k = (int64_t)a.j * TB + (a.band ? 0 : a.vlen);
+  const int64_t n = a.nitems;
+  const bool vpart = a.vlen > 0 && a.band == nullptr;  // some tiles have a V part before the factor's
+  const int64_t k = (int64_t)a.j * TB + (vpart ? a.vlen : 0);
   const int split = split_of(n, k);
+  if constexpr (MIXED || std::is_same<T, double>::value) {
+    if (a.part != nullptr && !vpart && k > 256) {
+      const UpdatePlan p = plan_update<MIXED>(n, k, PART_TILES);
+      // what the pieces of split_of would take
+      const double turn = (MIXED ? 1.05 : 1.75) * (double)(k / 16);
+      const double pieces = split == 4 ? 0.245 * turn : split == 2 ? 0.48 * turn * (double)((4 * n + NCU - 1) / NCU) : 1e30;
+      if (p.parts > 1 && p.us < pieces) {
+        StepArgs<T> b = a;
+        update_pieces<T, MIXED>(a, 0, p.whole, 1, st);
+        b.items += p.whole;
+        b.nitems = (int32_t)(n - p.whole);
+        b.nsplit = p.parts;
+        hipLaunchKernelGGL((k_update_part<T, MIXED>), dim3(pad8(b.nitems * p.parts)), dim3(NT),
+                           MIXED ? 0 : WG_GEMM_LDS, st, b);
+        const size_t lds = 2 * (size_t)a.d * (TB / 2) * (MIXED ? sizeof(double) : sizeof(T));
+        hipLaunchKernelGGL((k_update<T, MIXED, 2, true>), dim3(pad8(b.nitems * 4)), dim3(NT), lds, st, b);
+        return;
+      }
+    }
+  }
   // up to 64 tiles left over from full turns: a launch of their own, in pieces that fit
   // in half a turn
   const int64_t rest = split == 1 && n % NCU <= NCU / 4 ? n % NCU : 0;
@@ -438,7 +544,8 @@ hipError_t engine_init() {
   e = hipFuncSetAttribute((const void*)k_update<float, false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(float)));
   if (e != hipSuccess) return e;
-  for (const void* f : {(const void*)k_tile_gemm<double, 4>, (const void*)k_tile_gemm<float, 4>}) {
+  for (const void* f : {(const void*)k_tile_gemm<double, 4>, (const void*)k_tile_gemm<float, 4>,
+                        (const void*)k_update_part<double, false>}) {
     e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)WG_GEMM_LDS);
     if (e != hipSuccess) return e;
   }

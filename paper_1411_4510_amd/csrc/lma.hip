@@ -303,7 +303,7 @@ void build_summary(lma_state& f, std::vector<GemmTerm<TW>>& terms, TW* winbase) 
 struct BandPlan {
   std::vector<BandItem> items;
   std::vector<int64_t> brow;
-  int64_t o_items = 0, o_brow = 0, bytes = 0;
+  int64_t o_items = 0, o_brow = 0, o_part = -1, bytes = 0;
   void* mem = nullptr;
   hipStream_t st = nullptr;
   BandPlan() = default;
@@ -496,6 +496,10 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     bpl.o_items = align_up(wsz * off, 256);
     bpl.o_brow = bpl.o_items + align_up((int64_t)sizeof(BandItem) * (int64_t)bpl.items.size(), 256);
     bpl.bytes = bpl.o_brow + 8 * n;
+    if (p->mem_budget_bytes == 0 && maxT >= PART_MIN_T) {  // workspace of the split products behind the band
+      bpl.o_part = align_up(bpl.bytes, 256);
+      bpl.bytes = bpl.o_part + PART_BYTES;
+    }
   }
 
   // engine runs (built with arena offsets; pointers fixed after allocation)
@@ -725,6 +729,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     a.status = status + slot;
     a.maxT = maxTld;
     a.mixed_fit = mixed && slot == (int)M ? 1 : 0;
+    a.part = use_band && bpl.o_part >= 0 ? reinterpret_cast<double*>(static_cast<char*>(bpl.mem) + bpl.o_part) : nullptr;
     for (int j = 0; j < realT; ++j) {
       a.j = j;
       a.items = run.d_items + run.upd_off[j];
@@ -1261,6 +1266,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   const int64_t o_tb = ar.reserve(wsz * std::max<int64_t>(tb_elems, 1));
   const int64_t o_tbi = ar.reserve((int64_t)sizeof(BandItem) * std::max<int64_t>((int64_t)tb_items.size(), 1));
   const int64_t o_tbr = ar.reserve(8 * std::max<int64_t>((int64_t)tb_row.size(), 1));
+  const int64_t o_part = use_tband && maxT >= PART_MIN_T ? ar.reserve(PART_BYTES) : -1;  // split products
   auto build = [&](char* base) {
     ar.base = base;
     runS = Run<double>();
@@ -1563,6 +1569,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     a.logdiag = ldg;
     a.status = stat;
     a.maxT = maxT;
+    a.part = o_part >= 0 ? at<double>(ar, o_part) : nullptr;
     for (int j = 0; j < run.maxT; ++j) {
       a.j = j;
       a.items = run.d_items + run.upd_off[j];

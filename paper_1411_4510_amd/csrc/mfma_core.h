@@ -78,6 +78,7 @@ __device__ inline int xcd_logical(int bid, int nb) {
 // the thousands of k of a late column step loses accuracy linearly in k (about 10x a
 // blocked float32 Cholesky at k ~ 3000); chains of 144 are more accurate than one.
 constexpr int FOLD_ITERS = 3;
+constexpr int FOLD_CHUNKS = FOLD_ITERS * 3;  // 16-wide chunks per fold with the prefetch depth of 2 that folding uses
 template <typename Tin, typename Tc, bool PERMA, int PF, bool FOLD, int RA, int RB>
 __device__ __forceinline__ void wave_gemm_impl(typename Mfma<Tc>::acc (&acc)[RA][RB],
                                                const Tin* __restrict__ A, int64_t lda, int anr,

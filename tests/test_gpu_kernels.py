@@ -141,3 +141,12 @@ def test_network_piece_edges(sizes):
     for k in g:
         assert rel(g[k], w[k].grad.numpy()) < 10 * 2.0 ** -8, k
     assert np.all(np.isfinite(after.cpu().numpy()))
+
+
+# products split along k: one window of 24 column tiles (few tiles per launch), eight of 9
+# with a ragged test set, tiles left over from full turns of the CUs
+@pytest.mark.parametrize("precision,bar", [("fp64", BAR), ("mixed", 1e-4)])
+@pytest.mark.parametrize("n,M,B,s,n_u", [(3000, 1, 0, 60, 100), (3000, 2, 1, 60, 100), (3400, 9, 8, 140, 500)])
+def test_products_split_along_k(lib, n, M, B, s, n_u, precision, bar):
+    p = synth.make_random(seed=n + M, n=n, d=3, M=M, s=s, n_u=n_u, B=B, uneven=(n // M - 30, n // M + 30), sn2=0.05)
+    check_fit(lib, p, bar=bar, precision=precision)
