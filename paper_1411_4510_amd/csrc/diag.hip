@@ -219,18 +219,23 @@ __global__ __launch_bounds__(NT) void k_diag16(StepArgs<double> a, const int32_t
   }
 }
 
-// k_diag32 (mixed fits).  Both run on 32 x 32 blocks.  Factor, for each block column kb: one wave
-// factors the diagonal block in lock step (no workgroup barrier per column),
-// the rows below are solved against it one row per thread, and the trailing
-// block update is spread over the workgroup.  Inverse (in place, X = L^-1):
-// the four diagonal blocks are inverted by the four waves at once, then block
-// columns right to left: T_ib = sum_{k=jb+1..ib} X_ib,k L_k,jb for every block
-// row ib below jb, and X_ib,jb = -T_ib X_jb,jb.  About twenty workgroup
-// barriers per tile instead of two per column.
+// k_diag32 (mixed fits).  Both run on 32 x 32 blocks of the tile in LDS.  Factor, for
+// each block column kb: right-looking columns, pivot root and reciprocal correctly
+// rounded, the rows of the diagonal block scaled by the reciprocal and the rows below
+// divided by the root; then the trailing lower triangle minus one sum over the 32
+// columns.  Inverse (in place, X = L^-1): the four diagonal blocks, last column first,
+// with the even and the odd terms of a sum added at its end; then block columns right
+// to left: T_ib = sum_{k=jb+1..ib} X_ib,k L_k,jb and X_ib,jb = -T_ib X_jb,jb.
+// The float64 matrix instruction is a chain of fused multiply-adds in order of k, so
+// it forms those sums exactly as a loop over k does; the columns of a block run in
+// registers, a row per lane (lanes 0-31 of every wave the diagonal block, lanes 32-63
+// rows below it) with the pivot row by v_readlane.  Bound: the chain of 128 roots,
+// reciprocals and divisions.  Measured per launch: 215 us with the columns and sums as
+// loops over LDS, 62 us in this form, with the same bits.
 constexpr int DLD = TB + 1;      // row stride of the tile in LDS
-constexpr int DB = 32;          // block size of the diagonal-tile algorithms
-constexpr int DNB = TB / DB;    // blocks per tile side
-constexpr int DT_LD = DB + 1;   // row stride of the block products' scratch
+constexpr int DB = 32;           // block edge
+constexpr int DNB = TB / DB;     // blocks per tile side
+constexpr int DT_LD = DB + 1;    // row stride of the block products' scratch
 
 __device__ inline void wave_sync_lds() {
   // LDS writes of this wave are visible to its other lanes after this point
@@ -241,111 +246,98 @@ __device__ inline void wave_sync_lds() {
 
 template <typename T>
 __global__ __launch_bounds__(NT) void k_diag32(StepArgs<T> a, const int32_t* __restrict__ plist) {
-  typedef double TA;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  TA* A = reinterpret_cast<TA*>(smem_raw);  // [TB][DLD]
-  TA* Tt = A + TB * DLD;                // [DNB-1][DB][DT_LD] block products
-  __shared__ int bad;
+  double* A = reinterpret_cast<double*>(smem_raw);  // [TB][DLD]
+  double* Tt = A + TB * DLD;                        // [DNB-1][DB][DT_LD] block products
   __shared__ double lsum[NT / 64];
   const int p = plist[blockIdx.x];
   const ProbDesc pd = a.pd[p];
   const RowTile<T> rj = a.rt[pd.first + a.j];
   T* src = rj.panel + (int64_t)a.j * TB;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid == 0) bad = 0;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lh = lane >> 4;
+#pragma unroll 16
   for (int idx = tid; idx < TB * TB; idx += NT) {
     const int r = idx >> 7, c = idx & (TB - 1);
-    A[r * DLD + c] = c <= r ? (TA)src[(int64_t)r * rj.ld + c] : TA(0);
+    const double v = (double)src[(int64_t)r * rj.ld + c];  // loaded above the diagonal too: no branch
+    A[r * DLD + c] = c <= r ? v : 0.0;
   }
   __syncthreads();
 
   // ---- factor
+  int bad = 0;
   for (int kb = 0; kb < DNB; ++kb) {
     const int b0 = kb * DB;
-    if (w == 0) {  // diagonal block, right-looking, one wave in lock step
-      const int rl = lane & 31, h = lane >> 5, r = b0 + rl;
+    {
+      const bool in_diag = lane < DB;
+      const int r = in_diag ? b0 + lane : b0 + DB + w * DB + (lane - DB);
+      const bool live = r < TB;
+      double* row = A + (live ? r : 0) * DLD + b0;
+      double x[DB];
+#pragma unroll
+      for (int c = 0; c < DB; ++c) x[c] = row[c];
+      auto pivot = [&](double d, double& root, double& ip) {
+        const bool ok = d > 0.0;
+        bad |= !ok;
+        d = ok ? __builtin_fmin(d, 1.7976931348623157e308) : 1.0;
+        // correctly rounded root and reciprocal from the reciprocal root by one residual
+        // each (Markstein's theorems on division and square root)
+        const double y = rsqrt_pos(d), g = d * y;
+        root = __builtin_fma(__builtin_fma(-g, g, d), 0.5 * y, g);
+        ip = __builtin_fma(y, __builtin_fma(-root, y, 1.0), y);
+      };
+      double root, ip;
+      pivot(lane_value(x[0], 0), root, ip);
+#pragma unroll
       for (int k = 0; k < DB; ++k) {
-        const int kk = b0 + k;
-        TA dkk = A[kk * DLD + kk];
-        const bool ok = dkk > TA(0);
-        if (!ok) dkk = TA(1);
-        const TA piv = k_sqrt(dkk), ip = TA(1) / piv;
-        wave_sync_lds();  // every lane has read the pivot
-        if (h == 0) {
-          if (rl > k) {
-            A[r * DLD + kk] *= ip;
-          } else if (rl == k) {
-            A[kk * DLD + kk] = piv;
-            if (!ok) bad = 1;
-          }
+        const double up = x[k] * ip, below = __builtin_fma(__builtin_fma(-root, up, x[k]), ip, up);  // x / root
+        x[k] = lane == k ? root : in_diag ? up : below;
+        if (k + 1 < DB) {  // the next pivot first: its root and reciprocal run beside the other updates
+          x[k + 1] = __builtin_fma(-x[k], lane_value(x[k], k + 1), x[k + 1]);
+          pivot(lane_value(x[k + 1], k + 1), root, ip);
         }
-        wave_sync_lds();  // column kk scaled
-        if (rl > k) {
-          const TA lrk = A[r * DLD + kk];
-          for (int c = kk + 1 + h; c <= r; c += 2) A[r * DLD + c] -= lrk * A[c * DLD + kk];
-        }
-        wave_sync_lds();
+#pragma unroll
+        for (int c = k + 2; c < DB; ++c) x[c] = __builtin_fma(-x[k], lane_value(x[k], c), x[c]);
+        // keeps the updates of column k here (see k_diag16)
+#pragma unroll
+        for (int c = k + 1; c < DB; ++c) asm volatile("" : "+v"(x[c]));
+      }
+      __syncthreads();  // every wave has read the diagonal block
+      if (live && (w == 0 || !in_diag)) {
+#pragma unroll
+        for (int c = 0; c < DB; ++c) row[c] = (in_diag && c > lane) ? 0.0 : x[c];
       }
     }
     __syncthreads();
-    const int m = TB - b0 - DB;  // rows below the block
-    if (m == 0) break;
-    if (tid < m) {  // rows below: solve x L_kb^T = a, one row per thread
-      const int r = b0 + DB + tid;
-      TA x[DB];
+    // trailing lower triangle, one 16 x 16 block per wave at a time
+    const int m16 = (TB - b0 - DB) / 16;
+    for (int t = w; t < m16 * (m16 + 1) / 2; t += NT / 64) {
+      int bi = 0;
+      while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
+      const int r0 = b0 + DB + 16 * bi, c0 = b0 + DB + 16 * (t - bi * (bi + 1) / 2);
+      const double* pa = A + (r0 + l16) * DLD + b0 + lh;
+      const double* pb = A + (c0 + l16) * DLD + b0 + lh;
+      dv4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int c = 0; c < DB; ++c) x[c] = A[r * DLD + b0 + c];
+      for (int e = 0; e < DB / 4; ++e) acc = Mfma<double>::op(pa[4 * e], pb[4 * e], acc);
 #pragma unroll
-      for (int c = 0; c < DB; ++c) {
-        TA sacc = x[c];
-#pragma unroll
-        for (int k = 0; k < c; ++k) sacc -= x[k] * A[(b0 + c) * DLD + b0 + k];
-        x[c] = sacc / A[(b0 + c) * DLD + b0 + c];
+      for (int v = 0; v < 4; ++v) {
+        const int r = r0 + lh + 4 * v, c = c0 + l16;
+        if (c <= r) A[r * DLD + c] -= acc[v];
       }
-#pragma unroll
-      for (int c = 0; c < DB; ++c) A[r * DLD + b0 + c] = x[c];
-    }
-    __syncthreads();
-    // trailing update of the lower triangle below and right of the block, 4 x 4 per thread
-    const int m4 = m >> 2;
-    for (int t = tid; t < m4 * m4; t += NT) {
-      const int bi = t / m4, bj = t - bi * m4;
-      if (bj > bi) continue;
-      const int r0 = b0 + DB + 4 * bi, c0 = b0 + DB + 4 * bj;
-      TA acc[4][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = TA(0);
-      for (int k = 0; k < DB; ++k) {
-        TA ar[4], ac[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          ar[u] = A[(r0 + u) * DLD + b0 + k];
-          ac[u] = A[(c0 + u) * DLD + b0 + k];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[u][v] += ar[u] * ac[v];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (c0 + v <= r0 + u) A[(r0 + u) * DLD + c0 + v] -= acc[u][v];
     }
     __syncthreads();
   }
   if (bad && tid == 0) a.status[p] = 1;
   // store L_jj and its log-diagonal
+#pragma unroll 16
   for (int idx = tid; idx < TB * TB; idx += NT) {
     const int r = idx >> 7, c = idx & (TB - 1);
     src[(int64_t)r * rj.ld + c] = c <= r ? (T)A[r * DLD + c] : T(0);
   }
   {
     double ls = 0.0;
-    if (tid < TB && tid < rj.nvalid) ls = log((double)A[tid * DLD + tid]);
+    if (tid < TB && tid < rj.nvalid) ls = log(A[tid * DLD + tid]);
     for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o);
     if ((tid & 63) == 0) lsum[tid >> 6] = ls;
   }
@@ -357,47 +349,65 @@ __global__ __launch_bounds__(NT) void k_diag32(StepArgs<T> a, const int32_t* __r
 
   // ---- inverse, diagonal blocks: wave w inverts block w, last column first:
   //   X_jj = 1/L_jj,  X_ij = -X_jj sum_{k=j+1..i} X_ik L_kj
+  // lane (i, h) holds row i of X; h takes the terms k = j+1+h, j+3+h, ...
   {
     const int b0 = w * DB, il = lane & 31, h = lane >> 5;
+    double* blk = A + b0 * DLD + b0;
+    const double rec = 1.0 / blk[il * DLD + il];
+    double x[DB];
+#pragma unroll
+    for (int c = 0; c < DB; ++c) x[c] = 0.0;
+#pragma unroll
     for (int jj = DB - 1; jj >= 0; --jj) {
-      const TA xjj = TA(1) / A[(b0 + jj) * DLD + b0 + jj];
-      TA sacc = TA(0);
-      if (il > jj)
-        for (int k = jj + 1 + h; k <= il; k += 2) sacc += A[(b0 + il) * DLD + b0 + k] * A[(b0 + k) * DLD + b0 + jj];
+      const double xjj = lane_value(rec, jj);
+      double sacc = 0.0;
+      const double* col = blk + (jj + 1 + h) * DLD + jj;
+#pragma unroll
+      for (int k = jj + 1; k < DB; k += 2) {
+        // the odd half's last term may lie past the block: its x is zero, its L not read
+        const double xv = h ? (k + 1 < DB ? x[k + 1 < DB ? k + 1 : k] : 0.0) : x[k];
+        const double lv = k + 1 < DB || h == 0 ? col[(k - jj - 1) * DLD] : 0.0;
+        sacc = __builtin_fma(xv, lv, sacc);
+      }
       sacc += __shfl_xor(sacc, 32);
-      wave_sync_lds();  // column jj of L read by every lane
-      if (h == 0 && il > jj) A[(b0 + il) * DLD + b0 + jj] = -xjj * sacc;
-      if (lane == 0) A[(b0 + jj) * DLD + b0 + jj] = xjj;
-      wave_sync_lds();
+      x[jj] = il > jj ? -xjj * sacc : il == jj ? xjj : 0.0;
+      asm volatile("" : "+v"(x[jj]));
     }
+    wave_sync_lds();  // every lane has read L
+    if (h == 0)
+#pragma unroll
+      for (int c = 0; c < DB; ++c) blk[il * DLD + c] = x[c];
   }
   __syncthreads();
   // ---- inverse, block columns right to left
   for (int jb = DNB - 2; jb >= 0; --jb) {
     const int nb = DNB - 1 - jb;
-    for (int e = tid; e < nb * DB * DB; e += NT) {
-      const int q = e / (DB * DB), rem = e - q * (DB * DB), i = rem / DB, jc = rem - i * DB;
-      const int ib = jb + 1 + q;
-      TA sacc = TA(0);
-      for (int kb2 = jb + 1; kb2 <= ib; ++kb2) {
-        const TA* xr = A + (ib * DB + i) * DLD + kb2 * DB;
-        const TA* lc = A + (kb2 * DB) * DLD + jb * DB + jc;
-#pragma unroll 8
-        for (int kk = 0; kk < DB; ++kk) sacc += xr[kk] * lc[kk * DLD];
-      }
-      Tt[(q * DB + i) * DT_LD + jc] = sacc;
+    for (int t = w; t < 4 * nb; t += NT / 64) {
+      const int q = t >> 2, ib = jb + 1 + q, si = (t >> 1) & 1, sj = t & 1;
+      const double* pa = A + (ib * DB + 16 * si + l16) * DLD + lh;
+      const double* pb = A + lh * DLD + jb * DB + 16 * sj + l16;
+      dv4 acc = {0.0, 0.0, 0.0, 0.0};
+      for (int k = (jb + 1) * DB; k < (ib + 1) * DB; k += DB)
+#pragma unroll
+        for (int e = 0; e < DB / 4; ++e) acc = Mfma<double>::op(pa[k + 4 * e], pb[(k + 4 * e) * DLD], acc);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Tt[(q * DB + 16 * si + lh + 4 * v) * DT_LD + 16 * sj + l16] = acc[v];
     }
     __syncthreads();
-    for (int e = tid; e < nb * DB * DB; e += NT) {
-      const int q = e / (DB * DB), rem = e - q * (DB * DB), i = rem / DB, jc = rem - i * DB;
-      const int ib = jb + 1 + q;
-      TA sacc = TA(0);
-      for (int kk = jc; kk < DB; ++kk) sacc += Tt[(q * DB + i) * DT_LD + kk] * A[(jb * DB + kk) * DLD + jb * DB + jc];
-      A[(ib * DB + i) * DLD + jb * DB + jc] = -sacc;
+    for (int t = w; t < 4 * nb; t += NT / 64) {
+      const int q = t >> 2, ib = jb + 1 + q, si = (t >> 1) & 1, sj = t & 1;
+      const double* pa = Tt + (q * DB + 16 * si + l16) * DT_LD + lh;
+      const double* pb = A + (jb * DB + lh) * DLD + jb * DB + 16 * sj + l16;
+      dv4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int e = 0; e < DB / 4; ++e) acc = Mfma<double>::op(pa[4 * e], pb[4 * e * DLD], acc);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) A[(ib * DB + 16 * si + lh + 4 * v) * DLD + jb * DB + 16 * sj + l16] = -acc[v];
     }
     __syncthreads();
   }
   T* inv = a.invdiag + pd.invdiag_off + (int64_t)a.j * TB * TB;
+#pragma unroll 16
   for (int idx = tid; idx < TB * TB; idx += NT) {
     const int r = idx >> 7, c = idx & (TB - 1);
     inv[idx] = c <= r ? (T)A[r * DLD + c] : T(0);
