@@ -437,16 +437,10 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
       f.o_partial = ar.reserve(8 * (int64_t)groups * ntile * TB * TB);
     }
     f.o_Sdd = ar.reserve(8 * sp * sp);
-    f.o_ydd = ar.reserve(8 * sp);
-    f.o_q = ar.reserve(8);
     f.o_Ldd = ar.reserve(8 * panel_elems(Ts, 0));
     f.o_Ldd_inv = ar.reserve(8 * (int64_t)Ts * TB * TB);
-    f.o_g = ar.reserve(8 * sp);
     f.n_logdiag = (int64_t)(M + 2) * std::max(maxT, Ts);
-    f.o_logdiag = ar.reserve(8 * f.n_logdiag);
     f.n_status = M + 2;
-    f.o_status = ar.reserve(4 * f.n_status);
-    f.o_wt = ar.reserve(8 * 10 * M);
     f.o_xJ = ar.reserve(8 * f.vec_elems);
     f.o_xW = ar.reserve(8 * f.vec_elems);
     f.o_tJ = ar.reserve(8 * f.vec_elems);
@@ -613,6 +607,14 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
   auto plan_meta = [&]() {
     build_runs(nullptr);
     meta = runs_meta();
+    // read back together at the end: y_ddot, q, g, log-diagonals, status; filled
+    // together before the first kernel: from the log-diagonals (zero) on
+    f.o_ydd = ar.reserve(8 * sp);
+    f.o_q = ar.reserve(8);
+    f.o_g = ar.reserve(8 * sp);
+    f.o_logdiag = ar.reserve(8 * f.n_logdiag);
+    f.o_status = ar.reserve(4 * f.n_status);
+    f.o_wt = ar.reserve(8 * 10 * M);
     f.o_kvcols = ar.reserve(sizeof(KvCol) * std::max<size_t>(f.kvcols.size(), 1));
     f.o_kvcg = ar.reserve(sizeof(KvItem) * std::max<size_t>(f.kvcg.size(), 1));
     f.o_kvkmv = ar.reserve(sizeof(KvItem) * std::max<size_t>(f.kvkmv.size(), 1));
@@ -621,6 +623,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     f.o_sumterms = ar.reserve(sterm_bytes);
     f.o_sumout = ar.reserve(sizeof(GemmOut) * f.sumout.size());
     f.ar.cap = f.ar.used;
+    f.stage_bytes = f.ar.cap - f.o_logdiag;
   };
   plan_meta();
   const int64_t budget = p->mem_budget_bytes;
@@ -662,47 +665,76 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     }
     build_runs(reinterpret_cast<char*>(mem));
   }
-  // ---- upload schedules
+  // ---- window table
+  int maxTw = 0;
   {
+    std::vector<int64_t> tab(10 * M);
+    int64_t* t_wstart = tab.data();
+    int64_t* t_wlen = t_wstart + M;
+    int64_t* t_dstart = t_wlen + M;
+    int64_t* t_dlen = t_dstart + M;
+    int64_t* t_panel = t_dlen + M;
+    int64_t* t_inv = t_panel + M;
+    int64_t* t_vec = t_inv + M;
+    int64_t* t_rhs = t_vec + M;
+    int32_t* t_T = reinterpret_cast<int32_t*>(t_rhs + M);
+    int32_t* t_tw = t_T + M;
+    int64_t vec_acc = 0;
+    for (int64_t m = 0; m < M; ++m) {
+      const WinGeom g = win_geom(f.bp, M, f.B, m);
+      t_wstart[m] = g.wstart;
+      t_wlen[m] = g.w;
+      t_dstart[m] = g.dstart;
+      t_dlen[m] = g.b;
+      t_panel[m] = f.win_off[m];
+      t_inv[m] = f.inv_off[m];
+      t_vec[m] = vec_acc;
+      t_rhs[m] = f.win_off[m] + jpanel_off(g.T);
+      t_T[m] = g.T;
+      t_tw[m] = g.tw;
+      vec_acc += (int64_t)g.T * TB;
+      maxTw = std::max(maxTw, g.T);
+    }
+    f.wt_host = std::move(tab);
+  }
+  // ---- upload schedules, tables and lists; log-diagonals and status start at zero
+  Stage up(f.ptr<char>(f.o_logdiag), f.stage_bytes, st);
+  {
+    up.zero(f.ptr<char>(f.o_logdiag), 8 * (size_t)f.n_logdiag);
+    up.zero(f.ptr<char>(f.o_status), 4 * (size_t)f.n_status);
     char* mp = f.ptr<char>(f.o_meta);
-    f.runS.upload(mp, st);
+    f.runS.upload(mp, up);
     mp += f.runS.meta_bytes();
     for (auto& r : f.runsW32) {
-      r.upload(mp, st);
+      r.upload(mp, up);
       mp += r.meta_bytes();
     }
     for (auto& r : f.runsW64) {
-      r.upload(mp, st);
+      r.upload(mp, up);
       mp += r.meta_bytes();
     }
-    f.runD.upload(mp, st);
-    if (use_band) {
-      char* bm = static_cast<char*>(bpl.mem);
-      HIPCHK(hipMemcpyAsync(bm + bpl.o_items, bpl.items.data(), sizeof(BandItem) * bpl.items.size(),
-                            hipMemcpyHostToDevice, st));
-      HIPCHK(hipMemcpyAsync(bm + bpl.o_brow, bpl.brow.data(), 8 * n, hipMemcpyHostToDevice, st));
-    }
+    f.runD.upload(mp, up);
     if (mixed)
-      HIPCHK(hipMemcpyAsync(f.ptr<char>(f.o_sumterms), f.sum32.data(), sterm_bytes, hipMemcpyHostToDevice, st));
+      up.put(f.ptr<char>(f.o_sumterms), f.sum32);
     else
-      HIPCHK(hipMemcpyAsync(f.ptr<char>(f.o_sumterms), f.sum64.data(), sterm_bytes, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(f.ptr<char>(f.o_sumout), f.sumout.data(), sizeof(GemmOut) * f.sumout.size(),
-                          hipMemcpyHostToDevice, st));
-    if (!f.kvcols.empty())
-      HIPCHK(hipMemcpyAsync(f.ptr<char>(f.o_kvcols), f.kvcols.data(), sizeof(KvCol) * f.kvcols.size(),
-                            hipMemcpyHostToDevice, st));
-    if (!f.kvcg.empty())
-      HIPCHK(hipMemcpyAsync(f.ptr<char>(f.o_kvcg), f.kvcg.data(), sizeof(KvItem) * f.kvcg.size(),
-                            hipMemcpyHostToDevice, st));
-    if (!f.kvkmv.empty())
-      HIPCHK(hipMemcpyAsync(f.ptr<char>(f.o_kvkmv), f.kvkmv.data(), sizeof(KvItem) * f.kvkmv.size(),
-                            hipMemcpyHostToDevice, st));
+      up.put(f.ptr<char>(f.o_sumterms), f.sum64);
+    up.put(f.ptr<char>(f.o_sumout), f.sumout);
+    up.put(f.ptr<char>(f.o_kvcols), f.kvcols);
+    up.put(f.ptr<char>(f.o_kvcg), f.kvcg);
+    up.put(f.ptr<char>(f.o_kvkmv), f.kvkmv);
+    up.put(f.ptr<char>(f.o_wt), f.wt_host);
+    up.flush();
+  }
+  char* bm = use_band ? static_cast<char*>(bpl.mem) : nullptr;
+  Stage up_band(bm + bpl.o_items, use_band ? bpl.o_brow + 8 * n - bpl.o_items : 0, st);
+  if (use_band) {
+    up_band.put(bm + bpl.o_items, bpl.items);
+    up_band.put(bm + bpl.o_brow, bpl.brow);
+    up_band.flush();
   }
   // ---- compute
   int32_t* status = f.ptr<int32_t>(f.o_status);
   double* logdiag = f.ptr<double>(f.o_logdiag);
-  HIPCHK(hipMemsetAsync(status, 0, 4 * f.n_status, st));
-  HIPCHK(hipMemsetAsync(logdiag, 0, 8 * f.n_logdiag, st));
   prof::timed(prof::OTHER, 0.0, st, [&] { launch_scale(p->X, n, (int)d, f.ie, f.ptr<double>(f.o_Xs64), nullptr, st); });
   prof::timed(prof::OTHER, 0.0, st, [&] { launch_scale(p->S, s, (int)d, f.ie, f.ptr<double>(f.o_Ss64), nullptr, st); });
   prof::timed(prof::OTHER, 0.0, st, [&] { launch_center(p->y, n, f.mu, f.ptr<double>(f.o_c64), f.ptr<float>(f.o_c32), st); });
@@ -832,37 +864,8 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
   }
   // ---- beta_X = R_X^-1 (c_X - K_XS g) for every window and separator
   {
-    std::vector<int64_t> tab(10 * M);
-    int64_t* t_wstart = tab.data();
-    int64_t* t_wlen = t_wstart + M;
-    int64_t* t_dstart = t_wlen + M;
-    int64_t* t_dlen = t_dstart + M;
-    int64_t* t_panel = t_dlen + M;
-    int64_t* t_inv = t_panel + M;
-    int64_t* t_vec = t_inv + M;
-    int64_t* t_rhs = t_vec + M;
-    int32_t* t_T = reinterpret_cast<int32_t*>(t_rhs + M);
-    int32_t* t_tw = t_T + M;
-    int64_t vec_acc = 0;
-    int maxTw = 0;
-    for (int64_t m = 0; m < M; ++m) {
-      const WinGeom g = win_geom(f.bp, M, f.B, m);
-      t_wstart[m] = g.wstart;
-      t_wlen[m] = g.w;
-      t_dstart[m] = g.dstart;
-      t_dlen[m] = g.b;
-      t_panel[m] = f.win_off[m];
-      t_inv[m] = f.inv_off[m];
-      t_vec[m] = vec_acc;
-      t_rhs[m] = f.win_off[m] + jpanel_off(g.T);
-      t_T[m] = g.T;
-      t_tw[m] = g.tw;
-      vec_acc += (int64_t)g.T * TB;
-      maxTw = std::max(maxTw, g.T);
-    }
-    f.wt_host = tab;
+    const int64_t* t_vec = f.wt_host.data() + 6 * M;
     char* dt = f.ptr<char>(f.o_wt);
-    HIPCHK(hipMemcpyAsync(dt, f.wt_host.data(), 8 * 10 * M, hipMemcpyHostToDevice, st));
     const int64_t* dtab = reinterpret_cast<const int64_t*>(dt);
     f.wt.wstart = dtab;
     f.wt.wlen = dtab + M;
@@ -1027,12 +1030,17 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
   std::vector<double> hld(f.n_logdiag);
   f.g.resize(sp);
   f.ydd.resize(sp);
-  HIPCHK(hipMemcpyAsync(hstat.data(), status, 4 * f.n_status, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(hld.data(), logdiag, 8 * f.n_logdiag, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(f.g.data(), f.ptr<double>(f.o_g), 8 * sp, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(f.ydd.data(), f.ptr<double>(f.o_ydd), 8 * sp, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(&f.qsum, f.ptr<double>(f.o_q), 8, hipMemcpyDeviceToHost, st));
+  std::vector<char> back((size_t)(f.o_status + 4 * f.n_status - f.o_ydd));
+  HIPCHK(hipMemcpyAsync(back.data(), f.ptr<char>(f.o_ydd), back.size(), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
+  up.synchronised();
+  up_band.synchronised();
+  auto take = [&](void* dst, int64_t off, size_t bytes) { std::memcpy(dst, back.data() + (off - f.o_ydd), bytes); };
+  take(hstat.data(), f.o_status, 4 * hstat.size());
+  take(hld.data(), f.o_logdiag, 8 * hld.size());
+  take(f.g.data(), f.o_g, 8 * (size_t)sp);
+  take(f.ydd.data(), f.o_ydd, 8 * (size_t)sp);
+  take(&f.qsum, f.o_q, 8);
   prof::flush();
   if (const char* dump = std::getenv("LMA_DUMP_WINDOW")) {  // diagnostic: "m:path" writes window m's panel
     const int64_t m = std::atoll(dump);
@@ -1217,12 +1225,6 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   const int64_t o_G = ar.reserve(8 * n_u * ldG);
   const int64_t o_vn = ar.reserve(8 * n_u);
   const int64_t o_xi = ar.reserve(8 * n_u);
-  const int64_t o_ublk = ar.reserve(4 * n_u);
-  const int64_t o_uptr = ar.reserve(8 * (M + 1));
-  const int64_t o_Xoff = ar.reserve(8 * M);
-  const int64_t o_Tm = ar.reserve(4 * M);
-  const int64_t o_twm = ar.reserve(4 * M);
-  const int64_t o_stat = ar.reserve(4 * (M + 2));
   const int64_t o_ld = ar.reserve(8 * (M + 2) * (int64_t)maxT);  // log-diagonals of refactored windows
   const int64_t o_mtmp = mean ? 0 : ar.reserve(8 * n_u);
   const int64_t o_vtmp = (want_cov && !var) ? ar.reserve(8 * n_u) : 0;
@@ -1264,8 +1266,6 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   std::vector<KvItem> kvitems;
   const int64_t o_hq = ar.reserve(8 * M * sp);
   const int64_t o_tb = ar.reserve(wsz * std::max<int64_t>(tb_elems, 1));
-  const int64_t o_tbi = ar.reserve((int64_t)sizeof(BandItem) * std::max<int64_t>((int64_t)tb_items.size(), 1));
-  const int64_t o_tbr = ar.reserve(8 * std::max<int64_t>((int64_t)tb_row.size(), 1));
   const int64_t o_part = use_tband && maxT >= PART_MIN_T ? ar.reserve(PART_BYTES) : -1;  // split products
   auto build = [&](char* base) {
     ar.base = base;
@@ -1469,6 +1469,15 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   }
   int64_t wmeta = 0;
   for (auto& r : runsW) wmeta += r.meta_bytes();
+  // what the host fills: status words (zero), tables, lists and schedules
+  const int64_t o_stat = ar.reserve(4 * (M + 2));
+  const int64_t o_ublk = ar.reserve(4 * n_u);
+  const int64_t o_uptr = ar.reserve(8 * (M + 1));
+  const int64_t o_Xoff = ar.reserve(8 * M);
+  const int64_t o_Tm = ar.reserve(4 * M);
+  const int64_t o_twm = ar.reserve(4 * M);
+  const int64_t o_tbi = ar.reserve((int64_t)sizeof(BandItem) * std::max<int64_t>((int64_t)tb_items.size(), 1));
+  const int64_t o_tbr = ar.reserve(8 * std::max<int64_t>((int64_t)tb_row.size(), 1));
   const int64_t o_meta = ar.reserve(runS.meta_bytes() + wmeta + runD.meta_bytes());
   const int64_t o_kvc = ar.reserve(sizeof(KvCol) * std::max<size_t>(kvcols.size(), 1));
   const int64_t o_kvi = ar.reserve(sizeof(KvItem) * std::max<size_t>(kvitems.size(), 1));
@@ -1494,60 +1503,40 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     }
   } guard{mem, (size_t)ar.cap, st};
   build(reinterpret_cast<char*>(mem));
-  {
-    char* mp = at<char>(ar, o_meta);
-    runS.upload(mp, st);
-    mp += runS.meta_bytes();
-    for (auto& r : runsW) {
-      r.upload(mp, st);
-      mp += r.meta_bytes();
-    }
-    runD.upload(mp, st);
-    if (!terms.empty())
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_terms), terms.data(), sizeof(GemmTerm<TW>) * terms.size(),
-                            hipMemcpyHostToDevice, st));
-    if (!outs.empty())
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_outs), outs.data(), sizeof(GemmOut) * outs.size(), hipMemcpyHostToDevice,
-                            st));
-    if (!kvcols.empty())
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_kvc), kvcols.data(), sizeof(KvCol) * kvcols.size(), hipMemcpyHostToDevice,
-                            st));
-    if (!kvitems.empty())
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_kvi), kvitems.data(), sizeof(KvItem) * kvitems.size(),
-                            hipMemcpyHostToDevice, st));
-    if (!cb_items.empty())
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_cbi), cb_items.data(), sizeof(BandItem) * cb_items.size(),
-                            hipMemcpyHostToDevice, st));
-    if (!cterms.empty()) {
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_cterms), cterms.data(), sizeof(GemmTerm<double>) * cterms.size(),
-                            hipMemcpyHostToDevice, st));
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_couts), couts.data(), sizeof(GemmOut) * couts.size(),
-                            hipMemcpyHostToDevice, st));
-    }
-    if (!xterms.empty()) {
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_xterms), xterms.data(), sizeof(GemmTerm<TW>) * xterms.size(),
-                            hipMemcpyHostToDevice, st));
-      HIPCHK(hipMemcpyAsync(at<char>(ar, o_xouts), xouts.data(), sizeof(GemmOut) * xouts.size(),
-                            hipMemcpyHostToDevice, st));
-    }
-  }
   std::vector<int32_t> ublk(n_u);
   for (int64_t q = 0; q < M; ++q)
     for (int64_t u = ubp[q]; u < ubp[q + 1]; ++u) ublk[u] = (int32_t)q;
-  std::vector<int64_t> Xoff_h(Xoff);
-  HIPCHK(hipMemcpyAsync(at<char>(ar, o_ublk), ublk.data(), 4 * n_u, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(at<char>(ar, o_uptr), ubp.data(), 8 * (M + 1), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(at<char>(ar, o_Xoff), Xoff_h.data(), 8 * M, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(at<char>(ar, o_Tm), f.Tm.data(), 4 * M, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(at<char>(ar, o_twm), f.twm.data(), 4 * M, hipMemcpyHostToDevice, st));
-  if (use_tband) {
-    HIPCHK(hipMemcpyAsync(at<char>(ar, o_tbi), tb_items.data(), sizeof(BandItem) * tb_items.size(),
-                          hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(at<char>(ar, o_tbr), tb_row.data(), 8 * tb_row.size(), hipMemcpyHostToDevice, st));
+  Stage up(at<char>(ar, o_stat), ar.cap - o_stat, st);
+  {
+    up.zero(at<char>(ar, o_stat), 4 * (size_t)(M + 2));
+    char* mp = at<char>(ar, o_meta);
+    runS.upload(mp, up);
+    mp += runS.meta_bytes();
+    for (auto& r : runsW) {
+      r.upload(mp, up);
+      mp += r.meta_bytes();
+    }
+    runD.upload(mp, up);
+    up.put(at<char>(ar, o_terms), terms);
+    up.put(at<char>(ar, o_outs), outs);
+    up.put(at<char>(ar, o_kvc), kvcols);
+    up.put(at<char>(ar, o_kvi), kvitems);
+    up.put(at<char>(ar, o_cbi), cb_items);
+    up.put(at<char>(ar, o_cterms), cterms);
+    up.put(at<char>(ar, o_couts), couts);
+    up.put(at<char>(ar, o_xterms), xterms);
+    up.put(at<char>(ar, o_xouts), xouts);
+    up.put(at<char>(ar, o_ublk), ublk);
+    up.put(at<char>(ar, o_uptr), ubp);
+    up.put(at<char>(ar, o_Xoff), Xoff);
+    up.put(at<char>(ar, o_Tm), f.Tm);
+    up.put(at<char>(ar, o_twm), f.twm);
+    up.put(at<char>(ar, o_tbi), tb_items);
+    up.put(at<char>(ar, o_tbr), tb_row);
+    up.flush();
   }
   int32_t* stat = at<int32_t>(ar, o_stat);
   double* ldg = at<double>(ar, o_ld);
-  HIPCHK(hipMemsetAsync(stat, 0, 4 * (M + 2), st));
   // scale test inputs
   prof::timed(prof::OTHER, 0.0, st, [&] { launch_scale(U, n_u, (int)d, f.ie, at<double>(ar, o_Us64), nullptr, st); });
   HIPCHK(hipGetLastError());
@@ -1735,6 +1724,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     HIPCHK(hipGetLastError());
   }
   HIPCHK(hipStreamSynchronize(st));
+  up.synchronised();
   prof::flush();
 }
 

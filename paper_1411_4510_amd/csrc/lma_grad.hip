@@ -112,8 +112,8 @@ void solve_steps(Run<TT>& run, TT* invdiag, const lma_state& f, double* ldg, int
 }
 
 template <typename T>
-void upload_vec(char*& dst, const std::vector<T>& v, hipStream_t st) {
-  if (!v.empty()) HIPCHK(hipMemcpyAsync(dst, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice, st));
+void upload_vec(char*& dst, const std::vector<T>& v, Stage& up) {
+  up.put(dst, v);
   dst += align_up((int64_t)sizeof(T) * (int64_t)std::max<size_t>(v.size(), 1), 256);
 }
 template <typename T>
@@ -702,26 +702,28 @@ void grad_run(lma_state& f, double* grad_host, int64_t budget, hipStream_t st, T
   }
   // upload schedules
   char* mp = at<char>(ar, o_meta);
-  runXS.upload(mp, st);
+  Stage up(mp, meta, st);
+  runXS.upload(mp, up);
   mp += runXS.meta_bytes();
-  runXD.upload(mp, st);
+  runXD.upload(mp, up);
   mp += runXD.meta_bytes();
   for (auto& r : runX) {
-    r.upload(mp, st);
+    r.upload(mp, up);
     mp += r.meta_bytes();
   }
   const GemmTerm<TW>* dtw_terms = reinterpret_cast<const GemmTerm<TW>*>(mp);
-  upload_vec(mp, tw_terms, st);
+  upload_vec(mp, tw_terms, up);
   const GemmTerm<double>* dd_terms = reinterpret_cast<const GemmTerm<double>*>(mp);
-  upload_vec(mp, d_terms, st);
+  upload_vec(mp, d_terms, up);
   const GemmOut* douts_tw = reinterpret_cast<const GemmOut*>(mp);
-  upload_vec(mp, outs_tw, st);
+  upload_vec(mp, outs_tw, up);
   const GemmOut* douts_d = reinterpret_cast<const GemmOut*>(mp);
-  upload_vec(mp, outs_d, st);
+  upload_vec(mp, outs_d, up);
   const DcItem* ditems = reinterpret_cast<const DcItem*>(mp);
-  upload_vec(mp, items, st);
+  upload_vec(mp, items, up);
   const GemmTerm<TW>* dx_terms = reinterpret_cast<const GemmTerm<TW>*>(mp);
-  upload_vec(mp, x_terms, st);
+  upload_vec(mp, x_terms, up);
+  up.flush();
 
   double* part = at<double>(ar, o_part);
   int32_t* stat = at<int32_t>(ar, o_stat);
@@ -818,6 +820,7 @@ void grad_run(lma_state& f, double* grad_host, int64_t budget, hipStream_t st, T
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(grad_host, at<double>(ar, o_gdev), 8 * ncomp, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
+  up.synchronised();
   prof::flush();
   for (int q = 0; q < ncomp; ++q)
     if (!std::isfinite(grad_host[q])) throw Err{LMA_E_NOT_PD, "non-finite gradient"};
