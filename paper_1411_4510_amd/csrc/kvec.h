@@ -15,7 +15,7 @@ namespace lma {
 
 enum KvMode : int32_t {
   KV_CG = 0,    // out0[r] = base0[r] - acc0                    (c' = c - K_XS g)
-  KV_MEAN = 1,  // out0[r] = mu + acc0 - acc1 - vt_r . h0        (predictive mean)
+  KV_MEAN = 1,  // out0[r] = mu + acc0 - vt_r . h0               (predictive mean)
   KV_KMV = 2,   // out0[r] = base0[r] - (acc0 + sn2 self0[r] - vt_r . h0), and with flag
                 // out1[r] = base0[r] - (acc1 + sn2 self1[r] - vt_r . h1); padding rows get 0
 };
@@ -50,7 +50,26 @@ struct KvArgs {
   int32_t mode;
   int32_t d, sp;
   double sf2, sn2, mu;
+  int32_t nsplit;   // parts of every item's column list (kvec_split); used only with part
+  double* part;     // [nitems][nsplit][2][128] row sums of the parts, or null (no split)
 };
+
+// Workgroups that a launch is cut into: 4 per CU.
+constexpr int64_t KV_PIECES = 1024;
+// Parts for a launch of nitems items whose longest list has `longest` column tiles, and
+// the doubles they take.
+int kvec_split(int64_t nitems, int64_t longest);
+inline int64_t kvec_part_elems(int64_t nitems, int nsplit) { return nsplit > 1 ? nitems * nsplit * 256 : 0; }
+
+// Weights of the predictive mean of the test points of block q: training points
+// [x0, x1) (blocks q-B .. q+B), to out[.. + x - x0].
+struct KvWeights {
+  int32_t q, pad_;
+  int64_t x0, x1, out;
+};
+// tab: the window table of the fit (10 rows of M)
+void launch_kv_weights(const KvWeights* items, int nitems, int64_t longest, const int64_t* tab, const double* xJ,
+                       const double* xW, double* out, int M, int B, hipStream_t st);
 
 void launch_kvec(const KvArgs& a, hipStream_t st);
 // hq[q] = sum_{dl=0..min(B,q)} hJ[q-dl] - sum_{dl=1..min(B,q)} hW[q-dl]   ([M][sp])

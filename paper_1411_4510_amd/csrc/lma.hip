@@ -973,11 +973,20 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
       kv.sf2 = f.sf2;
       kv.sn2 = f.sn2;
       kv.mu = 0.0;
+      kv.part = use_band && bpl.o_part >= 0
+                    ? reinterpret_cast<double*>(static_cast<char*>(bpl.mem) + bpl.o_part)
+                    : nullptr;
+      int64_t kv_longest = Ts;
+      auto kv_launch = [&] {
+        kv.nsplit = kvec_split(kv.nitems, kv_longest);
+        if (8 * kvec_part_elems(kv.nitems, kv.nsplit) > PART_BYTES) kv.nsplit = 1;
+        launch_kvec(kv, st);
+      };
       // c' = c - K_XS g over all training points
       kv.items = reinterpret_cast<const KvItem*>(f.ptr<char>(f.o_kvcg));
       kv.nitems = (int32_t)f.kvcg.size();
       kv.mode = KV_CG;
-      prof::timed(prof::OTHER, 0.0, st, [&] { launch_kvec(kv, st); });
+      prof::timed(prof::OTHER, 0.0, st, kv_launch);
       for (int c = 0; c < nch; ++c) {
         resident(c);
         // 1. beta0 with the float32 factors
@@ -987,7 +996,8 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
         kv.items = reinterpret_cast<const KvItem*>(f.ptr<char>(f.o_kvkmv)) + f.kmvsplit[f.chunk[c]];
         kv.nitems = (int32_t)(f.kmvsplit[f.chunk[c + 1]] - f.kmvsplit[f.chunk[c]]);
         kv.mode = KV_KMV;
-        prof::timed(prof::OTHER, 0.0, st, [&] { launch_kvec(kv, st); });
+        kv_longest = maxT;
+        prof::timed(prof::OTHER, 0.0, st, kv_launch);
         full_solve(P, I, tJ, tW, c);
         axpy_chunk(1.0, c);
         h_chunk(c);
@@ -1264,6 +1274,26 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   std::vector<int> gsplit;  // streaming: G outputs of chunk ci, delta dl: [gsplit[k], gsplit[k+1]), k = ci*(B+1)+dl
   std::vector<KvCol> kvcols;
   std::vector<KvItem> kvitems;
+  std::vector<KvWeights> kvw;  // mean weights over the training points of each block's span
+  int64_t wq_elems = 0, kv_longest = 0, kv_span = 0;
+  for (int64_t q = 0; q < M; ++q) {
+    if (ubp[q + 1] == ubp[q]) continue;
+    KvWeights w;
+    w.q = (int32_t)q;
+    w.pad_ = 0;
+    w.x0 = f.bp[std::max<int64_t>(0, q - f.B)];
+    w.x1 = f.bp[std::min<int64_t>(M - 1, q + f.B) + 1];
+    w.out = wq_elems;
+    wq_elems += align_up(w.x1 - w.x0, 16);
+    kv_span = std::max(kv_span, w.x1 - w.x0);
+    kv_longest = std::max(kv_longest, cdiv(w.x1 - w.x0, TB) + Ts);
+    kvw.push_back(w);
+  }
+  int64_t nkv = 0;
+  for (int64_t q = 0; q < M; ++q) nkv += cdiv(ubp[q + 1] - ubp[q], TB);
+  const int kv_split = kvec_split(nkv, kv_longest);
+  const int64_t o_wq = ar.reserve(8 * wq_elems);
+  const int64_t o_kvpart = ar.reserve(8 * kvec_part_elems(nkv, kv_split));
   const int64_t o_hq = ar.reserve(8 * M * sp);
   const int64_t o_tb = ar.reserve(wsz * std::max<int64_t>(tb_elems, 1));
   const int64_t o_part = use_tband && maxT >= PART_MIN_T ? ar.reserve(PART_BYTES) : -1;  // split products
@@ -1294,20 +1324,15 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
                                           0));
     }
     runS.schedule();
-    // predictive mean: per test tile of block q, the support tiles with g, the J_m tiles
-    // of windows m = q-B..q with beta_J and (m < q) the W_m tiles with beta_W
+    // predictive mean: per test tile of block q, the support tiles with g and the
+    // training points of blocks q-B .. q+B with their weights
     {
       const double* Xs64 = f.ptr<double>(f.o_Xs64);
-      for (int64_t q = 0; q < M; ++q) {
-        if (ubp[q + 1] == ubp[q]) continue;
+      for (const KvWeights& w : kvw) {
+        const int64_t q = w.q;
         const int c0 = (int)kvcols.size();
         kv_support_cols(kvcols, f.ptr<double>(f.o_Ss64), f.s, d, f.ptr<double>(f.o_g));
-        for (int64_t dl = 0; dl <= f.B && dl <= q; ++dl) {
-          const int64_t m = q - dl;
-          const int64_t vo = f.wt_host[6 * M + m];
-          kv_window_cols(kvcols, win_geom(f.bp, M, f.B, m), Xs64, d, f.ptr<double>(f.o_xJ) + vo,
-                         dl > 0 ? f.ptr<double>(f.o_xW) + vo : nullptr);
-        }
+        kv_point_cols(kvcols, Xs64 + w.x0 * d, w.x1 - w.x0, d, at<double>(ar, o_wq) + w.out);
         const int c1 = (int)kvcols.size();
         for (int64_t u0 = ubp[q]; u0 < ubp[q + 1]; u0 += TB) {
           KvItem it = kv_item(at<double>(ar, o_Us64) + u0 * d, (int)std::min<int64_t>(TB, ubp[q + 1] - u0), c0, c1);
@@ -1481,6 +1506,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   const int64_t o_meta = ar.reserve(runS.meta_bytes() + wmeta + runD.meta_bytes());
   const int64_t o_kvc = ar.reserve(sizeof(KvCol) * std::max<size_t>(kvcols.size(), 1));
   const int64_t o_kvi = ar.reserve(sizeof(KvItem) * std::max<size_t>(kvitems.size(), 1));
+  const int64_t o_kvw = ar.reserve(sizeof(KvWeights) * std::max<size_t>(kvw.size(), 1));
   const int64_t o_terms = ar.reserve(sizeof(GemmTerm<TW>) * std::max<size_t>(terms.size(), 1));
   const int64_t o_outs = ar.reserve(sizeof(GemmOut) * std::max<size_t>(outs.size(), 1));
   const int64_t o_cbi = ar.reserve(sizeof(BandItem) * std::max<size_t>(cb_items.size(), 1));
@@ -1521,6 +1547,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     up.put(at<char>(ar, o_outs), outs);
     up.put(at<char>(ar, o_kvc), kvcols);
     up.put(at<char>(ar, o_kvi), kvitems);
+    up.put(at<char>(ar, o_kvw), kvw);
     up.put(at<char>(ar, o_cbi), cb_items);
     up.put(at<char>(ar, o_cterms), cterms);
     up.put(at<char>(ar, o_couts), couts);
@@ -1582,11 +1609,17 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     prof::timed(prof::OTHER, 0.0, st, [&] {
       launch_hq(f.ptr<double>(f.o_hJ), f.ptr<double>(f.o_hW), at<double>(ar, o_hq), (int)M, (int)f.B, (int)sp, st);
     });
+    prof::timed(prof::OTHER, 0.0, st, [&] {
+      launch_kv_weights(at<KvWeights>(ar, o_kvw), (int)kvw.size(), kv_span, f.ptr<int64_t>(f.o_wt),
+                        f.ptr<double>(f.o_xJ), f.ptr<double>(f.o_xW), at<double>(ar, o_wq), (int)M, (int)f.B, st);
+    });
     KvArgs kv;
     kv.items = at<KvItem>(ar, o_kvi);
     kv.cols = at<KvCol>(ar, o_kvc);
     kv.nitems = (int32_t)kvitems.size();
     kv.mode = KV_MEAN;
+    kv.nsplit = kv_split;
+    kv.part = kv_split > 1 ? at<double>(ar, o_kvpart) : nullptr;
     kv.d = (int)d;
     kv.sp = (int)sp;
     kv.sf2 = f.sf2;

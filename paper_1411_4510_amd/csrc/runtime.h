@@ -433,16 +433,21 @@ inline void kv_window_cols(std::vector<KvCol>& cols, const WinGeom& g, const dou
   }
 }
 
-inline void kv_support_cols(std::vector<KvCol>& cols, const double* Ss, int64_t s, int64_t d, const double* g) {
-  for (int64_t t = 0; t * TB < s; ++t) {
+// n points at x with one vector v
+inline void kv_point_cols(std::vector<KvCol>& cols, const double* x, int64_t n, int64_t d, const double* v) {
+  for (int64_t t = 0; t * TB < n; ++t) {
     KvCol c;
-    c.x = Ss + t * TB * d;
-    c.v0 = g + t * TB;
+    c.x = x + t * TB * d;
+    c.v0 = v + t * TB;
     c.v1 = nullptr;
-    c.nc = (int)std::min<int64_t>(TB, s - t * TB);
+    c.nc = (int)std::min<int64_t>(TB, n - t * TB);
     c.pad_ = 0;
     cols.push_back(c);
   }
+}
+
+inline void kv_support_cols(std::vector<KvCol>& cols, const double* Ss, int64_t s, int64_t d, const double* g) {
+  kv_point_cols(cols, Ss, s, d, g);
 }
 
 inline KvItem kv_item(const double* x, int nr, int c0, int c1) {

@@ -66,6 +66,17 @@ def test_pieces_of_tiles(lib, n, M, B, s, n_u, precision, bar):
     check_fit(lib, p, bar=bar, precision=precision)
 
 
+# mean and residual sums in parts of the column list: row tiles of 1 to 128 points (waves
+# share columns up to 64 rows), lists shorter and longer than the parts, 1024 and more
+# row tiles (no parts), windows at both ends of the overlap
+@pytest.mark.parametrize("precision,bar", [("fp64", BAR), ("mixed", 1e-4)])
+@pytest.mark.parametrize("n,M,B,n_u", [(90, 1, 0, 1), (300, 2, 1, 33), (500, 3, 0, 3 * 17), (900, 4, 3, 4 * 65),
+                                       (1300, 3, 1, 3 * 129), (2600, 1040, 1, 2080)])
+def test_kernel_sums_in_parts(lib, n, M, B, n_u, precision, bar):
+    p = synth.make_random(seed=n + 1, n=n, d=5, M=M, s=50, n_u=n_u, B=B, uneven=(max(1, n // M - 9), n // M + 9), sn2=0.05)
+    check_fit(lib, p, bar=bar, precision=precision)
+
+
 # partition kernels: sums in the documented order bit for bit (chunks of 4096 points,
 # groups of eight centres), counts in LDS up to 2048 centres and global beyond, the
 # sort's ranks over chunk and wave edges
