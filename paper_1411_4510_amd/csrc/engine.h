@@ -76,12 +76,20 @@ struct WorkItem {
   int32_t tile;   // local row-tile index: 0..T-1 J tiles, T..T+R-1 RHS tiles
 };
 
+// Tiles of at most THIN_ROWS valid rows (the output row of a window, a few test points):
+// thin.n of them stand last in a list, thin.rows is the largest row count among them.
+constexpr int THIN_ROWS = 64;
+struct Thin {
+  int32_t n, rows;
+};
+
 template <typename T>
 struct StepArgs {
   const RowTile<T>* rt;
   const ProbDesc* pd;
   const WorkItem* items;
   int32_t nitems;
+  Thin thin;          // right-hand-side tiles of few rows among the update items
   int32_t j;          // column tile of this step
   int32_t vlen;       // length of the whitened support rows (multiple of 16)
   int32_t d;
@@ -120,10 +128,14 @@ struct BandItem {
   int64_t ld;       // panel row stride (elements)
   int32_t nr, nc;   // valid rows / columns
 };
+// With BandArgs::brow, entry (p, q) lies at band[brow[p] + q] instead (off and ld unused):
+// the rows of a tile may then be points of several blocks.
 template <typename T>
 struct BandArgs {
   const BandItem* items;
   int32_t nitems;
+  Thin thin;
+  const int64_t* brow;
   int32_t d;
   int32_t vlen;       // length of the whitened support rows (multiple of 16)
   int32_t noise;      // 1: add sn2 where the row and column index agree (rows and columns are one point set)
@@ -188,6 +200,6 @@ inline GemmOut gemm_out(double* out, int64_t ld, int rows, int cols, int accumul
   return o;
 }
 template <typename T>
-void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, hipStream_t st);
+void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, Thin thin, hipStream_t st);
 
 }  // namespace lma

@@ -239,6 +239,189 @@ __global__ __launch_bounds__(NT, (std::is_same<T, double>::value) ? 2 : 1) void 
 }
 
 // ---------------------------------------------------------------------------
+// thin tiles: at most 16 RS valid rows
+// ---------------------------------------------------------------------------
+// Bound: reading the other operand once.  A whole tile costs its 128 rows of products
+// however few are real; here a workgroup takes 16 of the 128 columns and its 8 waves (4
+// from 64 rows on) share the sums over k, so a launch of 60 tiles has 4000 waves with six
+// chunks in flight each.  The waves' sums are added through LDS in order.
+// Measured: test rows of 100 points (62 tiles of 1 to 14 rows, k up to 3000) 108 -> 45 us
+// a launch, their products with the support rows 664 -> 250 us, their residual band (with
+// tiles over several blocks) 506 -> 83; a prediction 3.41 -> 1.60 ms, covariance of 512
+// points 2.73 -> 2.17 ms, fit and prediction of n=65536 34.8 -> 34.0 ms, mixed n=50021
+// 53.2 -> 51.0, n=262144 all updates 690 -> 676.
+template <int RS>
+struct ThinShape {
+  static constexpr int NW = RS < 4 ? 8 : 4, THREADS = 64 * NW, ELEMS = RS * 256;
+};
+
+// this wave's share of [k0, k1) in units of U chunks of 16; a last chunk of its own joins
+// the unit before it (as the folds of wave_gemm_fold do)
+template <int U, int NW>
+__device__ inline void thin_share(int k0, int k1, int w, int* a, int* b) {
+  const int nc = (k1 - k0) >> 4, nu = U > 1 && nc % U == 1 && nc > 1 ? nc / U : (nc + U - 1) / U;
+  *a = k0 + 16 * U * (nu * w / NW);
+  *b = w + 1 < NW ? k0 + 16 * U * (nu * (w + 1) / NW) : k0 + 16 * nc;
+}
+
+// red[w][row][16 columns] of this wave, then the barrier
+template <int RS>
+__device__ inline void thin_put(const dv4 (&acc)[RS][1], double* red, int w, int lane) {
+#pragma unroll
+  for (int rs = 0; rs < RS; ++rs)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      red[w * ThinShape<RS>::ELEMS + (rs * 16 + Mfma<double>::row(lane, v)) * 16 + (lane & 15)] = acc[rs][0][v];
+  __syncthreads();
+}
+template <int RS>
+__device__ inline double thin_sum(const double* red, int e) {
+  double s = red[e];
+#pragma unroll
+  for (int w = 1; w < ThinShape<RS>::NW; ++w) s += red[w * ThinShape<RS>::ELEMS + e];
+  return s;
+}
+
+template <typename T, bool MIXED, int RS>
+__global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_update_thin(StepArgs<T> a) {
+  typedef typename std::conditional<MIXED, double, T>::type TK;
+  static_assert(std::is_same<TK, double>::value, "sums in float64");
+  constexpr int NW = ThinShape<RS>::NW;
+  __shared__ double red[NW * ThinShape<RS>::ELEMS];
+  const int logical = xcd_logical(blockIdx.x, gridDim.x);
+  if (logical >= a.nitems * 8) return;
+  const WorkItem it = a.items[logical / 8];
+  const ProbDesc pd = a.pd[it.p];
+  const RowTile<T> ri = a.rt[pd.first + it.tile];
+  const RowTile<T> rj = a.rt[pd.first + a.j];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c0 = logical % 8 * 16;
+  const bool real = c0 < rj.nvalid, band = ri.src == SRC_BAND || ri.src == SRC_TBAND;
+  dv4 acc[RS][1];
+  zero_acc<double>(acc);
+  const double* vi = MIXED ? ri.vt64 : (const double*)ri.vt;
+  const double* vj = MIXED ? rj.vt64 : (const double*)rj.vt;
+  int k0, k1;
+  if (real && !band && vi != nullptr && vj != nullptr && a.vlen > 0) {
+    thin_share<1, NW>(0, a.vlen, w, &k0, &k1);
+    wave_gemm<double, double>(acc, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, k0, k1, 0, c0, lane);
+  }
+  const int kb = ri.kbeg > rj.kbeg ? ri.kbeg : rj.kbeg;
+  if (real && a.j > kb) {
+    const T* pa = ri.panel + (int64_t)(kb - ri.kbeg) * TB;
+    const T* pb = rj.panel + (int64_t)(kb - rj.kbeg) * TB;
+    thin_share<MIXED ? FOLD_CHUNKS : 1, NW>(0, (a.j - kb) * TB, w, &k0, &k1);
+    if constexpr (MIXED) {
+      fv4 accl[RS][1];
+      zero_acc<float>(accl);
+      wave_gemm_fold(accl, pa, ri.ld, ri.nvalid, pb, rj.ld, rj.nstore, k0, k1, 0, c0, lane, acc);
+    } else {
+      wave_gemm<T, T>(acc, pa, ri.ld, ri.nvalid, pb, rj.ld, rj.nstore, k0, k1, 0, c0, lane);
+    }
+  }
+  thin_put<RS>(acc, red, w, lane);
+  T* out = ri.panel + (int64_t)(a.j - ri.kbeg) * TB + c0;
+  const int stored = ri.nstore < 16 * RS ? ri.nstore : 16 * RS;
+  for (int e = tid; e < stored * 16; e += ThinShape<RS>::THREADS) {
+    const int row = e >> 4, col = c0 + (e & 15);
+    double val = 0.0;  // padding
+    if (row < ri.nvalid && col < rj.nvalid) {
+      double kv;
+      if (band) {
+        const int64_t p = ri.pt0 + row, q = rj.pt0 + col;
+        kv = (double)a.band[ri.src == SRC_TBAND || q <= p ? a.brow[p] + q : a.brow[q] + p];
+      } else if (ri.src == SRC_KERNEL) {
+        const double* x = (MIXED ? ri.xs64 : (const double*)ri.xs) + (int64_t)row * a.d;
+        const double* y = (MIXED ? rj.xs64 : (const double*)rj.xs) + (int64_t)col * a.d;
+        double sq = 0.0;
+        for (int t = 0; t < a.d; ++t) {
+          const double df = x[t] - y[t];
+          sq += df * df;
+        }
+        kv = a.sf2 * k_exp(-0.5 * sq);
+      } else if (ri.src == SRC_EXPLICIT) {
+        kv = (double)ri.expl[(int64_t)row * ri.eld + (int64_t)a.j * TB + col];
+      } else {
+        kv = row == 0 ? (double)rj.cv[col] : 0.0;
+      }
+      val = kv - thin_sum<RS>(red, e);
+    }
+    out[(int64_t)row * ri.ld + (e & 15)] = (T)val;
+  }
+  for (int e = tid + 16 * RS * 16; e < ri.nstore * 16; e += ThinShape<RS>::THREADS)
+    out[(int64_t)(e >> 4) * ri.ld + (e & 15)] = T(0);
+}
+
+template <typename T, int RS>
+__global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_tile_gemm_thin(const GemmTerm<T>* __restrict__ terms,
+                                                                           const GemmOut* __restrict__ outs, int nout) {
+  constexpr int NW = ThinShape<RS>::NW;
+  __shared__ double red[NW * ThinShape<RS>::ELEMS];
+  const int logical = xcd_logical(blockIdx.x, gridDim.x);
+  if (logical >= nout * 8) return;
+  const GemmOut o = outs[logical / 8];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c0 = logical % 8 * 16;
+  if (c0 >= o.cols) return;
+  dv4 acc[RS][1];
+  zero_acc<double>(acc);
+  for (int t = o.t0; t < o.t1; ++t) {
+    if (t == o.tneg && t > o.t0) {
+#pragma unroll
+      for (int r = 0; r < RS; ++r) acc[r][0] = -acc[r][0];
+    }
+    const GemmTerm<T> tm = terms[t];
+    int k0, k1;
+    thin_share<1, NW>(tm.k0, tm.k1, w, &k0, &k1);
+    wave_gemm<T, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, k0, k1, 0, c0, lane);
+  }
+  if (o.tneg == o.t1 && o.t1 > o.t0) {  // only subtracted terms
+#pragma unroll
+    for (int r = 0; r < RS; ++r) acc[r][0] = -acc[r][0];
+  }
+  thin_put<RS>(acc, red, w, lane);
+  for (int e = tid; e < o.rows * 16; e += ThinShape<RS>::THREADS) {
+    const int row = e >> 4, col = c0 + (e & 15);
+    if (col >= o.cols) continue;
+    double* q = o.out + (int64_t)row * o.ld + col;
+    double r = o.alpha * thin_sum<RS>(red, e);
+    if (o.c) r += o.beta * o.c[(int64_t)row * o.ldc + col];
+    *q = o.accumulate ? *q + r : r;
+  }
+}
+
+template <typename T, int RS>
+__global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_band_thin(BandArgs<T> a) {
+  constexpr int NW = ThinShape<RS>::NW;
+  __shared__ double red[NW * ThinShape<RS>::ELEMS];
+  const int logical = xcd_logical(blockIdx.x, gridDim.x);
+  if (logical >= a.nitems * 8) return;
+  const BandItem it = a.items[logical / 8];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c0 = logical % 8 * 16;
+  if (c0 >= it.nc) return;
+  dv4 acc[RS][1];
+  zero_acc<double>(acc);
+  int k0, k1;
+  thin_share<1, NW>(0, a.vlen, w, &k0, &k1);
+  wave_gemm<double, double>(acc, a.Vr + it.p0 * a.vld, a.vld, it.nr, a.Vt + it.q0 * a.vld, a.vld, it.nc, k0, k1, 0, c0,
+                            lane);
+  thin_put<RS>(acc, red, w, lane);
+  for (int e = tid; e < it.nr * 16; e += ThinShape<RS>::THREADS) {
+    const int row = e >> 4, col = c0 + (e & 15);
+    if (col >= it.nc) continue;
+    const double* x = a.Xr + (it.p0 + row) * a.d;
+    const double* y = a.Xs + (it.q0 + col) * a.d;
+    double sq = 0.0;
+    for (int t = 0; t < a.d; ++t) {
+      const double df = x[t] - y[t];
+      sq += df * df;
+    }
+    double kv = a.sf2 * k_exp(-0.5 * sq);
+    if (a.noise && it.p0 + row == it.q0 + col) kv += a.sn2;
+    const int64_t at = a.brow ? a.brow[it.p0 + row] + it.q0 : it.off + (int64_t)row * it.ld;
+    a.band[at + col] = (T)(kv - thin_sum<RS>(red, e));
+  }
+}
+
+// ---------------------------------------------------------------------------
 // trsm: L_ij = C_ij L_jj^-T (in place) for every item (p, i), i != j
 // ---------------------------------------------------------------------------
 // The inverse is lower triangular, so the sum for columns [c0, c0 + n) ends at
@@ -253,7 +436,7 @@ __global__ __launch_bounds__(NT) void k_trsm(StepArgs<T> a) {
   const WorkItem it = a.items[logical / NP];
   const ProbDesc pd = a.pd[it.p];
   const RowTile<T> ri = a.rt[pd.first + it.tile];
-  if (logical % NP * RS >= ri.nstore) return;
+  if (logical % NP * RS >= ri.nvalid) return;  // rows from nvalid on are zero and stay so
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int r0 = logical % NP * RS + w / WC * WS, c0 = w % WC * WS;
   T* C = ri.panel + (int64_t)(a.j - ri.kbeg) * TB;
@@ -384,7 +567,8 @@ __global__ __launch_bounds__(NT, 2) void k_band(BandArgs<T> a) {
         if (row < it.nr && col < it.nc) {
           double kv = a.sf2 * k_exp(-0.5 * sq[cs][v]);
           if (a.noise && it.p0 + row == it.q0 + col) kv += a.sn2;
-          a.band[it.off + (int64_t)row * it.ld + col] = (T)(kv - acc[rs][cs][v]);
+          const int64_t at = a.brow ? a.brow[it.p0 + row] + it.q0 : it.off + (int64_t)row * it.ld;
+          a.band[at + col] = (T)(kv - acc[rs][cs][v]);
         }
       }
   }
@@ -454,11 +638,62 @@ static UpdatePlan plan_update(int64_t n, int64_t k, int cap) {
   return best;
 }
 
+// Time of a launch of n tiles without thin ones, in us, on the same terms; the launch
+// itself and the epilogue are left out.
+template <bool MIXED>
+static double update_us(int64_t n, int64_t k, bool can_part) {
+  if (n <= 0) return 0.0;
+  const int split = split_of(n, k);
+  const double turn = (MIXED ? 1.05 : 1.75) * (double)(k / 16);
+  const double pieces = split == 4 ? 0.245 * turn * (double)((16 * n + NCU - 1) / NCU)
+                                   : split == 2 ? 0.48 * turn * (double)((4 * n + NCU - 1) / NCU) : 1e30;
+  const double whole = can_part ? plan_update<MIXED>(n, k, PART_TILES).us : turn * (double)((n + NCU - 1) / NCU);
+  return std::min(pieces, whole);
+}
+
+// row groups of 16 (1, 2 or 4) that hold `rows` rows
+static inline int thin_rs(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 : 4; }
+
+// Time of n thin tiles with products of length k: the other operand from memory, or the
+// products (256 cycles per row group and 16 k on each SIMD), and the launch.
+template <typename T>
+static double thin_us(int64_t n, int64_t k, int rs) {
+  const double bytes = (double)n * TB * (double)k * sizeof(T) / 4.0e6;
+  const double prod = (double)(n * 8) * (double)(k / 16) * 256.0 * rs / (1024.0 * 2400.0);
+  return 6.0 + std::max(bytes, prod);
+}
+
 template <typename T, bool MIXED>
 static void update_launches(const StepArgs<T>& a, hipStream_t st) {
   const int64_t n = a.nitems;
   const bool vpart = a.vlen > 0 && a.band == nullptr;  // some tiles have a V part before the factor's
   const int64_t k = (int64_t)a.j * TB + (vpart ? a.vlen : 0);
+  if constexpr (MIXED || std::is_same<T, double>::value) {
+    if (a.thin.n > 0) {
+      // Thin tiles in a launch of their own where that is estimated to take less than
+      // they add as whole tiles; always where the launch has no others.
+      const int64_t full = n - a.thin.n;
+      const int rs = thin_rs(a.thin.rows);
+      const bool part = a.part != nullptr && !vpart && k > 256;
+      StepArgs<T> b = a;
+      b.thin = Thin{0, 0};
+      if (full == 0 || update_us<MIXED>(n, k, part) - update_us<MIXED>(full, k, part) > thin_us<T>(a.thin.n, k, rs)) {
+        b.nitems = (int32_t)full;
+        if (full > 0) update_launches<T, MIXED>(b, st);
+        b.items += full;
+        b.nitems = a.thin.n;
+        const dim3 grid(pad8(8 * a.thin.n));
+        switch (rs) {
+          case 1: hipLaunchKernelGGL((k_update_thin<T, MIXED, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, b); break;
+          case 2: hipLaunchKernelGGL((k_update_thin<T, MIXED, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, b); break;
+          default: hipLaunchKernelGGL((k_update_thin<T, MIXED, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, b);
+        }
+      } else {
+        update_launches<T, MIXED>(b, st);
+      }
+      return;
+    }
+  }
   const int split = split_of(n, k);
   if constexpr (MIXED || std::is_same<T, double>::value) {
     if (a.part != nullptr && !vpart && k > 256) {
@@ -514,11 +749,34 @@ template <typename T>
 void launch_band(const BandArgs<T>& a, hipStream_t st) {
   if (a.nitems <= 0) return;
   const size_t lds = std::max(WG_GEMM_LDS, 2 * (size_t)a.d * TB * sizeof(double));
-  hipLaunchKernelGGL(k_band<T>, dim3(pad8(a.nitems)), dim3(NT), lds, st, a);
+  BandArgs<T> b = a;
+  b.nitems -= a.thin.n;
+  if (b.nitems > 0) hipLaunchKernelGGL(k_band<T>, dim3(pad8(b.nitems)), dim3(NT), lds, st, b);
+  if (a.thin.n <= 0) return;
+  b.items += b.nitems;
+  b.nitems = a.thin.n;
+  const dim3 grid(pad8(8 * b.nitems));
+  switch (thin_rs(a.thin.rows)) {
+    case 1: hipLaunchKernelGGL((k_band_thin<T, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, b); break;
+    case 2: hipLaunchKernelGGL((k_band_thin<T, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, b); break;
+    default: hipLaunchKernelGGL((k_band_thin<T, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, b);
+  }
 }
 
 template <typename T>
-void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, hipStream_t st) {
+void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, Thin thin, hipStream_t st) {
+  // thin outputs apart, unless there are so few others that their pieces (of which those
+  // without a row end at once) fill no more than a turn
+  if (thin.n > 0 && (thin.n == nout || nout > 64)) {
+    nout -= thin.n;
+    const GemmOut* to = outs + nout;
+    const dim3 grid(pad8(8 * thin.n));
+    switch (thin_rs(thin.rows)) {
+      case 1: hipLaunchKernelGGL((k_tile_gemm_thin<T, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, terms, to, thin.n); break;
+      case 2: hipLaunchKernelGGL((k_tile_gemm_thin<T, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, terms, to, thin.n); break;
+      default: hipLaunchKernelGGL((k_tile_gemm_thin<T, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, terms, to, thin.n);
+    }
+  }
   if (nout <= 0) return;
   // measured, whole / 4 / 16 pieces: float64 n = 48 204 / 75 / 110 us, n = 112 178 / 128 / 204,
   // n = 176 80 / 94 / 129; float32 operands leave the registers for three workgroups of
@@ -562,7 +820,7 @@ template void launch_trsm<double>(const StepArgs<double>&, hipStream_t);
 template void launch_trsm<float>(const StepArgs<float>&, hipStream_t);
 template void launch_band<double>(const BandArgs<double>&, hipStream_t);
 template void launch_band<float>(const BandArgs<float>&, hipStream_t);
-template void launch_tile_gemm<double>(const GemmTerm<double>*, const GemmOut*, int, hipStream_t);
-template void launch_tile_gemm<float>(const GemmTerm<float>*, const GemmOut*, int, hipStream_t);
+template void launch_tile_gemm<double>(const GemmTerm<double>*, const GemmOut*, int, Thin, hipStream_t);
+template void launch_tile_gemm<float>(const GemmTerm<float>*, const GemmOut*, int, Thin, hipStream_t);
 
 }  // namespace lma

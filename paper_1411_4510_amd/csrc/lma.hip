@@ -275,7 +275,7 @@ void build_summary(lma_state& f, std::vector<GemmTerm<TW>>& terms, TW* winbase) 
     for (int ta = 0; ta < nt; ++ta)
       for (int tb = 0; tb <= ta; ++tb) {
         const int t = ta * (ta + 1) / 2 + tb;
-        GemmOut o = gemm_out(partial + ((int64_t)gi * f.ntile + t) * TB * TB, TB, TB, TB, 0, (int)terms.size());
+        GemmOut o = gemm_out(partial + ((int64_t)gi * f.ntile + t) * TB * TB, TB, ta == Ts ? 1 : TB, TB, 0, (int)terms.size());
         for (int64_t m = m0; m < m1; ++m) {
           const WinGeom g = win_geom(f.bp, f.M, f.B, m);
           TW* rhs = winbase + f.win_off[m] + jpanel_off(g.T);
@@ -283,7 +283,7 @@ void build_summary(lma_state& f, std::vector<GemmTerm<TW>>& terms, TW* winbase) 
           GemmTerm<TW> tm;
           tm.a = rhs + (int64_t)ta * TB * ld;
           tm.lda = ld;
-          tm.anr = TB;
+          tm.anr = o.rows;
           tm.b = rhs + (int64_t)tb * TB * ld;
           tm.ldb = ld;
           tm.bnr = TB;
@@ -329,7 +329,8 @@ void build_summary_chunk(lma_state& f, std::vector<GemmTerm<TW>>& terms, TW* win
   for (int ta = 0; ta < nt; ++ta)
     for (int tb = 0; tb <= ta; ++tb) {
       const int t = ta * (ta + 1) / 2 + tb;
-      GemmOut o = gemm_out(partial + (int64_t)t * TB * TB, TB, TB, TB, accumulate ? 1 : 0, (int)terms.size());
+      GemmOut o = gemm_out(partial + (int64_t)t * TB * TB, TB, ta == nt - 1 ? 1 : TB, TB, accumulate ? 1 : 0,
+                           (int)terms.size());
       for (int64_t m = m0; m < m1; ++m) {
         const WinGeom g = win_geom(f.bp, f.M, f.B, m);
         TW* rhs = winbase + f.win_off[m] + jpanel_off(g.T);
@@ -337,7 +338,7 @@ void build_summary_chunk(lma_state& f, std::vector<GemmTerm<TW>>& terms, TW* win
         GemmTerm<TW> tm;
         tm.a = rhs + (int64_t)ta * TB * ld;
         tm.lda = ld;
-        tm.anr = TB;
+        tm.anr = o.rows;
         tm.b = rhs + (int64_t)tb * TB * ld;
         tm.ldb = ld;
         tm.bnr = TB;
@@ -537,6 +538,9 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
         f.sumsplit.pop_back();
       }
       f.sumsplit.push_back((int64_t)f.sumout.size());
+      f.sumthin.clear();
+      for (size_t c = 0; c + 1 < f.sumsplit.size(); ++c)
+        f.sumthin.push_back(thin_last(f.sumout.data() + f.sumsplit[c], f.sumout.data() + f.sumsplit[c + 1]));
     };
     if (mixed)
       window_runs(f.runsW32, f.sum32, f.ptr<float>(f.o_win), f.ptr<float>(f.o_c32));
@@ -766,6 +770,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
       a.j = j;
       a.items = run.d_items + run.upd_off[j];
       a.nitems = (int32_t)run.upd_n[j];
+      a.thin = run.upd_thin[j];
       double f64 = 0.0;
       const double fl = prof::on ? run.update_flops(j, vlen > 0 ? s : 0, &f64) : 0.0;
       prof::timed(prof::UPDATE, fl, st, [&] { launch_update<TT>(a, std::is_same<TT, float>::value, st); }, f64);
@@ -822,12 +827,12 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     if (mixed)
       prof::timed(prof::GEMM, prof::on ? gemm_flops(f.sum32, f.sumout, o0, o1) : 0.0, st, [&] {
         launch_tile_gemm<float>(reinterpret_cast<const GemmTerm<float>*>(f.ptr<char>(f.o_sumterms)), douts,
-                                (int)(o1 - o0), st);
+                                (int)(o1 - o0), f.sumthin[c], st);
       });
     else
       prof::timed(prof::GEMM, prof::on ? gemm_flops(f.sum64, f.sumout, o0, o1) : 0.0, st, [&] {
         launch_tile_gemm<double>(reinterpret_cast<const GemmTerm<double>*>(f.ptr<char>(f.o_sumterms)), douts,
-                                 (int)(o1 - o0), st);
+                                 (int)(o1 - o0), f.sumthin[c], st);
       });
     HIPCHK(hipGetLastError());
   }
@@ -1184,6 +1189,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   const int64_t wsz = (int64_t)sizeof(TW);
   const bool use_tband = need_var && n_u > 0 && !stream && std::getenv("LMA_NO_BAND") == nullptr;
   std::vector<BandItem> tb_items;
+  Thin tb_thin{0, 0};
   std::vector<int64_t> tb_row;
   int64_t tb_elems = 0;
   if (use_tband) {
@@ -1194,6 +1200,15 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
       const int64_t c0 = f.bp[std::max<int64_t>(0, q - f.B)], c1 = f.bp[std::min<int64_t>(M - 1, q + f.B) + 1];
       const int64_t w = c1 - c0;
       for (int64_t u = r0; u < r1; ++u) tb_row[u] = tb_elems + (u - r0) * w - c0;
+      tb_elems += (r1 - r0) * w;
+    }
+    // Tiles: the training points of block a against the test points of blocks a-B .. a+B,
+    // which lie next to each other (a tile per test block was mostly padding: 1920 tiles
+    // for 100 points in 64 blocks, 512 this way)
+    std::vector<BandItem> thin;
+    for (int64_t a = 0; a < M; ++a) {
+      const int64_t r0 = ubp[std::max<int64_t>(0, a - f.B)], r1 = ubp[std::min<int64_t>(M - 1, a + f.B) + 1];
+      const int64_t c0 = f.bp[a], c1 = f.bp[a + 1];
       for (int64_t g0 = r0; g0 < r1; g0 += 4 * TB) {
         const int64_t g1 = std::min<int64_t>(r1, g0 + 4 * TB);
         for (int64_t x0 = c0; x0 < c1; x0 += TB)
@@ -1201,15 +1216,20 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
             BandItem it;
             it.p0 = u0;
             it.q0 = x0;
-            it.off = tb_elems + (u0 - r0) * w + (x0 - c0);
-            it.ld = w;
+            it.off = it.ld = 0;
             it.nr = (int)std::min<int64_t>(TB, r1 - u0);
             it.nc = (int)std::min<int64_t>(TB, c1 - x0);
-            tb_items.push_back(it);
+            if (it.nr <= THIN_ROWS) {
+              thin.push_back(it);
+              tb_thin.rows = std::max(tb_thin.rows, it.nr);
+            } else {
+              tb_items.push_back(it);
+            }
           }
       }
-      tb_elems += (r1 - r0) * w;
     }
+    tb_thin.n = (int32_t)thin.size();
+    tb_items.insert(tb_items.end(), thin.begin(), thin.end());
   }
   std::vector<int64_t> pchunk = stream ? f.chunk : std::vector<int64_t>{0, M};
   // window geometry for test rows
@@ -1245,6 +1265,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   // (L_ddot^-1 E)^T (L_ddot^-1 E) over every tile pair, and the whitened
   // products xi of the windows that hold both points of a pair
   std::vector<BandItem> cb_items;
+  Thin cb_thin{0, 0};
   std::vector<GemmTerm<double>> cterms;
   std::vector<GemmOut> couts;
   std::vector<GemmTerm<TW>> xterms;
@@ -1264,6 +1285,9 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
             it.nc = (int)std::min<int64_t>(TB, ubp[r + 1] - v0);
             cb_items.push_back(it);
           }
+    auto few = std::stable_partition(cb_items.begin(), cb_items.end(), [](const BandItem& i) { return i.nr > THIN_ROWS; });
+    cb_thin.n = (int32_t)(cb_items.end() - few);
+    for (; few != cb_items.end(); ++few) cb_thin.rows = std::max(cb_thin.rows, few->nr);
   }
   // runs
   Run<double> runS;
@@ -1368,7 +1392,8 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
       for (int64_t t = 0; t < cdiv(uq, TB); ++t) {
         const int rows = (int)std::min<int64_t>(TB, uq - t * TB);
         for (int b = 0; b <= Ts; ++b) {
-          GemmOut o = gemm_out(at<double>(ar, o_G) + (ubp[q] + t * TB) * ldG + (int64_t)b * TB, ldG, rows, TB,
+          const int cols = b == Ts ? 1 : TB;  // the output row of the window is one
+          GemmOut o = gemm_out(at<double>(ar, o_G) + (ubp[q] + t * TB) * ldG + (int64_t)b * TB, ldG, rows, cols,
                                accumulate ? 1 : 0, (int)terms.size());
           GemmTerm<TW> tm;
           tm.a = Xm + t * TB * ldx;
@@ -1376,7 +1401,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
           tm.anr = rows;
           tm.b = rhs + (int64_t)b * TB * ldx;
           tm.ldb = ldx;
-          tm.bnr = TB;
+          tm.bnr = cols;
           tm.k0 = dl == 0 ? 0 : g.tw * TB;
           tm.k1 = g.T * TB;
           terms.push_back(tm);
@@ -1478,7 +1503,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     }
   };
   build(nullptr);
-  // dG outputs: one launch per delta; record split points
+  // dG outputs: one launch per delta (and chunk); record split points
   std::vector<int> dl_split(f.B + 2, 0);
   {
     int idx = 0;
@@ -1529,6 +1554,16 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     }
   } guard{mem, (size_t)ar.cap, st};
   build(reinterpret_cast<char*>(mem));
+  // launches of tile products, the outputs of few rows last
+  std::vector<Thin> gthin, xthin;
+  if (need_var) {
+    const std::vector<int>& gs = stream ? gsplit : dl_split;
+    for (size_t k = 0; k + 1 < gs.size(); ++k) gthin.push_back(thin_last(outs.data() + gs[k], outs.data() + gs[k + 1]));
+  }
+  if (want_cov)
+    for (int ci = 0; ci < nch; ++ci)
+      xthin.push_back(thin_last(xouts.data() + xsplit[ci], xouts.data() + xsplit[ci + 1]));
+  const Thin cthin = thin_last(couts.data(), couts.data() + couts.size());
   std::vector<int32_t> ublk(n_u);
   for (int64_t q = 0; q < M; ++q)
     for (int64_t u = ubp[q]; u < ubp[q + 1]; ++u) ublk[u] = (int32_t)q;
@@ -1590,6 +1625,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
       a.j = j;
       a.items = run.d_items + run.upd_off[j];
       a.nitems = (int32_t)run.upd_n[j];
+      a.thin = run.upd_thin[j];
       double f64 = 0.0;
       const double fl = prof::on ? run.update_flops(j, vlen > 0 ? f.s : 0, &f64) : 0.0;
       prof::timed(prof::UPDATE, fl, st, [&] { launch_update<TT>(a, std::is_same<TT, float>::value, st); }, f64);
@@ -1635,6 +1671,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     BandArgs<double> cb{};
     cb.items = at<BandItem>(ar, o_cbi);
     cb.nitems = (int32_t)cb_items.size();
+    cb.thin = cb_thin;
     cb.d = (int)d;
     cb.vlen = (int)sp;
     cb.noise = 1;  // one point set: sn2 on the diagonal
@@ -1657,7 +1694,8 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     const int a0 = xsplit[ci], a1 = xsplit[ci + 1];
     if (a1 > a0)
       prof::timed(prof::GEMM, prof::on ? gemm_flops(xterms, xouts, a0, a1) : 0.0, st, [&] {
-        launch_tile_gemm<TW>(at<GemmTerm<TW>>(ar, o_xterms), at<GemmOut>(ar, o_xouts) + a0, a1 - a0, st);
+        launch_tile_gemm<TW>(at<GemmTerm<TW>>(ar, o_xterms), at<GemmOut>(ar, o_xouts) + a0, a1 - a0, xthin[ci],
+                             st);
       });
     HIPCHK(hipGetLastError());
   };
@@ -1666,9 +1704,12 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     prof::flush();
     return;
   }
-  auto g_launch = [&](int a0, int a1) {
+  auto g_launch = [&](const std::vector<int>& split, int k) {
+    const int a0 = split[k], a1 = split[k + 1];
     if (a1 > a0)
-      prof::timed(prof::GEMM, prof::on ? gemm_flops(terms, outs, a0, a1) : 0.0, st, [&] { launch_tile_gemm<TW>(at<GemmTerm<TW>>(ar, o_terms), at<GemmOut>(ar, o_outs) + a0, a1 - a0, st); });
+      prof::timed(prof::GEMM, prof::on ? gemm_flops(terms, outs, a0, a1) : 0.0, st, [&] {
+        launch_tile_gemm<TW>(at<GemmTerm<TW>>(ar, o_terms), at<GemmOut>(ar, o_outs) + a0, a1 - a0, gthin[k], st);
+      });
     HIPCHK(hipGetLastError());
   };
   auto xi_launch = [&](int64_t m0, int64_t m1, bool accumulate) {
@@ -1693,6 +1734,8 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     BandArgs<TW> ba{};
     ba.items = at<BandItem>(ar, o_tbi);
     ba.nitems = (int32_t)tb_items.size();
+    ba.thin = tb_thin;
+    ba.brow = at<int64_t>(ar, o_tbr);
     ba.d = (int)d;
     ba.vlen = (int)sp;
     ba.noise = 0;  // test and training points are different sets: no noise term
@@ -1712,7 +1755,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   }
   if (!stream) {
     exec(runsW[0], invs, (int)sp, false, use_tband);
-    for (int dl = 0; dl <= f.B; ++dl) g_launch(dl_split[dl], dl_split[dl + 1]);
+    for (int dl = 0; dl <= f.B; ++dl) g_launch(dl_split, dl);
     xi_launch(0, M, false);
     x_launch(0);
   } else {
@@ -1720,8 +1763,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     for (int ci = 0; ci < nch; ++ci) {
       exec(runsW[ci], invs, (int)sp, true);
       for (int dl = 0; dl <= f.B; ++dl) {
-        const int k = ci * ((int)f.B + 1) + dl;
-        g_launch(gsplit[k], gsplit[k + 1]);
+        g_launch(gsplit, ci * ((int)f.B + 1) + dl);
       }
       xi_launch(pchunk[ci], pchunk[ci + 1], ci > 0);
       x_launch(ci);
@@ -1752,7 +1794,8 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   HIPCHK(hipGetLastError());
   if (want_cov && !couts.empty()) {
     prof::timed(prof::GEMM, prof::on ? gemm_flops(cterms, couts, 0, (int64_t)couts.size()) : 0.0, st, [&] {
-      launch_tile_gemm<double>(at<GemmTerm<double>>(ar, o_cterms), at<GemmOut>(ar, o_couts), (int)couts.size(), st);
+      launch_tile_gemm<double>(at<GemmTerm<double>>(ar, o_cterms), at<GemmOut>(ar, o_couts), (int)couts.size(),
+                                   cthin, st);
     });
     HIPCHK(hipGetLastError());
   }

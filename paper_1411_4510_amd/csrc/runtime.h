@@ -166,6 +166,14 @@ double gemm_flops(const std::vector<GemmTerm<T>>& terms, const std::vector<GemmO
   return fl;
 }
 
+// Moves the outputs of at most THIN_ROWS rows among [b, e) to the end, keeping orders.
+inline Thin thin_last(GemmOut* b, GemmOut* e) {
+  GemmOut* t = std::stable_partition(b, e, [](const GemmOut& o) { return o.rows > THIN_ROWS; });
+  Thin n{(int32_t)(e - t), 0};
+  for (; t < e; ++t) n.rows = std::max(n.rows, t->rows);
+  return n;
+}
+
 // Lock-step column schedule of one engine run, uploaded once.
 template <typename T>
 struct Run {
@@ -178,6 +186,7 @@ struct Run {
   std::vector<WorkItem> items;
   std::vector<int32_t> plist;
   std::vector<int64_t> upd_off, upd_n, trs_off, trs_n, pl_off, pl_n;
+  std::vector<Thin> upd_thin;  // tiles of few rows, last in a step's update items
   // device copies
   RowTile<T>* d_rt = nullptr;
   ProbDesc* d_pd = nullptr;
@@ -208,15 +217,28 @@ struct Run {
     trs_n.assign(maxT, 0);
     pl_off.assign(maxT, 0);
     pl_n.assign(maxT, 0);
+    upd_thin.assign(maxT, Thin{0, 0});
+    std::vector<WorkItem> thin;
     for (int j = 0; j < maxT; ++j) {
+      thin.clear();
       upd_off[j] = (int64_t)items.size();
       for (int p = 0; p < np; ++p) {
         if (pd[p].T <= j) continue;
         if (!solve_only[p])
           for (int i = j; i < pd[p].T; ++i) items.push_back({p, i});
-        for (int r = 0; r < pd[p].R; ++r)
-          if (rt[pd[p].first + pd[p].T + r].kbeg <= j) items.push_back({p, pd[p].T + r});
+        for (int r = 0; r < pd[p].R; ++r) {
+          const RowTile<T>& t = rt[pd[p].first + pd[p].T + r];
+          if (t.kbeg > j) continue;
+          if (t.nvalid <= THIN_ROWS && t.src != SRC_IDENT) {
+            thin.push_back({p, pd[p].T + r});
+            upd_thin[j].rows = std::max(upd_thin[j].rows, t.nvalid);
+          } else {
+            items.push_back({p, pd[p].T + r});
+          }
+        }
       }
+      upd_thin[j].n = (int32_t)thin.size();
+      items.insert(items.end(), thin.begin(), thin.end());
       upd_n[j] = (int64_t)items.size() - upd_off[j];
       trs_off[j] = (int64_t)items.size();
       for (int p = 0; p < np; ++p) {
@@ -326,6 +348,7 @@ struct lma_state {
   std::vector<int64_t> chunk;
   int64_t win_area = 0, inv_area = 0;  // elements of the window areas
   std::vector<int64_t> sumsplit;    // summary outputs of chunk c: [sumsplit[c], sumsplit[c+1])
+  std::vector<lma::Thin> sumthin;   // of these, the ones of few rows (last)
   std::vector<int64_t> kmvsplit;    // KV_KMV items of window m start at kmvsplit[m] ([M+1])
   bool streaming() const { return chunk.size() > 2; }
   int groups = 1, ntile = 1;

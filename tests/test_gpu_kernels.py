@@ -66,6 +66,32 @@ def test_pieces_of_tiles(lib, n, M, B, s, n_u, precision, bar):
     check_fit(lib, p, bar=bar, precision=precision)
 
 
+# test tiles of 1 to 65 rows (16, 32 and 64 rows have forms of their own, 65 none), alone
+# and beside whole tiles in one launch (blocks without and with many test points), with
+# the output row of windows of 1 to 20 tiles; full covariance over such tiles; a memory
+# budget, which forms the test rows without a band and the windows chunk by chunk
+@pytest.mark.parametrize("precision,bar", [("fp64", BAR), ("mixed", 1e-4)])
+@pytest.mark.parametrize("n,M,B,counts", [(700, 3, 1, (1, 0, 16)), (2700, 3, 2, (17, 32, 33)), (2600, 4, 3, (64, 1, 0, 65)),
+                                          (2560, 1, 0, (5,)), (9000, 30, 2, (3,) * 29 + (140,))])
+def test_tiles_of_few_rows(lib, n, M, B, counts, precision, bar):
+    rng = np.random.default_rng(n)
+    p = synth.make_random(seed=n + 2, n=n, d=3, M=M, s=61, n_u=sum(counts), B=B, uneven=(n // M - 9, n // M + 9), sn2=0.05)
+    p.u_block_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    p.U = rng.uniform(size=(sum(counts), 3))
+    ref = olma.fit_predict(p)
+    cov_ref = olma.predict_cov(p)[1]
+    full = 0
+    for share in (1.0, 0.6) if M > 3 else (1.0,):  # three windows do not fit a smaller budget one by one
+        st = lib.fit_problem(p, precision=precision, mem_budget=int(share * full) if share < 1 else 0)
+        full = st.nbytes()
+        mean, var = st.predict(p.U, p.u_block_ptr)
+        mean2, cov = st.predict_cov(p.U, p.u_block_ptr)
+        st.free()
+        assert rel(mean.cpu().numpy(), ref["mean"]) < bar and rel(mean2.cpu().numpy(), ref["mean"]) < bar
+        assert rel(var.cpu().numpy(), ref["var"]) < bar
+        assert rel(cov.cpu().numpy(), cov_ref) < bar
+
+
 # mean and residual sums in parts of the column list: row tiles of 1 to 128 points (waves
 # share columns up to 64 rows), lists shorter and longer than the parts, 1024 and more
 # row tiles (no parts), windows at both ends of the overlap
