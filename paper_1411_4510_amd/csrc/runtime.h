@@ -112,7 +112,7 @@ class Stage {
 };
 
 // Device blocks released by lma_free / lma_predict / the end of a fit are kept
-// (at most four) and reused by the next call that fits in them (see lma.hip).
+// (at most eight, four of them up to 1 GiB) and reused by the next call that fits in them (see lma.hip).
 namespace devcache {
 void* get(size_t bytes);
 void put(void* p, size_t bytes);
@@ -373,6 +373,12 @@ struct lma_state {
   ~lma_state() {
     if (ar.base) lmart::devcache::put(ar.base, (size_t)ar.cap);
   }
+  // A fit whose gradient is wanted: the forms of the factorisation and the summary
+  // that keep one order of sums (k_diag32, no products split along k).  Where points lie
+  // dense the gradient is a small difference of large traces and carries a reordered
+  // factor's rounding 1e8 times larger (d = 1, n = 4507, |S| = 703: two orders agree to
+  // 3e-7, their common order to 2e-12); the mean, variance and likelihood do not.
+  bool one_order = false;
   bool mixed() const { return precision == LMA_MIXED; }
   template <typename T>
   T* ptr(int64_t off) const {
