@@ -422,7 +422,7 @@ constexpr size_t diag32_lds_bytes = sizeof(double) * (size_t)(TB * DLD + (DNB - 
 template <>
 void launch_diag<double>(const StepArgs<double>& a, const int32_t* plist, int np, hipStream_t st) {
   if (np <= 0) return;
-  if (a.mixed_fit)
+  if (a.diag32)
     hipLaunchKernelGGL(k_diag32<double>, dim3(np), dim3(NT), diag32_lds_bytes, st, a, plist);
   else
     hipLaunchKernelGGL(k_diag16, dim3(np), dim3(NT), 0, st, a, plist);

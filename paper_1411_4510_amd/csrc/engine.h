@@ -104,10 +104,12 @@ struct StepArgs {
   // (u, x) at band[brow[u] + x]; null when no row of the run uses one
   const T* band;
   const int64_t* brow;
-  int32_t mixed_fit;  // 1: Sigma_SS of a mixed-precision fit (which diagonal kernel runs, see diag.hip)
+  int32_t diag32;     // 1: float64 diagonal tiles by k_diag32 instead of k_diag16 (see diag.hip)
   // workspace for tiles whose products are split along k (launch_update): PART_TILES tiles
   // of TB x TB, or null (no tile is split).  In use only within one launch_update.
   double* part;
+  int32_t any_order;  // 1: the order of the sums may depend on the size of the launch; 0: it may
+                      // not (the gradient, which is the same bit for bit however it is chunked)
   int32_t nsplit;     // set by launch_update: parts of every tile of a launch
 };
 constexpr int PART_TILES = 512;
@@ -199,7 +201,9 @@ inline GemmOut gemm_out(double* out, int64_t ld, int rows, int cols, int accumul
   o.t0 = o.tneg = o.t1 = t0;
   return o;
 }
+// any_order as in StepArgs; without it thin.n must be 0.
 template <typename T>
-void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, Thin thin, hipStream_t st);
+void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, Thin thin, bool any_order,
+                      hipStream_t st);
 
 }  // namespace lma

@@ -92,15 +92,35 @@ __global__ __launch_bounds__(NT, (std::is_same<T, double>::value && SUB == 4) ? 
   // factor columns kb .. j-1 (a row is zero left of its kbeg)
   const int kb = ri.kbeg > rj.kbeg ? ri.kbeg : rj.kbeg;
   if constexpr (FIX) {
+    // several parts in flight (one after the other they took 1 us each)
+    constexpr int FLY = SUB == 1 ? 8 : 2;
     const double* part = a.part + (int64_t)(logical / (NQ * NQ)) * a.nsplit * TB * TB;
-    for (int p = 0; p < a.nsplit; ++p, part += TB * TB)
+    auto add = [&](auto np) {
+      constexpr int NP = decltype(np)::value;
+      double q[NP][SUB][SUB][4];
 #pragma unroll
-      for (int rs = 0; rs < SUB; ++rs)
+      for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int cs = 0; cs < SUB; ++cs)
+        for (int rs = 0; rs < SUB; ++rs)
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            accv[rs][cs][v] += (TK)part[(r0 + rs * 16 + Mfma<TK>::row(lane, v)) * TB + c0 + cs * 16 + (lane & 15)];
+          for (int cs = 0; cs < SUB; ++cs)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              q[p][rs][cs][v] =
+                  part[p * TB * TB + (r0 + rs * 16 + Mfma<TK>::row(lane, v)) * TB + c0 + cs * 16 + (lane & 15)];
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int rs = 0; rs < SUB; ++rs)
+#pragma unroll
+          for (int cs = 0; cs < SUB; ++cs)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) accv[rs][cs][v] += (TK)q[p][rs][cs][v];
+      part += NP * TB * TB;
+    };
+    int p = 0;
+    for (; p + FLY <= a.nsplit; p += FLY) add(std::integral_constant<int, FLY>());
+    for (; p < a.nsplit; ++p) add(std::integral_constant<int, 1>());
   } else if (real && a.j > kb) {
     const T* pa = ri.panel + (int64_t)(kb - ri.kbeg) * TB;
     const T* pb = rj.panel + (int64_t)(kb - rj.kbeg) * TB;
@@ -242,9 +262,9 @@ __global__ __launch_bounds__(NT, (std::is_same<T, double>::value) ? 2 : 1) void 
 // thin tiles: at most 16 RS valid rows
 // ---------------------------------------------------------------------------
 // Bound: reading the other operand once.  A whole tile costs its 128 rows of products
-// however few are real; here a workgroup takes 16 of the 128 columns and its 8 waves (4
-// from 64 rows on) share the sums over k, so a launch of 60 tiles has 4000 waves with six
-// chunks in flight each.  The waves' sums are added through LDS in order.
+// however few are real; here a workgroup takes 16 of the 128 columns and its 8 waves
+// share the sums over k, so a launch of 60 tiles has 4000 waves with six chunks in flight
+// each.  The waves' sums are added through LDS in order.
 // Measured: test rows of 100 points (62 tiles of 1 to 14 rows, k up to 3000) 108 -> 45 us
 // a launch, their products with the support rows 664 -> 250 us, their residual band (with
 // tiles over several blocks) 506 -> 83; a prediction 3.41 -> 1.60 ms, covariance of 512
@@ -252,7 +272,7 @@ __global__ __launch_bounds__(NT, (std::is_same<T, double>::value) ? 2 : 1) void 
 // 53.2 -> 51.0, n=262144 all updates 690 -> 676.
 template <int RS>
 struct ThinShape {
-  static constexpr int NW = RS < 4 ? 8 : 4, THREADS = 64 * NW, ELEMS = RS * 256;
+  static constexpr int NW = 8, THREADS = 64 * NW, ELEMS = RS * 256;
 };
 
 // this wave's share of [k0, k1) in units of U chunks of 16; a last chunk of its own joins
@@ -282,20 +302,27 @@ __device__ inline double thin_sum(const double* red, int e) {
   return s;
 }
 
+// groups: row groups of 16 RS per tile; 1 for thin tiles (their other rows are zero).
+// Launches of a few whole tiles take the same form: a 32 x 32 piece of such a tile was one
+// serial chain over k on a quarter of its MFMA slots.  n = 16 tiles, k = 128 .. 1280: 9 ..
+// 37 us as pieces, 5 .. 26 here (the rate is that of the operands from L2, 33 TFLOP/s).
 template <typename T, bool MIXED, int RS>
-__global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_update_thin(StepArgs<T> a) {
+__global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_update_slim(StepArgs<T> a, int groups) {
   typedef typename std::conditional<MIXED, double, T>::type TK;
   static_assert(std::is_same<TK, double>::value, "sums in float64");
-  constexpr int NW = ThinShape<RS>::NW;
+  constexpr int NW = ThinShape<RS>::NW, RG = 16 * RS;
   __shared__ double red[NW * ThinShape<RS>::ELEMS];
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
-  if (logical >= a.nitems * 8) return;
-  const WorkItem it = a.items[logical / 8];
+  if (logical >= a.nitems * 8 * groups) return;
+  const WorkItem it = a.items[logical / (8 * groups)];
   const ProbDesc pd = a.pd[it.p];
   const RowTile<T> ri = a.rt[pd.first + it.tile];
   const RowTile<T> rj = a.rt[pd.first + a.j];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c0 = logical % 8 * 16;
-  const bool real = c0 < rj.nvalid, band = ri.src == SRC_BAND || ri.src == SRC_TBAND;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r0 = logical / 8 % groups * RG, c0 = logical % 8 * 16;
+  const bool diag = ri.is_j && it.tile == a.j;
+  if (r0 >= ri.nstore || (diag && c0 >= r0 + RG)) return;
+  const bool real = r0 < ri.nvalid && c0 < rj.nvalid, band = ri.src == SRC_BAND || ri.src == SRC_TBAND;
   dv4 acc[RS][1];
   zero_acc<double>(acc);
   const double* vi = MIXED ? ri.vt64 : (const double*)ri.vt;
@@ -303,7 +330,7 @@ __global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_update_thin(StepArgs
   int k0, k1;
   if (real && !band && vi != nullptr && vj != nullptr && a.vlen > 0) {
     thin_share<1, NW>(0, a.vlen, w, &k0, &k1);
-    wave_gemm<double, double>(acc, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, k0, k1, 0, c0, lane);
+    wave_gemm<double, double>(acc, vi, a.vld, ri.nvalid, vj, a.vld, rj.nvalid, k0, k1, r0, c0, lane);
   }
   const int kb = ri.kbeg > rj.kbeg ? ri.kbeg : rj.kbeg;
   if (real && a.j > kb) {
@@ -313,22 +340,25 @@ __global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_update_thin(StepArgs
     if constexpr (MIXED) {
       fv4 accl[RS][1];
       zero_acc<float>(accl);
-      wave_gemm_fold(accl, pa, ri.ld, ri.nvalid, pb, rj.ld, rj.nstore, k0, k1, 0, c0, lane, acc);
+      wave_gemm_fold(accl, pa, ri.ld, ri.nvalid, pb, rj.ld, rj.nstore, k0, k1, r0, c0, lane, acc);
     } else {
-      wave_gemm<T, T>(acc, pa, ri.ld, ri.nvalid, pb, rj.ld, rj.nstore, k0, k1, 0, c0, lane);
+      wave_gemm<T, T>(acc, pa, ri.ld, ri.nvalid, pb, rj.ld, rj.nstore, k0, k1, r0, c0, lane);
     }
   }
   thin_put<RS>(acc, red, w, lane);
   T* out = ri.panel + (int64_t)(a.j - ri.kbeg) * TB + c0;
-  const int stored = ri.nstore < 16 * RS ? ri.nstore : 16 * RS;
+  const int stored = ri.nstore - r0 < RG ? ri.nstore - r0 : RG;
+#pragma unroll 1
   for (int e = tid; e < stored * 16; e += ThinShape<RS>::THREADS) {
-    const int row = e >> 4, col = c0 + (e & 15);
-    double val = 0.0;  // padding
-    if (row < ri.nvalid && col < rj.nvalid) {
-      double kv;
+    const int row = r0 + (e >> 4), col = c0 + (e & 15);
+    double val = 0.0;
+    if (ri.src == SRC_IDENT) {
+      val = ri.kbeg == a.j && row == col ? 1.0 : 0.0;
+      if (row < ri.nvalid && col < rj.nvalid) val -= thin_sum<RS>(red, e);
+    } else if (row < ri.nvalid && col < rj.nvalid) {
       if (band) {
         const int64_t p = ri.pt0 + row, q = rj.pt0 + col;
-        kv = (double)a.band[ri.src == SRC_TBAND || q <= p ? a.brow[p] + q : a.brow[q] + p];
+        val = (double)a.band[ri.src == SRC_TBAND || q <= p ? a.brow[p] + q : a.brow[q] + p];
       } else if (ri.src == SRC_KERNEL) {
         const double* x = (MIXED ? ri.xs64 : (const double*)ri.xs) + (int64_t)row * a.d;
         const double* y = (MIXED ? rj.xs64 : (const double*)rj.xs) + (int64_t)col * a.d;
@@ -337,30 +367,36 @@ __global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_update_thin(StepArgs
           const double df = x[t] - y[t];
           sq += df * df;
         }
-        kv = a.sf2 * k_exp(-0.5 * sq);
+        val = a.sf2 * k_exp(-0.5 * sq);
+        if (diag && row == col) val += a.sn2;
       } else if (ri.src == SRC_EXPLICIT) {
-        kv = (double)ri.expl[(int64_t)row * ri.eld + (int64_t)a.j * TB + col];
+        val = (double)ri.expl[(int64_t)row * ri.eld + (int64_t)a.j * TB + col];
       } else {
-        kv = row == 0 ? (double)rj.cv[col] : 0.0;
+        val = row == 0 ? (double)rj.cv[col] : 0.0;
       }
-      val = kv - thin_sum<RS>(red, e);
+      val -= thin_sum<RS>(red, e);
+    } else if (diag && row == col) {
+      val = 1.0;  // padding: identity on the diagonal tile, zero elsewhere
     }
     out[(int64_t)row * ri.ld + (e & 15)] = (T)val;
   }
-  for (int e = tid + 16 * RS * 16; e < ri.nstore * 16; e += ThinShape<RS>::THREADS)
-    out[(int64_t)(e >> 4) * ri.ld + (e & 15)] = T(0);
+  if (groups == 1)
+    for (int e = tid + 16 * RG; e < ri.nstore * 16; e += ThinShape<RS>::THREADS)
+      out[(int64_t)(e >> 4) * ri.ld + (e & 15)] = T(0);
 }
 
 template <typename T, int RS>
-__global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_tile_gemm_thin(const GemmTerm<T>* __restrict__ terms,
-                                                                           const GemmOut* __restrict__ outs, int nout) {
+__global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_tile_gemm_slim(const GemmTerm<T>* __restrict__ terms,
+                                                                           const GemmOut* __restrict__ outs, int nout,
+                                                                           int groups) {
   constexpr int NW = ThinShape<RS>::NW;
   __shared__ double red[NW * ThinShape<RS>::ELEMS];
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
-  if (logical >= nout * 8) return;
-  const GemmOut o = outs[logical / 8];
+  if (logical >= nout * 8 * groups) return;
+  const GemmOut o = outs[logical / (8 * groups)];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c0 = logical % 8 * 16;
-  if (c0 >= o.cols) return;
+  const int r0 = logical / 8 % groups * 16 * RS;
+  if (c0 >= o.cols || r0 >= o.rows) return;
   dv4 acc[RS][1];
   zero_acc<double>(acc);
   for (int t = o.t0; t < o.t1; ++t) {
@@ -371,15 +407,16 @@ __global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_tile_gemm_thin(const
     const GemmTerm<T> tm = terms[t];
     int k0, k1;
     thin_share<1, NW>(tm.k0, tm.k1, w, &k0, &k1);
-    wave_gemm<T, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, k0, k1, 0, c0, lane);
+    wave_gemm<T, double>(acc, tm.a, tm.lda, tm.anr, tm.b, tm.ldb, tm.bnr, k0, k1, r0, c0, lane);
   }
   if (o.tneg == o.t1 && o.t1 > o.t0) {  // only subtracted terms
 #pragma unroll
     for (int r = 0; r < RS; ++r) acc[r][0] = -acc[r][0];
   }
   thin_put<RS>(acc, red, w, lane);
-  for (int e = tid; e < o.rows * 16; e += ThinShape<RS>::THREADS) {
-    const int row = e >> 4, col = c0 + (e & 15);
+  const int n = (o.rows - r0 < 16 * RS ? o.rows - r0 : 16 * RS) * 16;
+  for (int e = tid; e < n; e += ThinShape<RS>::THREADS) {
+    const int row = r0 + (e >> 4), col = c0 + (e & 15);
     if (col >= o.cols) continue;
     double* q = o.out + (int64_t)row * o.ld + col;
     double r = o.alpha * thin_sum<RS>(red, e);
@@ -428,9 +465,11 @@ __global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_band_thin(BandArgs<T
 // c0 + n.  WR waves stand above each other: 2, a workgroup takes the 128 x 128 tile
 // (4 x 4 sub-tiles per wave); 1, it takes 32 rows of it (2 x 2 per wave).  Rows are
 // never split between workgroups, so the tile is replaced in place.
+// WR 0: eight waves side by side, 16 rows, one sub-tile each.
 template <typename T, int WR>
-__global__ __launch_bounds__(NT) void k_trsm(StepArgs<T> a) {
-  constexpr int SUB = 2 * WR, WS = 16 * SUB, WC = 4 / WR, RS = WR * WS, NP = TB / RS;
+__global__ __launch_bounds__(WR == 0 ? 2 * NT : NT) void k_trsm(StepArgs<T> a) {
+  constexpr int SUB = WR == 0 ? 1 : 2 * WR, WS = 16 * SUB, WC = WR == 0 ? 8 : 4 / WR;
+  constexpr int RS = WR == 0 ? WS : WR * WS, NP = TB / RS;
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
   if (logical >= a.nitems * NP) return;
   const WorkItem it = a.items[logical / NP];
@@ -651,6 +690,16 @@ static double update_us(int64_t n, int64_t k, bool can_part) {
   return std::min(pieces, whole);
 }
 
+// A few whole tiles in the form of thin ones, in rs row groups of 16 per workgroup: as many
+// workgroups as fit the CUs once.  Measured us per 128 k (float64; mixed precision 0.56 of
+// it): n <= 4 0.72, 8 1.05, 16 2.05, 32 4.2; beyond 32 the pieces of split_of are faster
+// (n = 48, k = 640 31 and 28 us).
+static inline int slim_rs(int64_t n) { return n <= 4 ? 1 : n <= 8 ? 2 : 4; }
+template <bool MIXED>
+static double slim_us(int64_t n, int64_t k) {
+  return (MIXED ? 0.56 : 1.0) * (n <= 4 ? 0.72 : n <= 8 ? 1.05 : n <= 16 ? 2.05 : 4.2) * (double)k / 128.0;
+}
+
 // row groups of 16 (1, 2 or 4) that hold `rows` rows
 static inline int thin_rs(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 : 4; }
 
@@ -661,6 +710,16 @@ static double thin_us(int64_t n, int64_t k, int rs) {
   const double bytes = (double)n * TB * (double)k * sizeof(T) / 4.0e6;
   const double prod = (double)(n * 8) * (double)(k / 16) * 256.0 * rs / (1024.0 * 2400.0);
   return 6.0 + std::max(bytes, prod);
+}
+
+template <typename T, bool MIXED>
+static void slim_launch(const StepArgs<T>& a, int rs, int groups, hipStream_t st) {
+  const dim3 grid(pad8(8 * groups * a.nitems));
+  switch (rs) {
+    case 1: hipLaunchKernelGGL((k_update_slim<T, MIXED, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, a, groups); break;
+    case 2: hipLaunchKernelGGL((k_update_slim<T, MIXED, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, a, groups); break;
+    default: hipLaunchKernelGGL((k_update_slim<T, MIXED, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, a, groups);
+  }
 }
 
 template <typename T, bool MIXED>
@@ -682,12 +741,7 @@ static void update_launches(const StepArgs<T>& a, hipStream_t st) {
         if (full > 0) update_launches<T, MIXED>(b, st);
         b.items += full;
         b.nitems = a.thin.n;
-        const dim3 grid(pad8(8 * a.thin.n));
-        switch (rs) {
-          case 1: hipLaunchKernelGGL((k_update_thin<T, MIXED, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, b); break;
-          case 2: hipLaunchKernelGGL((k_update_thin<T, MIXED, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, b); break;
-          default: hipLaunchKernelGGL((k_update_thin<T, MIXED, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, b);
-        }
+        slim_launch<T, MIXED>(b, rs, 1, st);
       } else {
         update_launches<T, MIXED>(b, st);
       }
@@ -696,6 +750,11 @@ static void update_launches(const StepArgs<T>& a, hipStream_t st) {
   }
   const int split = split_of(n, k);
   if constexpr (MIXED || std::is_same<T, double>::value) {
+    if (a.any_order && n <= 32 && slim_us<MIXED>(n, k) <= update_us<MIXED>(n, k, a.part != nullptr && !vpart && k > 256)) {
+      const int rs = slim_rs(n);
+      slim_launch<T, MIXED>(a, rs, 8 / rs, st);
+      return;
+    }
     if (a.part != nullptr && !vpart && k > 256) {
       const UpdatePlan p = plan_update<MIXED>(n, k, PART_TILES);
       // what the pieces of split_of would take
@@ -710,7 +769,10 @@ static void update_launches(const StepArgs<T>& a, hipStream_t st) {
         hipLaunchKernelGGL((k_update_part<T, MIXED>), dim3(pad8(b.nitems * p.parts)), dim3(NT),
                            MIXED ? 0 : WG_GEMM_LDS, st, b);
         const size_t lds = 2 * (size_t)a.d * (TB / 2) * (MIXED ? sizeof(double) : sizeof(T));
-        hipLaunchKernelGGL((k_update<T, MIXED, 2, true>), dim3(pad8(b.nitems * 4)), dim3(NT), lds, st, b);
+        if (b.nitems <= 32)
+          hipLaunchKernelGGL((k_update<T, MIXED, 1, true>), dim3(pad8(b.nitems * 16)), dim3(NT), lds / 2, st, b);
+        else
+          hipLaunchKernelGGL((k_update<T, MIXED, 2, true>), dim3(pad8(b.nitems * 4)), dim3(NT), lds, st, b);
         return;
       }
     }
@@ -736,11 +798,14 @@ void launch_update(const StepArgs<T>& a, bool mixed, hipStream_t st) {
 template <typename T>
 void launch_trsm(const StepArgs<T>& a, hipStream_t st) {
   if (a.nitems <= 0) return;
+  // 16 rows per workgroup up to 32 tiles: 9.4 -> 7.3 us (n = 62 of few rows 9.0, 9.5);
   // 32 rows per workgroup: measured 22 -> 10 us for n <= 64 tiles, 25 -> 17 at n = 128;
   // from there on it is slower in float64 (26 -> 32 us at n = 224), and faster in
   // float32 while its lower occupancy shows (n = 544 39 -> 37, n = 1680 97 -> 92, n = 2000 109 -> 123)
   if (a.nitems > (std::is_same<T, float>::value ? 1200 : NCU / 2))
     hipLaunchKernelGGL((k_trsm<T, 2>), dim3(pad8(a.nitems)), dim3(NT), 0, st, a);
+  else if (a.nitems <= NCU / 8)
+    hipLaunchKernelGGL((k_trsm<T, 0>), dim3(pad8(8 * a.nitems)), dim3(2 * NT), 0, st, a);
   else
     hipLaunchKernelGGL((k_trsm<T, 1>), dim3(pad8(4 * a.nitems)), dim3(NT), 0, st, a);
 }
@@ -764,24 +829,30 @@ void launch_band(const BandArgs<T>& a, hipStream_t st) {
 }
 
 template <typename T>
-void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, Thin thin, hipStream_t st) {
-  // thin outputs apart, unless there are so few others that their pieces (of which those
-  // without a row end at once) fill no more than a turn
+static void tile_gemm_slim(const GemmTerm<T>* terms, const GemmOut* outs, int n, int rs, int groups, hipStream_t st) {
+  const dim3 grid(pad8(8 * groups * n));
+  switch (rs) {
+    case 1: hipLaunchKernelGGL((k_tile_gemm_slim<T, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, terms, outs, n, groups); break;
+    case 2: hipLaunchKernelGGL((k_tile_gemm_slim<T, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, terms, outs, n, groups); break;
+    default: hipLaunchKernelGGL((k_tile_gemm_slim<T, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, terms, outs, n, groups);
+  }
+}
+
+template <typename T>
+void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, Thin thin, bool any_order,
+                      hipStream_t st) {
+  // thin outputs apart, unless the whole launch is small
   if (thin.n > 0 && (thin.n == nout || nout > 64)) {
     nout -= thin.n;
-    const GemmOut* to = outs + nout;
-    const dim3 grid(pad8(8 * thin.n));
-    switch (thin_rs(thin.rows)) {
-      case 1: hipLaunchKernelGGL((k_tile_gemm_thin<T, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, terms, to, thin.n); break;
-      case 2: hipLaunchKernelGGL((k_tile_gemm_thin<T, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, terms, to, thin.n); break;
-      default: hipLaunchKernelGGL((k_tile_gemm_thin<T, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, terms, to, thin.n);
-    }
+    tile_gemm_slim(terms, outs + nout, thin.n, thin_rs(thin.rows), 1, st);
   }
   if (nout <= 0) return;
-  // measured, whole / 4 / 16 pieces: float64 n = 48 204 / 75 / 110 us, n = 112 178 / 128 / 204,
-  // n = 176 80 / 94 / 129; float32 operands leave the registers for three workgroups of
-  // pieces on a CU: n = 240 863 / 755 / 893, n = 14240 8071 / 6637 / 11110
-  if (nout <= 16)
+  // measured, whole tiles / 4 pieces: float64 n = 48 204 / 75 us, n = 112 178 / 128, n = 176
+  // 80 / 94; float32 operands leave the registers for three workgroups of pieces on a CU:
+  // n = 240 863 / 755, n = 14240 8071 / 6637.  Up to 16 the waves share k.
+  if (nout <= 16 && any_order)
+    tile_gemm_slim(terms, outs, nout, slim_rs(nout), 8 / slim_rs(nout), st);
+  else if (nout <= 16)  // 16 pieces: n = 14 31 us, 4 pieces 47
     hipLaunchKernelGGL((k_tile_gemm<T, 1>), dim3(pad8(16 * nout)), dim3(NT), 0, st, terms, outs, nout);
   else if (nout <= NCU / 2 || std::is_same<T, float>::value)
     hipLaunchKernelGGL((k_tile_gemm<T, 2>), dim3(pad8(4 * nout)), dim3(NT), 0, st, terms, outs, nout);
@@ -820,7 +891,7 @@ template void launch_trsm<double>(const StepArgs<double>&, hipStream_t);
 template void launch_trsm<float>(const StepArgs<float>&, hipStream_t);
 template void launch_band<double>(const BandArgs<double>&, hipStream_t);
 template void launch_band<float>(const BandArgs<float>&, hipStream_t);
-template void launch_tile_gemm<double>(const GemmTerm<double>*, const GemmOut*, int, Thin, hipStream_t);
-template void launch_tile_gemm<float>(const GemmTerm<float>*, const GemmOut*, int, Thin, hipStream_t);
+template void launch_tile_gemm<double>(const GemmTerm<double>*, const GemmOut*, int, Thin, bool, hipStream_t);
+template void launch_tile_gemm<float>(const GemmTerm<float>*, const GemmOut*, int, Thin, bool, hipStream_t);
 
 }  // namespace lma

@@ -362,12 +362,13 @@ void build_summary_chunk(lma_state& f, std::vector<GemmTerm<TW>>& terms, TW* win
     }
 }
 
-lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool keep) {
+lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool keep, bool for_grad = false) {
   check_problem(p);
   ensure_init();
   std::unique_ptr<lma_state> F(new lma_state());
   lma_state& f = *F;
   f.precision = p->precision;
+  f.one_order = for_grad;
   f.n = p->n;
   f.d = p->d;
   f.s = p->s;
@@ -502,7 +503,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     bpl.o_items = align_up(wsz * off, 256);
     bpl.o_brow = bpl.o_items + align_up((int64_t)sizeof(BandItem) * (int64_t)bpl.items.size(), 256);
     bpl.bytes = bpl.o_brow + 8 * n;
-    if (p->mem_budget_bytes == 0 && maxT >= PART_MIN_T) {  // workspace of the split products behind the band
+    if (p->mem_budget_bytes == 0 && maxT >= PART_MIN_T && !f.one_order) {  // workspace of the split products behind the band
       bpl.o_part = align_up(bpl.bytes, 256);
       bpl.bytes = bpl.o_part + PART_BYTES;
     }
@@ -775,13 +776,14 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     a.logdiag = logdiag + (int64_t)slot * maxTld;
     a.status = status + slot;
     a.maxT = maxTld;
-    a.mixed_fit = mixed && slot == (int)M ? 1 : 0;
-    a.part = use_band && bpl.o_part >= 0 ? reinterpret_cast<double*>(static_cast<char*>(bpl.mem) + bpl.o_part) : nullptr;
+    a.diag32 = f.one_order || (mixed && slot == (int)M) ? 1 : 0;
+    a.any_order = f.one_order ? 0 : 1;
+    a.part = a.any_order && use_band && bpl.o_part >= 0 ? reinterpret_cast<double*>(static_cast<char*>(bpl.mem) + bpl.o_part) : nullptr;
     for (int j = 0; j < realT; ++j) {
       a.j = j;
       a.items = run.d_items + run.upd_off[j];
       a.nitems = (int32_t)run.upd_n[j];
-      a.thin = run.upd_thin[j];
+      if (a.any_order) a.thin = run.upd_thin[j];
       double f64 = 0.0;
       const double fl = prof::on ? run.update_flops(j, vlen > 0 ? s : 0, &f64) : 0.0;
       prof::timed(prof::UPDATE, fl, st, [&] { launch_update<TT>(a, std::is_same<TT, float>::value, st); }, f64);
@@ -835,15 +837,16 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     factor_chunk(c);
     const int64_t o0 = f.sumsplit[c], o1 = f.sumsplit[c + 1];
     const GemmOut* douts = reinterpret_cast<const GemmOut*>(f.ptr<char>(f.o_sumout)) + o0;
+    const Thin thin = f.one_order ? Thin{0, 0} : f.sumthin[c];
     if (mixed)
       prof::timed(prof::GEMM, prof::on ? gemm_flops(f.sum32, f.sumout, o0, o1) : 0.0, st, [&] {
         launch_tile_gemm<float>(reinterpret_cast<const GemmTerm<float>*>(f.ptr<char>(f.o_sumterms)), douts,
-                                (int)(o1 - o0), f.sumthin[c], st);
+                                (int)(o1 - o0), thin, !f.one_order, st);
       });
     else
       prof::timed(prof::GEMM, prof::on ? gemm_flops(f.sum64, f.sumout, o0, o1) : 0.0, st, [&] {
         launch_tile_gemm<double>(reinterpret_cast<const GemmTerm<double>*>(f.ptr<char>(f.o_sumterms)), douts,
-                                 (int)(o1 - o0), f.sumthin[c], st);
+                                 (int)(o1 - o0), thin, !f.one_order, st);
       });
     HIPCHK(hipGetLastError());
   }
@@ -1637,6 +1640,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
       a.items = run.d_items + run.upd_off[j];
       a.nitems = (int32_t)run.upd_n[j];
       a.thin = run.upd_thin[j];
+      a.any_order = 1;
       double f64 = 0.0;
       const double fl = prof::on ? run.update_flops(j, vlen > 0 ? f.s : 0, &f64) : 0.0;
       prof::timed(prof::UPDATE, fl, st, [&] { launch_update<TT>(a, std::is_same<TT, float>::value, st); }, f64);
@@ -1706,7 +1710,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     if (a1 > a0)
       prof::timed(prof::GEMM, prof::on ? gemm_flops(xterms, xouts, a0, a1) : 0.0, st, [&] {
         launch_tile_gemm<TW>(at<GemmTerm<TW>>(ar, o_xterms), at<GemmOut>(ar, o_xouts) + a0, a1 - a0, xthin[ci],
-                             st);
+                             true, st);
       });
     HIPCHK(hipGetLastError());
   };
@@ -1719,7 +1723,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
     const int a0 = split[k], a1 = split[k + 1];
     if (a1 > a0)
       prof::timed(prof::GEMM, prof::on ? gemm_flops(terms, outs, a0, a1) : 0.0, st, [&] {
-        launch_tile_gemm<TW>(at<GemmTerm<TW>>(ar, o_terms), at<GemmOut>(ar, o_outs) + a0, a1 - a0, gthin[k], st);
+        launch_tile_gemm<TW>(at<GemmTerm<TW>>(ar, o_terms), at<GemmOut>(ar, o_outs) + a0, a1 - a0, gthin[k], true, st);
       });
     HIPCHK(hipGetLastError());
   };
@@ -1806,7 +1810,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   if (want_cov && !couts.empty()) {
     prof::timed(prof::GEMM, prof::on ? gemm_flops(cterms, couts, 0, (int64_t)couts.size()) : 0.0, st, [&] {
       launch_tile_gemm<double>(at<GemmTerm<double>>(ar, o_cterms), at<GemmOut>(ar, o_couts), (int)couts.size(),
-                                   cthin, st);
+                                   cthin, true, st);
     });
     HIPCHK(hipGetLastError());
   }
@@ -1818,9 +1822,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
 // ---------------------------------------------------------------------------
 // C ABI
 // ---------------------------------------------------------------------------
-extern "C" {
-
-lma_status lma_fit(const lma_problem* p, hipStream_t stream, lma_state** out) {
+static lma_status fit_guarded(const lma_problem* p, hipStream_t stream, lma_state** out, bool for_grad) {
   g_err.clear();
   g_failed = -3;
   if (!out) {
@@ -1829,7 +1831,7 @@ lma_status lma_fit(const lma_problem* p, hipStream_t stream, lma_state** out) {
   }
   *out = nullptr;
   try {
-    return do_fit(p, stream, out, true);
+    return do_fit(p, stream, out, true, for_grad);
   } catch (const Err& e) {
     set_err(e);
     return e.st;
@@ -1840,6 +1842,12 @@ lma_status lma_fit(const lma_problem* p, hipStream_t stream, lma_state** out) {
     g_err = std::string("internal error: ") + e.what();
     return LMA_E_INTERNAL;
   }
+}
+
+extern "C" {
+
+lma_status lma_fit(const lma_problem* p, hipStream_t stream, lma_state** out) {
+  return fit_guarded(p, stream, out, false);
 }
 
 lma_status lma_predict(lma_state* f, int64_t n_u, const double* U, const int64_t* u_block_ptr, double* mean,
@@ -1911,7 +1919,7 @@ lma_status lma_lml(const lma_problem* p, double* lml, double* grad, hipStream_t 
     return LMA_E_ARG;
   }
   lma_state* f = nullptr;
-  lma_status s = lma_fit(p, stream, &f);
+  lma_status s = fit_guarded(p, stream, &f, grad != nullptr);
   if (s != LMA_OK) return s;
   std::unique_ptr<lma_state> own(f);
   *lml = f->lml;

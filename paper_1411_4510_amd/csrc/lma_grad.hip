@@ -92,11 +92,11 @@ void solve_steps(Run<TT>& run, TT* invdiag, const lma_state& f, double* ldg, int
   a.logdiag = ldg;
   a.status = stat;
   a.maxT = maxT;
+  a.diag32 = f.one_order ? 1 : 0;  // as in the fit
   for (int j = 0; j < run.maxT; ++j) {
     a.j = j;
     a.items = run.d_items + run.upd_off[j];
     a.nitems = (int32_t)run.upd_n[j];
-    a.thin = run.upd_thin[j];
     double f64 = 0.0;
     const double fl = prof::on ? run.update_flops(j, factor ? f.s : 0, &f64) : 0.0;
     prof::timed(prof::UPDATE, fl, st, [&] { launch_update<TT>(a, factor && std::is_same<TT, float>::value, st); }, f64);
@@ -732,7 +732,7 @@ void grad_run(lma_state& f, double* grad_host, int64_t budget, hipStream_t st, T
   auto gemm_d = [&](const GemmBatch& b) {
     if (b.o1 > b.o0)
       prof::timed(prof::GEMM, prof::on ? gemm_flops(d_terms, outs_d, b.o0, b.o1) : 0.0, st,
-                  [&] { launch_tile_gemm<double>(dd_terms, douts_d + b.o0, (int)(b.o1 - b.o0), Thin{0, 0}, st); });
+                  [&] { launch_tile_gemm<double>(dd_terms, douts_d + b.o0, (int)(b.o1 - b.o0), Thin{0, 0}, false, st); });
     HIPCHK(hipGetLastError());
   };
   // 2 x multiply-adds of the tile products of contraction items [i0, i1) on valid entries
@@ -786,7 +786,7 @@ void grad_run(lma_state& f, double* grad_host, int64_t budget, hipStream_t st, T
     for (const GemmBatch& b : {c2[c], c2b[c]})
       if (b.o1 > b.o0)
         prof::timed(prof::GEMM, prof::on ? gemm_flops(tw_terms, outs_tw, b.o0, b.o1) : 0.0, st, [&] {
-          launch_tile_gemm<TW>(dtw_terms, douts_tw + b.o0, (int)(b.o1 - b.o0), Thin{0, 0}, st);
+          launch_tile_gemm<TW>(dtw_terms, douts_tw + b.o0, (int)(b.o1 - b.o0), Thin{0, 0}, false, st);
         });
     HIPCHK(hipGetLastError());
     gemm_d(c3[c]);
