@@ -461,39 +461,118 @@ __global__ __launch_bounds__(ThinShape<RS>::THREADS) void k_band_thin(BandArgs<T
 // ---------------------------------------------------------------------------
 // trsm: L_ij = C_ij L_jj^-T (in place) for every item (p, i), i != j
 // ---------------------------------------------------------------------------
-// The inverse is lower triangular, so the sum for columns [c0, c0 + n) ends at
-// c0 + n.  WR waves stand above each other: 2, a workgroup takes the 128 x 128 tile
-// (4 x 4 sub-tiles per wave); 1, it takes 32 rows of it (2 x 2 per wave).  Rows are
-// never split between workgroups, so the tile is replaced in place.
-// WR 0: eight waves side by side, 16 rows, one sub-tile each.
-template <typename T, int WR>
-__global__ __launch_bounds__(WR == 0 ? 2 * NT : NT) void k_trsm(StepArgs<T> a) {
-  constexpr int SUB = WR == 0 ? 1 : 2 * WR, WS = 16 * SUB, WC = WR == 0 ? 8 : 4 / WR;
-  constexpr int RS = WR == 0 ? WS : WR * WS, NP = TB / RS;
+// The inverse is lower triangular: column block c (16 wide) of a row takes the first c + 1
+// of its 8 blocks.  Rows are never split between waves, so a tile is replaced in place.
+//
+// k_trsm: a wave holds its 16 RW rows in registers (all of its loads in flight at once) and
+// reads the inverse's 36 lower blocks from LDS, where they are staged once per workgroup
+// (units of 16 bytes, placed so that a fragment's 16 rows touch every bank once); two
+// workgroups on a CU.  Bound: reading and writing the tile (3000 tiles: 800 MB, 160 us at
+// the rate of a copy).  With operands from memory and one wave per SIMD it took 259 us a
+// launch at n=262144, 212 this way; n=65536 all launches 3.72 -> 3.08 ms, mixed n=50021
+// 3.08 -> 2.66.  Sums in the same order as before, bit for bit.
+//
+// k_trsm_few: 16 rows per workgroup (strips of a tile that may hold rows), a wave per column block, operands from memory: the
+// shortest chain where the chip is not filled.
+template <typename T>
+struct TrsmLds {
+  static constexpr int PER = 16 / sizeof(T), UNITS = 16 / PER;  // elements per unit, units per block row
+  static constexpr size_t BYTES = 36 * 256 * sizeof(T);
+  // unit u of row r of a block
+  __device__ static inline int at(int r, int u) {
+    return r * UNITS + (u ^ (sizeof(T) == 8 ? (r >> 1) & 7 : (r >> 2) & 3));
+  }
+};
+
+template <typename T, int RW>
+__global__ __launch_bounds__(NT, 2) void k_trsm(StepArgs<T> a) {
+  typedef TrsmLds<T> L;
+  typedef T unit __attribute__((ext_vector_type(16 / sizeof(T))));
+  typedef typename V4<T>::type vin;
+  constexpr int RG = 64 * RW, NP = TB / RG;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  unit* inv = reinterpret_cast<unit*>(smem_raw);
   const int logical = xcd_logical(blockIdx.x, gridDim.x);
   if (logical >= a.nitems * NP) return;
   const WorkItem it = a.items[logical / NP];
   const ProbDesc pd = a.pd[it.p];
   const RowTile<T> ri = a.rt[pd.first + it.tile];
-  if (logical % NP * RS >= ri.nvalid) return;  // rows from nvalid on are zero and stay so
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int r0 = logical % NP * RS + w / WC * WS, c0 = w % WC * WS;
+  if (logical % NP * RG >= ri.nvalid) return;  // rows from nvalid on are zero and stay so
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, q = lane >> 4;
+  const int r0 = logical % NP * RG + w * 16 * RW;
   T* C = ri.panel + (int64_t)(a.j - ri.kbeg) * TB;
   const T* Li = a.invdiag + pd.invdiag_off + (int64_t)a.j * TB * TB;
-  typename Mfma<T>::acc acc[SUB][SUB];
-  zero_acc<T>(acc);
-  wave_gemm<T, T>(acc, C, ri.ld, ri.nstore, Li, TB, TB, 0, c0 + WS, r0, c0, lane);
-  __syncthreads();  // every wave has consumed its reads of C before anyone overwrites it
+  vin sa[RW][8];
 #pragma unroll
-  for (int rs = 0; rs < SUB; ++rs)
+  for (int rs = 0; rs < RW; ++rs) {
+    const int row = r0 + rs * 16 + r16;
+    const T* p = C + (int64_t)(row < ri.nstore ? row : 0) * ri.ld + 4 * q;
 #pragma unroll
-    for (int cs = 0; cs < SUB; ++cs)
+    for (int k = 0; k < 8; ++k) sa[rs][k] = *reinterpret_cast<const vin*>(p + 16 * k);
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const int nu = (c + 1) * L::UNITS;
+    for (int i = tid; i < 16 * nu; i += NT) {
+      const int r = i / nu, u = i - r * nu;
+      inv[(c * (c + 1) / 2 + u / L::UNITS) * 16 * L::UNITS + L::at(r, u % L::UNITS)] =
+          *reinterpret_cast<const unit*>(Li + (c * 16 + r) * TB + u * L::PER);
+    }
+  }
+  __syncthreads();
+  if (r0 >= ri.nvalid) return;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    typename Mfma<T>::acc acc[RW][1];
+    zero_acc<T>(acc);
+#pragma unroll
+    for (int k = 0; k <= c; ++k) {
+      const unit* blk = inv + (c * (c + 1) / 2 + k) * 16 * L::UNITS;
+      vin b;
+      if constexpr (sizeof(T) == 8) {
+        const unit b0 = blk[L::at(r16, 2 * q)], b1 = blk[L::at(r16, 2 * q + 1)];
+        b = vin{b0[0], b0[1], b1[0], b1[1]};
+      } else {
+        b = blk[L::at(r16, q)];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int rs = 0; rs < RW; ++rs) acc[rs][0] = Mfma<T>::op(sa[rs][k][e], b[e], acc[rs][0]);
+    }
+#pragma unroll
+    for (int rs = 0; rs < RW; ++rs)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = r0 + rs * 16 + Mfma<T>::row(lane, v);
-        const int col = c0 + cs * 16 + (lane & 15);
-        if (row < ri.nstore) C[(int64_t)row * ri.ld + col] = acc[rs][cs][v];
+        if (row < ri.nstore) C[(int64_t)row * ri.ld + c * 16 + r16] = acc[rs][0][v];
       }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(2 * NT) void k_trsm_few(StepArgs<T> a, int strips) {
+  const int logical = xcd_logical(blockIdx.x, gridDim.x);
+  if (logical >= a.nitems * strips) return;
+  const WorkItem it = a.items[logical / strips];
+  const ProbDesc pd = a.pd[it.p];
+  const RowTile<T> ri = a.rt[pd.first + it.tile];
+  if (logical % strips * 16 >= ri.nvalid) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // w / 8 is 0: written so, the row stays in a vector register and a launch takes 7.6 us
+  // instead of 9.0 (111 registers for 122)
+  const int r0 = logical % strips * 16 + w / 8 * 16, c0 = w % 8 * 16;
+  T* C = ri.panel + (int64_t)(a.j - ri.kbeg) * TB;
+  const T* Li = a.invdiag + pd.invdiag_off + (int64_t)a.j * TB * TB;
+  typename Mfma<T>::acc acc[1][1];
+  zero_acc<T>(acc);
+  wave_gemm<T, T>(acc, C, ri.ld, ri.nstore, Li, TB, TB, 0, c0 + 16, r0, c0, lane);
+  __syncthreads();  // every wave has consumed its reads of C before anyone overwrites it
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int row = r0 + Mfma<T>::row(lane, v);
+    if (row < ri.nstore) C[(int64_t)row * ri.ld + c0 + (lane & 15)] = acc[0][0][v];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -798,16 +877,17 @@ void launch_update(const StepArgs<T>& a, bool mixed, hipStream_t st) {
 template <typename T>
 void launch_trsm(const StepArgs<T>& a, hipStream_t st) {
   if (a.nitems <= 0) return;
-  // 16 rows per workgroup up to 32 tiles: 9.4 -> 7.3 us (n = 62 of few rows 9.0, 9.5);
-  // 32 rows per workgroup: measured 22 -> 10 us for n <= 64 tiles, 25 -> 17 at n = 128;
-  // from there on it is slower in float64 (26 -> 32 us at n = 224), and faster in
-  // float32 while its lower occupancy shows (n = 544 39 -> 37, n = 1680 97 -> 92, n = 2000 109 -> 123)
-  if (a.nitems > (std::is_same<T, float>::value ? 1200 : NCU / 2))
-    hipLaunchKernelGGL((k_trsm<T, 2>), dim3(pad8(a.nitems)), dim3(NT), 0, st, a);
-  else if (a.nitems <= NCU / 8)
-    hipLaunchKernelGGL((k_trsm<T, 0>), dim3(pad8(8 * a.nitems)), dim3(2 * NT), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_trsm<T, 1>), dim3(pad8(4 * a.nitems)), dim3(NT), 0, st, a);
+  // Few rows: two workgroups per CU (n = 62 tiles of up to 14 rows 9 us, 14 with k_trsm; n =
+  // 17 to 19 tiles 7.6 and 18).  Half tiles fill the CUs up to 256 tiles in float64 (all launches of a
+  // full GP of n=16384 8.7 ms, 9.0 with a limit of 64, 9.4 without one); in float32, where
+  // the stage is half as large, always (mixed n=50021 2.66 ms, 2.73 with a limit of 512).
+  const int strips = a.thin.n == a.nitems ? (a.thin.rows + 15) / 16 : 8;  // all of them thin tiles
+  if (a.nitems * strips <= 2 * NCU)
+    hipLaunchKernelGGL((k_trsm_few<T>), dim3(pad8(strips * a.nitems)), dim3(2 * NT), 0, st, a, strips);
+  else if (a.nitems <= NCU || std::is_same<T, float>::value)
+    hipLaunchKernelGGL((k_trsm<T, 1>), dim3(pad8(2 * a.nitems)), dim3(NT), TrsmLds<T>::BYTES, st, a);
+  else if constexpr (std::is_same<T, double>::value)
+    hipLaunchKernelGGL((k_trsm<T, 2>), dim3(pad8(a.nitems)), dim3(NT), TrsmLds<T>::BYTES, st, a);
 }
 
 template <typename T>
@@ -876,6 +956,10 @@ hipError_t engine_init() {
   for (const void* f : {(const void*)k_tile_gemm<double, 4>, (const void*)k_tile_gemm<float, 4>,
                         (const void*)k_update_part<double, false>}) {
     e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)WG_GEMM_LDS);
+    if (e != hipSuccess) return e;
+  }
+  for (const void* f : {(const void*)k_trsm<double, 1>, (const void*)k_trsm<double, 2>}) {
+    e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)TrsmLds<double>::BYTES);
     if (e != hipSuccess) return e;
   }
   e = hipFuncSetAttribute((const void*)k_band<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
