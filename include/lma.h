@@ -146,9 +146,9 @@ lma_status lma_predict_cov(lma_state *f, int64_t n_u, const double *U, const int
 lma_status lma_lml(const lma_problem *p, double *lml, double *grad, hipStream_t stream);
 
 /* Release a state (NULL is ignored).  Its device memory is kept for reuse by
- * the next lma_fit / lma_predict of a similar size (at most four blocks above
- * 1 GiB and four others are kept per process); lma_release_cache() hands them
- * back to the runtime. */
+ * the next lma_fit / lma_predict of a similar size (at most six blocks above
+ * 1 GiB and four others are kept per process, the most recent ones);
+ * lma_release_cache() hands them back to the runtime. */
 void lma_free(lma_state *f);
 
 /* Free the device blocks kept for reuse. */

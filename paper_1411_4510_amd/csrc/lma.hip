@@ -43,7 +43,7 @@ thread_local int64_t g_failed = -3;  // -3: no block (see lma_failed_block)
 namespace lmart {
 
 // Device blocks released by lma_free / lma_predict / the end of a fit are
-// kept (at most eight, four of them up to 1 GiB) and reused by the next call that fits in them: a state
+// kept (at most ten, see below) and reused by the next call that fits in them: a state
 // at the n=524288 workload is ~95 GB and mapping it anew each fit costs a few
 // hundred milliseconds.  lma_release_cache() returns them to the runtime.
 namespace devcache {
@@ -54,13 +54,14 @@ struct Block {
   uint64_t at = 0;  // when it was put back
 };
 std::mutex mu;
-// Four blocks above SMALL bytes, of which the smallest makes room, and four others, of
-// which the oldest does.  Sharing the slots, a process that had run large problems kept
-// their four blocks and allocated those of every later small call anew; past some calls
-// a second the driver then held each up until freed memory was cleared (likelihood and
+// Six slots for blocks above SMALL bytes and four for others; the oldest makes room.  More
+// than four large blocks are kept only while all of them take at most CAP bytes.  With four
+// slots for all, of which the smallest made room, a process that had run large problems kept
+// their blocks and allocated those of every later smaller call anew; past some gigabytes a
+// second the driver then held each call up until freed memory was cleared (likelihood and
 // gradient of n=1910, |S|=770 after a fit of n=65536: 16.7 ms a call, 4.7 with its own slots).
-constexpr int NSLOT = 8, NLARGE = 4;
-constexpr size_t SMALL = (size_t)1 << 30;
+constexpr int NSLOT = 10, NLARGE = 6;
+constexpr size_t SMALL = (size_t)1 << 30, CAP = (size_t)160 << 30;
 Block slots[NSLOT];
 uint64_t puts = 0;
 // real size of every block handed out (a cached block can be larger than the
@@ -125,24 +126,29 @@ void put(void* p, size_t bytes) {
     bytes = known->second;
     out_sizes.erase(known);
   }
-  const bool small = bytes <= SMALL;
-  const int s0 = small ? NLARGE : 0, s1 = small ? NSLOT : NLARGE;
-  int victim = s0;
-  for (int i = s0; i < s1; ++i) {
-    const bool before = small ? slots[i].at < slots[victim].at : slots[i].bytes < slots[victim].bytes;
-    if (!slots[i].p) {
-      victim = i;
-      break;
+  const int s0 = bytes <= SMALL ? NLARGE : 0, s1 = bytes <= SMALL ? NSLOT : NLARGE;
+  int to = -1;
+  for (;;) {
+    int oldest = -1, held = 0;
+    size_t total = bytes;
+    to = -1;
+    for (int i = s0; i < s1; ++i) {
+      if (!slots[i].p) {
+        to = i;
+        continue;
+      }
+      ++held;
+      total += slots[i].bytes;
+      if (oldest < 0 || slots[i].at < slots[oldest].at) oldest = i;
     }
-    if (before) victim = i;
-  }
-  if (slots[victim].p) {
+    if (to >= 0 && (held < 4 || total <= CAP)) break;
     const double t0 = trace() ? now_s() : 0.0;
-    (void)hipFree(slots[victim].p);
-    if (trace()) fprintf(stderr, "[devcache] evict %.2f GB in %.3f s\n", slots[victim].bytes / 1e9, now_s() - t0);
+    (void)hipFree(slots[oldest].p);
+    if (trace()) fprintf(stderr, "[devcache] evict %.2f GB in %.3f s\n", slots[oldest].bytes / 1e9, now_s() - t0);
+    slots[oldest] = Block{};
   }
   if (trace()) fprintf(stderr, "[devcache] put %.2f GB\n", bytes / 1e9);
-  slots[victim] = Block{p, bytes, dev, ++puts};
+  slots[to] = Block{p, bytes, dev, ++puts};
 }
 void release() {
   std::lock_guard<std::mutex> lk(mu);
