@@ -279,7 +279,7 @@ __global__ __launch_bounds__(NT) void k_diag32(StepArgs<T> a, const int32_t* __r
       auto pivot = [&](double d, double& root, double& ip) {
         const bool ok = d > 0.0;
         bad |= !ok;
-        d = ok ? __builtin_fmin(d, 1.7976931348623157e308) : 1.0;
+        d = ok ? __builtin_fmin(d, 1.7976931348623157e308) : 1.0;  // keeps the residuals below defined
         // correctly rounded root and reciprocal from the reciprocal root by one residual
         // each (Markstein's theorems on division and square root)
         const double y = rsqrt_pos(d), g = d * y;
@@ -337,7 +337,12 @@ __global__ __launch_bounds__(NT) void k_diag32(StepArgs<T> a, const int32_t* __r
   }
   {
     double ls = 0.0;
-    if (tid < TB && tid < rj.nvalid) ls = log(A[tid * DLD + tid]);
+    if (tid < TB && tid < rj.nvalid) {
+      // sqrt(DBL_MAX), 1.340780793e154, is the root of a pivot that was infinite (a variance beyond the range of
+      // T): its factor has no finite determinant, and the fit is refused for that
+      const double root = A[tid * DLD + tid];
+      ls = root < 1.34078079299e154 ? log(root) : INFINITY;
+    }
     for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o);
     if ((tid & 63) == 0) lsum[tid >> 6] = ls;
   }
