@@ -279,7 +279,10 @@ __global__ void k_gather_rows(const double* __restrict__ P, int d, const int64_t
 // ---------------------------------------------------------------------------
 // Every point without a centre proposes to its nearest centre holding fewer
 // than hi points (ties to the lower index).
-// Four waves share 64 points and the centres as in the nearest-centre assignment.
+// Four waves share 64 points and the centres as in the nearest-centre assignment.  At most
+// PROPOSE_WG workgroups walk over the points: with one per 64 points a launch has four
+// threads per point, and from 2^30 points on more than its 2^32 - 1.
+constexpr int64_t PROPOSE_WG = 65536;
 __global__ __launch_bounds__(NT) void k_propose(const double* __restrict__ P, int64_t n, int d,
                                                 const double* __restrict__ C, int k, int64_t hi,
                                                 const int64_t* __restrict__ cnt, const int32_t* __restrict__ label,
@@ -290,55 +293,58 @@ __global__ __launch_bounds__(NT) void k_propose(const double* __restrict__ P, in
   __shared__ int sa[4][64];
   __shared__ uint32_t hist[HIST_K];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
-  const bool live = i < n && label[i] < 0;
-  const double* p = P + (i < n ? i : 0) * d;
-  double best = INFINITY;
-  int arg = -1;
-  if (__any(live))
-    for (int c0 = w * CG; c0 < k; c0 += 4 * CG) {
-      const int nc = k - c0 < CG ? k - c0 : CG;
-      double acc[CG];
+  for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < n; i0 += (int64_t)gridDim.x * 64) {
+    const int64_t i = i0 + lane;
+    const bool live = i < n && label[i] < 0;
+    const double* p = P + (i < n ? i : 0) * d;
+    double best = INFINITY;
+    int arg = -1;
+    if (__any(live))
+      for (int c0 = w * CG; c0 < k; c0 += 4 * CG) {
+        const int nc = k - c0 < CG ? k - c0 : CG;
+        double acc[CG];
 #pragma unroll
-      for (int jj = 0; jj < CG; ++jj) acc[jj] = 0.0;
-      const double* cb = C + (int64_t)c0 * d;
-      for (int t = 0; t < d; ++t) {
-        const double x = p[t];
+        for (int jj = 0; jj < CG; ++jj) acc[jj] = 0.0;
+        const double* cb = C + (int64_t)c0 * d;
+        for (int t = 0; t < d; ++t) {
+          const double x = p[t];
 #pragma unroll
-        for (int jj = 0; jj < CG; ++jj) {
-          if (jj < nc) {
-            const double df = x - cb[jj * d + t];
-            const double sq = df * df;
-            acc[jj] = acc[jj] + sq;
+          for (int jj = 0; jj < CG; ++jj) {
+            if (jj < nc) {
+              const double df = x - cb[jj * d + t];
+              const double sq = df * df;
+              acc[jj] = acc[jj] + sq;
+            }
           }
         }
-      }
 #pragma unroll
-      for (int jj = 0; jj < CG; ++jj)
-        if (jj < nc && cnt[c0 + jj] < hi && (arg < 0 || acc[jj] < best)) {
-          best = acc[jj];
-          arg = c0 + jj;
-        }
-    }
-  sb[w][lane] = best;
-  sa[w][lane] = arg;
-  __syncthreads();
-  int take = -1;
-  if (w == 0 && live) {
-    for (int q = 1; q < 4; ++q) {
-      const double v = sb[q][lane];
-      const int c = sa[q][lane];
-      // the first open centre wins whatever its distance, a later one if it is nearer
-      if (c >= 0 && (arg < 0 || v < best || (c < arg && !(best < v)))) {
-        best = v;
-        arg = c;
+        for (int jj = 0; jj < CG; ++jj)
+          if (jj < nc && cnt[c0 + jj] < hi && (arg < 0 || acc[jj] < best)) {
+            best = acc[jj];
+            arg = c0 + jj;
+          }
       }
+    sb[w][lane] = best;
+    sa[w][lane] = arg;
+    __syncthreads();
+    int take = -1;
+    if (w == 0 && live) {
+      for (int q = 1; q < 4; ++q) {
+        const double v = sb[q][lane];
+        const int c = sa[q][lane];
+        // the first open centre wins whatever its distance, a later one if it is nearer
+        if (c >= 0 && (arg < 0 || v < best || (c < arg && !(best < v)))) {
+          best = v;
+          arg = c;
+        }
+      }
+      tgt[i] = arg;
+      key[i] = best;
+      take = arg;  // an open centre exists while points are left
     }
-    tgt[i] = arg;
-    key[i] = best;
-    take = arg;  // an open centre exists while points are left
+    count_place(pcnt, k, take, k <= HIST_K ? hist : nullptr, nullptr);
+    __syncthreads();  // sb, sa and hist are read before the next points overwrite them
   }
-  count_place(pcnt, k, take, k <= HIST_K ? hist : nullptr, nullptr);
 }
 
 // One workgroup: segment offsets from the per-segment counts (which it then
@@ -857,8 +863,8 @@ int32_t bounded(const double* P, int64_t n, int32_t d, const double* C, int32_t 
   while (left > 0) {
     if (rounds > k + 1) throw Err{LMA_E_INTERNAL, "bounded assignment did not finish in k + 1 rounds"};
     ++rounds;
-    hipLaunchKernelGGL(k_propose, dim3((unsigned)((n + 63) / 64)), dim3(NT), 0, st, P, n, (int)d, C, (int)k, hi, b.cnt, label,
-                       b.tgt, b.key, b.pcnt);
+    hipLaunchKernelGGL(k_propose, dim3((unsigned)std::min<int64_t>((n + 63) / 64, PROPOSE_WG)), dim3(NT), 0, st, P, n,
+                       (int)d, C, (int)k, hi, b.cnt, label, b.tgt, b.key, b.pcnt);
     chk();
     hipLaunchKernelGGL(k_seg_offsets, dim3(1), dim3(1024), 0, st, b.pcnt, (int)k, b.seg_ptr, b.cursor, b.cnt, hi, 0,
                        b.rank);

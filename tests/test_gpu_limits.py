@@ -24,3 +24,18 @@ def test_variance_beyond_the_storage_type_is_refused(lib, precision, log_sn2, B)
         with pytest.raises(lib.LmaError) as e:
             call()
         assert e.value.status == lib.LMA_E_NOT_PD and e.value.block is None
+
+
+# 2^30 points (a launch holds fewer than 2^32 threads) and one more: every count and label
+def test_bounded_assignment_of_two_to_the_thirty_points(lib):
+    import torch
+    n = 2 ** 30 + 1
+    P = torch.rand((n, 1), dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    C = torch.tensor([[0.25], [0.75]], dtype=torch.float64, device="cuda")
+    label, count, rounds = lib.bounded_assign(P, C, 0, n)
+    nearer = (P[:, 0] - 0.25) ** 2 <= (P[:, 0] - 0.75) ** 2   # ties to the lower index
+    assert rounds == 1 and bool(torch.equal(label == 0, nearer))
+    assert count.tolist() == [int(nearer.sum()), n - int(nearer.sum())]
+    del P, label, nearer
+    lib.release_cache()
+    torch.cuda.empty_cache()
