@@ -14,14 +14,17 @@
 //     select on the (float64 bit pattern, index) pair: non-negative doubles
 //     order like their bit patterns.
 //
-// Seeding: two launches per round.  One updates each point's distance to its
-// nearest chosen centre and the block maxima; every workgroup of it first finds the
-// point drawn last for itself (a scan of the block sums, then of the weights of one
-// block; the distances alternate between two arrays, so that block is still there
-// unchanged).  The other derives the power-of-two scale from the maxima, again in
-// every workgroup, and forms the block sums of the weights.  No host synchronisation
-// between rounds.  Bound: the launches (2 to 4 us each); with the scale and the draw
-// in launches of one workgroup a round had four (n=65536, k=64: 775 us in 252 launches, 500 us in 126 now).
+// Seeding: two launches per round up to SEED_SCAN blocks of points.  One updates each
+// point's distance to its nearest chosen centre and the block maxima; every workgroup of
+// it first finds the point drawn last for itself (a scan of the block sums, then of the
+// weights of one block; the distances alternate between two arrays, so that block is
+// still there unchanged).  The other derives the power-of-two scale from the maxima,
+// again in every workgroup, and forms the block sums of the weights.  No host
+// synchronisation between rounds.  Bound: the launches (2 to 4 us each).  What the
+// workgroups scan grows with the square of n, so beyond SEED_SCAN the scale and the draw
+// are launches of one workgroup (four a round) and the bound is reading the points.  us a
+// round at d=4, two launches / four: n=65536 8.9 / 11.0, 524288 16.0 / 18.5, 1048576
+// 55.4 / 29.8, 4194304 906 / 83, 16777216 17494 / 340.
 //
 // Counts per centre are formed in LDS and added to the global counters once per
 // workgroup and centre (k <= HIST_K): one atomic per point on a few dozen counters
@@ -203,18 +206,48 @@ __device__ int64_t seed_pick(const double* __restrict__ dmin, int64_t n, const i
   return found_i;
 }
 
-// Round j: draw point j (j > 0) from the weights of dold, then the distances to the
-// nearest of the points 0..j in dnew and their block maxima.
+// Shift W - e of the weights and whether every weight is 0, from the block maxima
+// (workgroup-wide; the same in every workgroup).
+struct SeedScale {
+  int shift, zero, nonfinite;
+};
+__device__ SeedScale seed_scale(const double* __restrict__ bmax, int64_t nb, int wbits) {
+  __shared__ double sh[NT / 64];
+  double m = 0.0;
+  for (int64_t b = threadIdx.x; b < nb; b += NT) m = fmax(m, bmax[b]);
+  m = block_max(m, sh);
+  SeedScale s{0, 1, !isfinite(m)};
+  if (isfinite(m) && m > 0.0) {
+    int e = 0;
+    (void)frexp(m, &e);
+    s.shift = wbits - e;
+    s.zero = 0;
+  }
+  return s;
+}
+// scal[0] = shift, scal[1] = 1 when every weight is 0, scal[2] |= 1 on a non-finite maximum
+__device__ void put_scale(const SeedScale& s, int32_t* __restrict__ scal) {
+  scal[0] = s.shift;
+  scal[1] = s.zero;
+  if (s.nonfinite) scal[2] = 1;
+}
+
+// Round j: the distances to the nearest of the points 0..j in dnew and their block maxima.
+// PICK: point j (j > 0) is drawn here from the weights of dold, which every workgroup reads
+// and none may overwrite; else it is in sidx[j], and dnew may be dold.
+template <bool PICK>
 __global__ __launch_bounds__(NT) void k_seed_dmin(const double* __restrict__ P, int64_t n, int d, int j,
                                                   const int32_t* __restrict__ scal, const uint64_t* __restrict__ bsum,
                                                   int64_t nb, const uint32_t* __restrict__ rnd,
-                                                  int64_t* __restrict__ sidx, const double* __restrict__ dold,
-                                                  double* __restrict__ dnew, double* __restrict__ bmax) {
+                                                  int64_t* __restrict__ sidx, const double* dold, double* dnew,
+                                                  double* __restrict__ bmax) {
   __shared__ double sh[NT / 64];
-  int64_t c = sidx[0];
-  if (j > 0) {
+  int64_t c;
+  if (PICK && j > 0) {
     c = seed_pick(dold, n, scal, bsum, nb, rnd[j]);
     if (blockIdx.x == 0 && threadIdx.x == 0) sidx[j] = c;
+  } else {
+    c = sidx[j];
   }
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
   double v = 0.0;
@@ -228,35 +261,34 @@ __global__ __launch_bounds__(NT) void k_seed_dmin(const double* __restrict__ P, 
   if (threadIdx.x == 0) bmax[blockIdx.x] = m;
 }
 
-// Block sums of the weights; scal[0] = shift W - e, scal[1] = 1 when every weight is
-// 0, scal[2] |= 1 on a non-finite maximum
+// one workgroup: the scale of a round
+__global__ __launch_bounds__(NT) void k_seed_scale(const double* __restrict__ bmax, int64_t nb, int wbits,
+                                                   int32_t* __restrict__ scal) {
+  const SeedScale s = seed_scale(bmax, nb, wbits);
+  if (threadIdx.x == 0) put_scale(s, scal);
+}
+
+// Block sums of the weights.  SCALE: with the scale from the block maxima, which goes to
+// scal; else with the scale in scal.
+template <bool SCALE>
 __global__ __launch_bounds__(NT) void k_seed_wsum(const double* __restrict__ dmin, int64_t n,
                                                   const double* __restrict__ bmax, int64_t nb, int wbits,
                                                   int32_t* __restrict__ scal, uint64_t* __restrict__ bsum) {
-  __shared__ double shd[NT / 64];
   __shared__ uint64_t sh[NT / 64];
-  double m = 0.0;
-  for (int64_t b = threadIdx.x; b < nb; b += NT) m = fmax(m, bmax[b]);
-  m = block_max(m, shd);
-  int shift = 0, zero = 1;
-  if (isfinite(m) && m > 0.0) {
-    int e = 0;
-    (void)frexp(m, &e);
-    shift = wbits - e;
-    zero = 0;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    scal[0] = shift;
-    scal[1] = zero;
-    if (!isfinite(m)) scal[2] = 1;
+  SeedScale sc;
+  if (SCALE) {
+    sc = seed_scale(bmax, nb, wbits);
+    if (blockIdx.x == 0 && threadIdx.x == 0) put_scale(sc, scal);
+  } else {
+    sc = SeedScale{scal[0], scal[1], 0};
   }
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  const uint64_t w = i < n ? weight_of(dmin[i], shift, zero) : 0;
+  const uint64_t w = i < n ? weight_of(dmin[i], sc.shift, sc.zero) : 0;
   const uint64_t s = block_sum_u64(w, sh);
   if (threadIdx.x == 0) bsum[blockIdx.x] = s;
 }
 
-// one workgroup: the drawn point of the last round
+// one workgroup: the point of round j
 __global__ __launch_bounds__(NT) void k_seed_pick(const double* __restrict__ dmin, int64_t n,
                                                   const int32_t* __restrict__ scal,
                                                   const uint64_t* __restrict__ bsum, int64_t nb,
@@ -687,6 +719,11 @@ constexpr int MAX_K = 65536;
 
 int64_t nblocks(int64_t n) { return (n + NT - 1) / NT; }
 
+constexpr int64_t SEED_SCAN = 2048;  // blocks of points up to which every workgroup scans them all (see above)
+
+// distances of the seeding: two arrays where every workgroup draws for itself
+size_t seed_dist_bytes(int64_t n) { return (nblocks(n) <= SEED_SCAN ? 16 : 8) * (size_t)n; }
+
 void chk() {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) throw Err{LMA_E_HIP, std::string("partition kernel launch: ") + hipGetErrorString(e)};
@@ -751,7 +788,7 @@ void check_finite(const double* a, int64_t n, int32_t* flag, hipStream_t st, con
 }
 
 // k-means++ seeding: indices into sidx (device [k]), centres into C (device
-// [k][d]); ws pieces: dmin [2][n], bmax/bsum [nb], scal [3], rnd [k].
+// [k][d]); ws pieces: dmin (seed_dist_bytes), bmax/bsum [nb], scal [3], rnd [k].
 void seed(const double* P, int64_t n, int32_t d, int32_t k, const uint32_t* rand_h, double* C, int64_t* sidx,
           double* dmin, double* bmax, uint64_t* bsum, int32_t* scal, uint32_t* rnd, hipStream_t st) {
   const int64_t nb = nblocks(n);
@@ -761,16 +798,26 @@ void seed(const double* P, int64_t n, int32_t d, int32_t k, const uint32_t* rand
   HIPCHK(hipMemcpyAsync(sidx, &first, 8, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemsetAsync(scal, 0, 12, st));
   const int wb = weight_bits(n);
+  const dim3 all((unsigned)nb), one(1), nt(NT);
   for (int j = 0; j < k - 1; ++j) {
-    double* dnew = dmin + (j & 1) * n;
-    hipLaunchKernelGGL(k_seed_dmin, dim3((unsigned)nb), dim3(NT), 0, st, P, n, (int)d, j, scal, bsum, nb, rnd, sidx,
-                       dmin + ((j + 1) & 1) * n, dnew, bmax);
-    chk();
-    hipLaunchKernelGGL(k_seed_wsum, dim3((unsigned)nb), dim3(NT), 0, st, dnew, n, bmax, nb, wb, scal, bsum);
-    chk();
-  }
-  if (k > 1) {
-    hipLaunchKernelGGL(k_seed_pick, dim3(1), dim3(NT), 0, st, dmin + (k & 1) * n, n, scal, bsum, nb, rnd, k - 1, sidx);
+    const bool own = nb <= SEED_SCAN;
+    const double* dold = dmin + (own ? ((j + 1) & 1) * n : 0);
+    double* dnew = dmin + (own ? (j & 1) * n : 0);
+    if (own) {
+      hipLaunchKernelGGL(k_seed_dmin<true>, all, nt, 0, st, P, n, (int)d, j, scal, bsum, nb, rnd, sidx, dold, dnew, bmax);
+      chk();
+      hipLaunchKernelGGL(k_seed_wsum<true>, all, nt, 0, st, dnew, n, bmax, nb, wb, scal, bsum);
+      chk();
+      if (j < k - 2) continue;
+    } else {
+      hipLaunchKernelGGL(k_seed_dmin<false>, all, nt, 0, st, P, n, (int)d, j, scal, bsum, nb, rnd, sidx, dold, dnew, bmax);
+      chk();
+      hipLaunchKernelGGL(k_seed_scale, one, nt, 0, st, bmax, nb, wb, scal);
+      chk();
+      hipLaunchKernelGGL(k_seed_wsum<false>, all, nt, 0, st, dnew, n, bmax, nb, wb, scal, bsum);
+      chk();
+    }
+    hipLaunchKernelGGL(k_seed_pick, one, nt, 0, st, dnew, n, scal, bsum, nb, rnd, j + 1, sidx);
     chk();
   }
   const int64_t kd = (int64_t)k * d;
@@ -978,7 +1025,7 @@ lma_status lma_kmeans_seed(const double* P, int64_t n, int32_t d, int32_t k, con
     if (!rand || !C) throw Err{LMA_E_ARG, "NULL array"};
     const int64_t nb = nblocks(n);
     Work w;
-    const size_t o_dmin = w.take(16 * (size_t)n), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
+    const size_t o_dmin = w.take(seed_dist_bytes(n)), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
     const size_t o_scal = w.take(16), o_rnd = w.take(4 * (size_t)k), o_sidx = w.take(8 * (size_t)k);
     w.get(stream);
     check_finite(P, n * d, w.at<int32_t>(o_scal), stream, "P");
@@ -1029,7 +1076,7 @@ lma_status lma_partition(const double* X, int64_t n, const double* U, int64_t n_
     Work w;
     std::vector<size_t> o;
     bounded_reserve(w, n, M, o);
-    const size_t o_dmin = w.take(16 * (size_t)n), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
+    const size_t o_dmin = w.take(seed_dist_bytes(n)), o_bmax = w.take(8 * (size_t)nb), o_bsum = w.take(8 * (size_t)nb);
     const size_t o_scal = w.take(16), o_rnd = w.take(4 * (size_t)M), o_sidx = w.take(8 * (size_t)M);
     const size_t o_C = w.take(8 * (size_t)M * d), o_Cb = w.take(8 * (size_t)M * d);
     const size_t o_label = w.take(4 * (size_t)nmax), o_keys = w.take(4 * (size_t)nmax);

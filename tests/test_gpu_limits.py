@@ -39,3 +39,38 @@ def test_bounded_assignment_of_two_to_the_thirty_points(lib):
     del P, label, nearer
     lib.release_cache()
     torch.cuda.empty_cache()
+
+
+# seeding with its draw in every workgroup (up to 2048 blocks of 256 points) and in one:
+# the same indices as the oracle on both sides of the edge, no points, one round, several
+@pytest.mark.parametrize("n,k", [(2048 * 256, 5), (2048 * 256 + 1, 1), (2048 * 256 + 1, 2), (2048 * 256 + 1, 3), (700001, 6)])
+def test_seeding_on_both_sides_of_the_scan_limit(lib, n, k):
+    from oracle import partition as opart
+    rng = np.random.default_rng(n + k)
+    P = np.round(rng.uniform(size=(n, 2)), 2)     # points on chosen centres: weights of 0
+    rand = rng.integers(0, 2 ** 32, size=k, dtype=np.uint64).astype(np.uint32)
+    C, idx = lib.kmeans_seed(P, k, rand)
+    Co, io = opart.seed(P, k, rand)
+    assert np.array_equal(idx.cpu().numpy(), io) and np.array_equal(C.cpu().numpy(), Co)
+
+
+# the time of a round grows as the points do: fourfold points take about four times as long
+# (17 times where every workgroup scanned every block)
+def test_seeding_time_is_linear_in_the_points(lib):
+    import time
+    import torch
+    rand = np.random.default_rng(1).integers(0, 2 ** 32, size=33, dtype=np.uint64).astype(np.uint32)
+    t = []
+    for n in (2 ** 22, 2 ** 24):
+        P = torch.rand((n, 4), dtype=torch.float64, device="cuda")
+        lib.kmeans_seed(P, 33, rand)
+        runs = []
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            lib.kmeans_seed(P, 33, rand)
+            torch.cuda.synchronize()
+            runs.append(time.perf_counter() - t0)
+        t.append(min(runs))
+    print(f"  33 centres: {t[0] * 1e3:.2f} ms at 2^22 points, {t[1] * 1e3:.2f} ms at 2^24", flush=True)
+    assert t[1] < 8 * t[0]
