@@ -682,6 +682,11 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     f.ar.used = f.ar.cap;
     if (use_band) {
       bpl.mem = devcache::get((size_t)bpl.bytes);
+      if (!bpl.mem && bpl.o_part >= 0) {  // the band alone
+        bpl.bytes = bpl.o_part;
+        bpl.o_part = -1;
+        bpl.mem = devcache::get((size_t)bpl.bytes);
+      }
       bpl.st = st;
       if (!bpl.mem) use_band = false;  // not enough device memory: windows form their entries themselves
     }
@@ -1344,7 +1349,6 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   const int64_t o_kvpart = ar.reserve(8 * kvec_part_elems(nkv, kv_split));
   const int64_t o_hq = ar.reserve(8 * M * sp);
   const int64_t o_tb = ar.reserve(wsz * std::max<int64_t>(tb_elems, 1));
-  const int64_t o_part = use_tband && maxT >= PART_MIN_T ? ar.reserve(PART_BYTES) : -1;  // split products
   auto build = [&](char* base) {
     ar.base = base;
     runS = Run<double>();
@@ -1563,8 +1567,16 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   const int64_t o_couts = ar.reserve(sizeof(GemmOut) * std::max<size_t>(couts.size(), 1));
   const int64_t o_xterms = ar.reserve(sizeof(GemmTerm<TW>) * std::max<size_t>(xterms.size(), 1));
   const int64_t o_xouts = ar.reserve(sizeof(GemmOut) * std::max<size_t>(xouts.size(), 1));
+  const int64_t need = ar.used;
+  // split products, where the memory is there for it
+  int64_t o_part = use_tband && maxT >= PART_MIN_T ? ar.reserve(PART_BYTES) : -1;
   ar.cap = ar.used;
   void* mem = devcache::get((size_t)ar.cap);
+  if (!mem && o_part >= 0) {
+    o_part = -1;
+    ar.cap = need;
+    mem = devcache::get((size_t)ar.cap);
+  }
   if (!mem) throw Err{LMA_E_NOMEM, "device allocation of the prediction workspace failed"};
   struct Guard {
     void* p;
@@ -1591,7 +1603,7 @@ static void predict_impl(lma_state& f, int64_t n_u, const double* U, const int64
   std::vector<int32_t> ublk(n_u);
   for (int64_t q = 0; q < M; ++q)
     for (int64_t u = ubp[q]; u < ubp[q + 1]; ++u) ublk[u] = (int32_t)q;
-  Stage up(at<char>(ar, o_stat), ar.cap - o_stat, st);
+  Stage up(at<char>(ar, o_stat), need - o_stat, st);
   {
     up.zero(at<char>(ar, o_stat), 4 * (size_t)(M + 2));
     char* mp = at<char>(ar, o_meta);

@@ -74,3 +74,56 @@ def test_seeding_time_is_linear_in_the_points(lib):
         t.append(min(runs))
     print(f"  33 centres: {t[0] * 1e3:.2f} ms at 2^22 points, {t[1] * 1e3:.2f} ms at 2^24", flush=True)
     assert t[1] < 8 * t[0]
+
+
+def settled_free_memory():
+    """Free device memory once the driver has taken back what was freed."""
+    import time
+    import torch
+    torch.cuda.synchronize()
+    last = -1
+    for _ in range(40):
+        now = torch.cuda.mem_get_info()[0]
+        if now == last:
+            break
+        last = now
+        time.sleep(0.25)
+    return last
+
+
+# A prediction with 24 MiB more than it cannot do without: the 64 MiB for sums of split
+# products are an extra that it leaves out (the order of its sums differs then, no more)
+def test_prediction_without_room_for_its_extra_workspace(lib):
+    import torch
+    p = synth.make_random(seed=3, n=6000, d=4, M=5, s=60, n_u=100, B=2, uneven=(1180, 1220), sn2=0.05)
+    state = lib.fit_problem(p)
+    U = torch.as_tensor(p.U, device="cuda")
+    mean, var = (t.clone() for t in state.predict(U, p.u_block_ptr))
+    lib.release_cache()
+    torch.cuda.empty_cache()
+    before = settled_free_memory()
+    state.predict(U, p.u_block_ptr)
+    workspace = before - settled_free_memory()  # the library keeps it for the next call
+    lib.release_cache()
+    torch.cuda.empty_cache()
+    fill = [torch.empty(settled_free_memory() - (2 << 30), dtype=torch.uint8, device="cuda")]
+    for piece in (256 << 20, 12 << 20):  # until the device is full
+        try:
+            while True:
+                fill.append(torch.empty(piece, dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:
+            if piece == 256 << 20:
+                fill.pop()  # room for small pieces
+                torch.cuda.empty_cache()
+    room = 0
+    while room < workspace - (40 << 20):
+        room += fill.pop().numel()
+    torch.cuda.empty_cache()
+    print(f"  workspace {workspace >> 20} MiB, room {room >> 20} MiB", flush=True)
+    mean2, var2 = state.predict(U, p.u_block_ptr)
+    del fill
+    state.free()
+    lib.release_cache()
+    torch.cuda.empty_cache()
+    assert workspace > (64 << 20)
+    assert float((mean2 - mean).norm() / mean.norm()) < 1e-9 and float((var2 - var).norm() / var.norm()) < 1e-9
