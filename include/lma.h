@@ -146,8 +146,9 @@ lma_status lma_predict_cov(lma_state *f, int64_t n_u, const double *U, const int
 lma_status lma_lml(const lma_problem *p, double *lml, double *grad, hipStream_t stream);
 
 /* Release a state (NULL is ignored).  Its device memory is kept for reuse by
- * the next lma_fit / lma_predict of a similar size (at most six blocks above
- * 1 GiB and four others are kept per process, the most recent ones);
+ * the next lma_fit / lma_predict of a similar size: per process the most recent
+ * blocks up to 1 GiB, at most twelve and 4 GiB in all, and the most recent larger
+ * ones, at most four of any size, or eight of together 160 GiB;
  * lma_release_cache() hands them back to the runtime. */
 void lma_free(lma_state *f);
 

@@ -43,7 +43,7 @@ thread_local int64_t g_failed = -3;  // -3: no block (see lma_failed_block)
 namespace lmart {
 
 // Device blocks released by lma_free / lma_predict / the end of a fit are
-// kept (at most ten, see below) and reused by the next call that fits in them: a state
+// kept (up to two caps, see below) and reused by the next call that fits in them: a state
 // at the n=524288 workload is ~95 GB and mapping it anew each fit costs a few
 // hundred milliseconds.  lma_release_cache() returns them to the runtime.
 namespace devcache {
@@ -54,14 +54,17 @@ struct Block {
   uint64_t at = 0;  // when it was put back
 };
 std::mutex mu;
-// Six slots for blocks above SMALL bytes and four for others; the oldest makes room.  More
-// than four large blocks are kept only while all of them take at most CAP bytes.  With four
-// slots for all, of which the smallest made room, a process that had run large problems kept
-// their blocks and allocated those of every later smaller call anew; past some gigabytes a
-// second the driver then held each call up until freed memory was cleared (likelihood and
-// gradient of n=1910, |S|=770 after a fit of n=65536: 16.7 ms a call, 4.7 with its own slots).
-constexpr int NSLOT = 10, NLARGE = 6;
-constexpr size_t SMALL = (size_t)1 << 30, CAP = (size_t)160 << 30;
+// Slots of their own for blocks above SMALL bytes and for others; in each class the oldest
+// block makes room.  More than four blocks of a class are kept only while all of them take
+// at most its cap.  With four slots for all, of which the smallest made room, a process that
+// had run large problems kept their blocks and allocated those of every later smaller call
+// anew; past some gigabytes a second the driver then held each call up until freed memory
+// was cleared (likelihood and gradient of n=1910, |S|=770 after a fit of n=65536: 16.7 ms a
+// call, 4.7 with its own slots).  One fit, prediction and gradient use four blocks, so there
+// are slots for two problems and more taken in turn (likelihood and gradient of n=1500 in
+// turn with one of n=6000, |S|=1000: 3.0 ms with four slots, 2.2 now).
+constexpr int NLARGE = 8, NSLOT = NLARGE + 12;
+constexpr size_t SMALL = (size_t)1 << 30, CAP_SMALL = (size_t)4 << 30, CAP_LARGE = (size_t)160 << 30;
 Block slots[NSLOT];
 uint64_t puts = 0;
 // real size of every block handed out (a cached block can be larger than the
@@ -126,7 +129,8 @@ void put(void* p, size_t bytes) {
     bytes = known->second;
     out_sizes.erase(known);
   }
-  const int s0 = bytes <= SMALL ? NLARGE : 0, s1 = bytes <= SMALL ? NSLOT : NLARGE;
+  const bool small = bytes <= SMALL;
+  const int s0 = small ? NLARGE : 0, s1 = small ? NSLOT : NLARGE;
   int to = -1;
   for (;;) {
     int oldest = -1, held = 0;
@@ -141,7 +145,7 @@ void put(void* p, size_t bytes) {
       total += slots[i].bytes;
       if (oldest < 0 || slots[i].at < slots[oldest].at) oldest = i;
     }
-    if (to >= 0 && (held < 4 || total <= CAP)) break;
+    if (to >= 0 && (held < 4 || total <= (small ? CAP_SMALL : CAP_LARGE))) break;
     const double t0 = trace() ? now_s() : 0.0;
     (void)hipFree(slots[oldest].p);
     if (trace()) fprintf(stderr, "[devcache] evict %.2f GB in %.3f s\n", slots[oldest].bytes / 1e9, now_s() - t0);

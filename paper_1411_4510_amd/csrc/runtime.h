@@ -112,7 +112,7 @@ class Stage {
 };
 
 // Device blocks released by lma_free / lma_predict / the end of a fit are kept
-// (at most ten) and reused by the next call that fits in them (see lma.hip).
+// (up to two caps) and reused by the next call that fits in them (see lma.hip).
 namespace devcache {
 void* get(size_t bytes);
 void put(void* p, size_t bytes);

@@ -127,3 +127,65 @@ def test_prediction_without_room_for_its_extra_workspace(lib):
     torch.cuda.empty_cache()
     assert workspace > (64 << 20)
     assert float((mean2 - mean).norm() / mean.norm()) < 1e-9 and float((var2 - var).norm() / var.norm()) < 1e-9
+
+
+CACHE_SCRIPT = """
+import sys
+import numpy as np
+import paper_1411_4510_amd as lma
+import synth
+
+def problem(n, M, s, seed):
+    return synth.make_random(seed=seed, n=n, d=3, M=M, s=s, n_u=50, B=2, uneven=(n // M - 20, n // M + 20), sn2=0.05)
+
+def mark(text):
+    print("== " + text, file=sys.stderr, flush=True)
+
+a, b = problem(6000, 3, 1000, 1), problem(1500, 3, 200, 2)
+for i in range(4):
+    mark("cycle %d" % i)
+    for p in (a, b):
+        st = lma.fit_problem(p)
+        st.predict(p.U, p.u_block_ptr)
+        st.free()
+        lma.LmlProblem.from_problem(p)(p.log_hyp, grad=True)
+mark("many")
+states = [lma.fit_problem(problem(6000 + 300 * i, 3, 400, i)) for i in range(16)]
+for st in states:
+    st.free()
+mark("released")
+lma.release_cache()
+mark("end")
+"""
+
+
+# The device cache, by its own trace: two problems of different sizes taken in turn allocate
+# nothing once both have run, and what is kept is at most twelve blocks and 4 GiB of those
+# up to 1 GiB, all of it handed back by lma_release_cache
+def test_device_cache_keeps_two_problems_and_is_bounded(lib):
+    import os
+    import re
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", CACHE_SCRIPT], cwd=root, env={**os.environ, "LMA_CACHE_TRACE": "1"},
+                       capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    where, kept, mallocs, most = "", [], {}, (0, 0.0)
+    for line in r.stderr.splitlines():
+        if line.startswith("== "):
+            where = line[3:]
+        elif "hipMalloc" in line:
+            mallocs[where] = mallocs.get(where, 0) + 1
+        elif m := re.search(r"put ([\d.]+) GB", line):
+            kept.append(float(m[1]))
+        elif m := re.search(r"cached block of ([\d.]+) GB|evict ([\d.]+) GB", line):
+            kept.remove(float(m[1] or m[2]))
+        elif m := re.search(r"free all: ([\d.]+) GB", line):
+            assert abs(float(m[1]) - sum(kept)) < 0.01 * (len(kept) + 1)
+            kept = []
+        if "put" not in line:      # a block is put once its predecessor is evicted
+            most = max(most, (len([k for k in kept if k <= 1.08]), sum(k for k in kept if k <= 1.08)))
+    print(f"  hipMalloc calls {mallocs}, most blocks kept {most}", flush=True)
+    assert mallocs["cycle 0"] > 0 and mallocs.get("cycle 2", 0) == mallocs.get("cycle 3", 0) == 0
+    assert most[0] <= 12 and most[1] <= 4.3 + 0.12 and kept == []
