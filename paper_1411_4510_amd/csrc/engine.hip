@@ -272,7 +272,7 @@ __global__ __launch_bounds__(NT, (std::is_same<T, double>::value) ? 2 : 1) void 
 // 53.2 -> 51.0, n=262144 all updates 690 -> 676.
 template <int RS>
 struct ThinShape {
-  static constexpr int NW = 8, THREADS = 64 * NW, ELEMS = RS * 256;
+  static constexpr int NW = 8, THREADS = 64 * NW, ELEMS = RS * 256;  // NW whatever RS is
 };
 
 // this wave's share of [k0, k1) in units of U chunks of 16; a last chunk of its own joins
@@ -698,6 +698,16 @@ __global__ __launch_bounds__(NT, 2) void k_band(BandArgs<T> a) {
 constexpr int NCU = 256;  // compute units
 static inline int pad8(int n) { return ((n + 7) / 8) * 8; }
 
+// Calls f(first, count) for pieces of n items that fit a launch (fewer than 2^32 threads; of
+// a larger one only the remainder runs, without an error) with `threads` per item.  The
+// forms that give a tile eight workgroups of 512 reach that with 1048576 tiles, which half a
+// million windows of one or two points have.
+template <class F>
+static void in_launches(int64_t n, int64_t threads, F&& f) {
+  const int64_t most = 0xffffffffll / threads & ~7ll;  // whole launches of a multiple of 8 workgroups
+  for (int64_t i = 0; i < n; i += most) f(i, std::min(most, n - i));
+}
+
 // Pieces per tile side (1, 2 or 4) of a launch of n whole tiles with products of
 // length k.  A whole tile gives its products the most reuse but only one workgroup
 // fits on a CU, so n tiles take ceil(n / 256) turns.  Measured (k_update, float64, in
@@ -714,18 +724,20 @@ static inline int split_of(int64_t n, int64_t k) {
 }
 
 template <typename T, bool MIXED>
-static void update_pieces(StepArgs<T> a, int64_t i0, int64_t n, int split, hipStream_t st) {
-  if (n <= 0) return;
-  a.items += i0;
-  a.nitems = (int32_t)n;
-  size_t lds = 2 * (size_t)a.d * (TB / split) * (MIXED ? sizeof(double) : sizeof(T));
+static void update_pieces(const StepArgs<T>& all, int64_t first, int64_t count, int split, hipStream_t st) {
+  size_t lds = 2 * (size_t)all.d * (TB / split) * (MIXED ? sizeof(double) : sizeof(T));
   if (std::is_same<T, double>::value && split == 1) lds = std::max(lds, WG_GEMM_LDS);
-  const dim3 grid(pad8(a.nitems * split * split));
-  switch (split) {
-    case 1: hipLaunchKernelGGL((k_update<T, MIXED, 4>), grid, dim3(NT), lds, st, a); break;
-    case 2: hipLaunchKernelGGL((k_update<T, MIXED, 2>), grid, dim3(NT), lds, st, a); break;
-    default: hipLaunchKernelGGL((k_update<T, MIXED, 1>), grid, dim3(NT), lds, st, a);
-  }
+  in_launches(count, split * split * NT, [&](int64_t i0, int64_t n) {
+    StepArgs<T> a = all;
+    a.items += first + i0;
+    a.nitems = (int32_t)n;
+    const dim3 grid(pad8(a.nitems * split * split));
+    switch (split) {
+      case 1: hipLaunchKernelGGL((k_update<T, MIXED, 4>), grid, dim3(NT), lds, st, a); break;
+      case 2: hipLaunchKernelGGL((k_update<T, MIXED, 2>), grid, dim3(NT), lds, st, a); break;
+      default: hipLaunchKernelGGL((k_update<T, MIXED, 1>), grid, dim3(NT), lds, st, a);
+    }
+  });
 }
 
 // A launch of n tiles with products of length k as `whole` tiles in full turns of the
@@ -792,13 +804,18 @@ static double thin_us(int64_t n, int64_t k, int rs) {
 }
 
 template <typename T, bool MIXED>
-static void slim_launch(const StepArgs<T>& a, int rs, int groups, hipStream_t st) {
-  const dim3 grid(pad8(8 * groups * a.nitems));
-  switch (rs) {
-    case 1: hipLaunchKernelGGL((k_update_slim<T, MIXED, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, a, groups); break;
-    case 2: hipLaunchKernelGGL((k_update_slim<T, MIXED, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, a, groups); break;
-    default: hipLaunchKernelGGL((k_update_slim<T, MIXED, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, a, groups);
-  }
+static void slim_launch(const StepArgs<T>& all, int rs, int groups, hipStream_t st) {
+  in_launches(all.nitems, 8 * groups * ThinShape<1>::THREADS, [&](int64_t i0, int64_t n) {
+    StepArgs<T> a = all;
+    a.items += i0;
+    a.nitems = (int32_t)n;
+    const dim3 grid(pad8(8 * groups * a.nitems)), nt(ThinShape<1>::THREADS);
+    switch (rs) {
+      case 1: hipLaunchKernelGGL((k_update_slim<T, MIXED, 1>), grid, nt, 0, st, a, groups); break;
+      case 2: hipLaunchKernelGGL((k_update_slim<T, MIXED, 2>), grid, nt, 0, st, a, groups); break;
+      default: hipLaunchKernelGGL((k_update_slim<T, MIXED, 4>), grid, nt, 0, st, a, groups);
+    }
+  });
 }
 
 template <typename T, bool MIXED>
@@ -885,7 +902,12 @@ void launch_trsm(const StepArgs<T>& a, hipStream_t st) {
   if (a.nitems * strips <= 2 * NCU)
     hipLaunchKernelGGL((k_trsm_few<T>), dim3(pad8(strips * a.nitems)), dim3(2 * NT), 0, st, a, strips);
   else if (a.nitems <= NCU || std::is_same<T, float>::value)
-    hipLaunchKernelGGL((k_trsm<T, 1>), dim3(pad8(2 * a.nitems)), dim3(NT), TrsmLds<T>::BYTES, st, a);
+    in_launches(a.nitems, 2 * NT, [&](int64_t i0, int64_t n) {
+      StepArgs<T> b = a;
+      b.items += i0;
+      b.nitems = (int32_t)n;
+      hipLaunchKernelGGL((k_trsm<T, 1>), dim3(pad8(2 * b.nitems)), dim3(NT), TrsmLds<T>::BYTES, st, b);
+    });
   else if constexpr (std::is_same<T, double>::value)
     hipLaunchKernelGGL((k_trsm<T, 2>), dim3(pad8(a.nitems)), dim3(NT), TrsmLds<T>::BYTES, st, a);
 }
@@ -898,24 +920,31 @@ void launch_band(const BandArgs<T>& a, hipStream_t st) {
   b.nitems -= a.thin.n;
   if (b.nitems > 0) hipLaunchKernelGGL(k_band<T>, dim3(pad8(b.nitems)), dim3(NT), lds, st, b);
   if (a.thin.n <= 0) return;
-  b.items += b.nitems;
-  b.nitems = a.thin.n;
-  const dim3 grid(pad8(8 * b.nitems));
-  switch (thin_rs(a.thin.rows)) {
-    case 1: hipLaunchKernelGGL((k_band_thin<T, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, b); break;
-    case 2: hipLaunchKernelGGL((k_band_thin<T, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, b); break;
-    default: hipLaunchKernelGGL((k_band_thin<T, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, b);
-  }
+  const BandItem* few = a.items + b.nitems;
+  in_launches(a.thin.n, 8 * ThinShape<1>::THREADS, [&](int64_t i0, int64_t n) {
+    b.items = few + i0;
+    b.nitems = (int32_t)n;
+    const dim3 grid(pad8(8 * b.nitems)), nt(ThinShape<1>::THREADS);
+    switch (thin_rs(a.thin.rows)) {
+      case 1: hipLaunchKernelGGL((k_band_thin<T, 1>), grid, nt, 0, st, b); break;
+      case 2: hipLaunchKernelGGL((k_band_thin<T, 2>), grid, nt, 0, st, b); break;
+      default: hipLaunchKernelGGL((k_band_thin<T, 4>), grid, nt, 0, st, b);
+    }
+  });
 }
 
 template <typename T>
-static void tile_gemm_slim(const GemmTerm<T>* terms, const GemmOut* outs, int n, int rs, int groups, hipStream_t st) {
-  const dim3 grid(pad8(8 * groups * n));
-  switch (rs) {
-    case 1: hipLaunchKernelGGL((k_tile_gemm_slim<T, 1>), grid, dim3(ThinShape<1>::THREADS), 0, st, terms, outs, n, groups); break;
-    case 2: hipLaunchKernelGGL((k_tile_gemm_slim<T, 2>), grid, dim3(ThinShape<2>::THREADS), 0, st, terms, outs, n, groups); break;
-    default: hipLaunchKernelGGL((k_tile_gemm_slim<T, 4>), grid, dim3(ThinShape<4>::THREADS), 0, st, terms, outs, n, groups);
-  }
+static void tile_gemm_slim(const GemmTerm<T>* terms, const GemmOut* all, int nall, int rs, int groups, hipStream_t st) {
+  in_launches(nall, 8 * groups * ThinShape<1>::THREADS, [&](int64_t i0, int64_t m) {
+    const GemmOut* outs = all + i0;
+    const int n = (int)m;
+    const dim3 grid(pad8(8 * groups * n)), nt(ThinShape<1>::THREADS);
+    switch (rs) {
+      case 1: hipLaunchKernelGGL((k_tile_gemm_slim<T, 1>), grid, nt, 0, st, terms, outs, n, groups); break;
+      case 2: hipLaunchKernelGGL((k_tile_gemm_slim<T, 2>), grid, nt, 0, st, terms, outs, n, groups); break;
+      default: hipLaunchKernelGGL((k_tile_gemm_slim<T, 4>), grid, nt, 0, st, terms, outs, n, groups);
+    }
+  });
 }
 
 template <typename T>
@@ -935,7 +964,9 @@ void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, T
   else if (nout <= 16)  // 16 pieces: n = 14 31 us, 4 pieces 47
     hipLaunchKernelGGL((k_tile_gemm<T, 1>), dim3(pad8(16 * nout)), dim3(NT), 0, st, terms, outs, nout);
   else if (nout <= NCU / 2 || std::is_same<T, float>::value)
-    hipLaunchKernelGGL((k_tile_gemm<T, 2>), dim3(pad8(4 * nout)), dim3(NT), 0, st, terms, outs, nout);
+    in_launches(nout, 4 * NT, [&](int64_t i0, int64_t n) {
+      hipLaunchKernelGGL((k_tile_gemm<T, 2>), dim3(pad8(4 * (int)n)), dim3(NT), 0, st, terms, outs + i0, (int)n);
+    });
   else
     hipLaunchKernelGGL((k_tile_gemm<T, 4>), dim3(pad8(nout)), dim3(NT), WG_GEMM_LDS, st, terms, outs, nout);
 }

@@ -189,3 +189,43 @@ def test_device_cache_keeps_two_problems_and_is_bounded(lib):
     print(f"  hipMalloc calls {mallocs}, most blocks kept {most}", flush=True)
     assert mallocs["cycle 0"] > 0 and mallocs.get("cycle 2", 0) == mallocs.get("cycle 3", 0) == 0
     assert most[0] <= 12 and most[1] <= 4.3 + 0.12 and kept == []
+
+
+# 540000 windows of one point, a test point each.  The support rows and the output row of the
+# windows, and the products of the test rows, are 1080000 tiles of few rows: more than one
+# launch holds (2^32 threads, 4096 per tile; of a larger one only the remainder would run).
+# With one point per window the definition has a closed form; tolerance: the mixed bar.
+def test_half_a_million_windows(lib):
+    M, s, ell, sn2 = 540000, 64, 0.5, 1.0
+    rng = np.random.default_rng(5)
+    X = np.sort(rng.uniform(0, 100.0, size=M))
+    y = np.sin(X) + 0.1 * rng.standard_normal(M)
+    U = X + 1e-3
+    S = X[::M // s][:s]
+    ptr = np.arange(M + 1, dtype=np.int64)
+    state = lib.fit(X[:, None], y, ptr, S[:, None], 0, np.log([ell, 1.0, sn2]), precision="mixed")
+    mean, var = (t.cpu().numpy() for t in state.predict(U[:, None], ptr))
+    lml = state.lml()
+    state.free()
+    lib.release_cache()
+
+    def kernel(a, b):
+        return np.exp(-0.5 * ((a[:, None] - b[None]) / ell) ** 2)
+
+    Sig = kernel(S, S) + sn2 * np.eye(s)
+    Li = np.linalg.inv(np.linalg.cholesky(Sig)).T
+    K, Ku = kernel(X, S), kernel(U, S)
+    V, Vu = K @ Li, Ku @ Li
+    R = 1.0 + sn2 - (V ** 2).sum(1)
+    Z, z = K / np.sqrt(R)[:, None], y / np.sqrt(R)
+    Sdd, ydd = Sig + Z.T @ Z, Z.T @ z
+    g = np.linalg.solve(Sdd, ydd)
+    x = (np.exp(-0.5 * ((U - X) / ell) ** 2) - (Vu * V).sum(1)) / np.sqrt(R)
+    E = Ku - x[:, None] * Z
+    want_mean = E @ g + x * z
+    want_var = 1.0 + sn2 - (Vu ** 2).sum(1) - x ** 2 + (E * np.linalg.solve(Sdd, E.T).T).sum(1)
+    want = -0.5 * (z @ z - ydd @ g + np.log(R).sum() + np.linalg.slogdet(Sdd)[1] - np.linalg.slogdet(Sig)[1]
+                   + M * np.log(2 * np.pi))
+    for got, ref in ((mean, want_mean), (var, want_var)):
+        assert np.abs(got - ref).max() < 1e-4 * np.abs(ref).max()
+    assert abs(lml - want) < 1e-4 * abs(want)
