@@ -54,14 +54,6 @@ __device__ inline u16 f2bf(float x) {
 }
 __device__ inline float bf2f(u16 h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ inline bf8 load8(const u16* p) { return __builtin_bit_cast(bf8, *(const uint4*)p); }
-__device__ inline bf8 pack8(const u16 (&h)[8]) {
-  uint4 q;
-  q.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-  q.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
-  q.z = (uint32_t)h[4] | ((uint32_t)h[5] << 16);
-  q.w = (uint32_t)h[6] | ((uint32_t)h[7] << 16);
-  return __builtin_bit_cast(bf8, q);
-}
 __device__ inline f4v mma(bf8 a, bf8 b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 __device__ inline uint2 pack4(const u16 (&h)[4]) {
   return make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));

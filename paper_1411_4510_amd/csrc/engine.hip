@@ -967,7 +967,7 @@ void launch_tile_gemm(const GemmTerm<T>* terms, const GemmOut* outs, int nout, T
     in_launches(nout, 4 * NT, [&](int64_t i0, int64_t n) {
       hipLaunchKernelGGL((k_tile_gemm<T, 2>), dim3(pad8(4 * (int)n)), dim3(NT), 0, st, terms, outs + i0, (int)n);
     });
-  else
+  else if constexpr (std::is_same<T, double>::value)
     hipLaunchKernelGGL((k_tile_gemm<T, 4>), dim3(pad8(nout)), dim3(NT), WG_GEMM_LDS, st, terms, outs, nout);
 }
 
@@ -984,8 +984,7 @@ hipError_t engine_init() {
   e = hipFuncSetAttribute((const void*)k_update<float, false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)(2 * 64 * TB * sizeof(float)));
   if (e != hipSuccess) return e;
-  for (const void* f : {(const void*)k_tile_gemm<double, 4>, (const void*)k_tile_gemm<float, 4>,
-                        (const void*)k_update_part<double, false>}) {
+  for (const void* f : {(const void*)k_tile_gemm<double, 4>, (const void*)k_update_part<double, false>}) {
     e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)WG_GEMM_LDS);
     if (e != hipSuccess) return e;
   }

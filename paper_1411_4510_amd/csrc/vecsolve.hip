@@ -31,15 +31,6 @@ __device__ inline int64_t win_point(const WinTab& w, int m, int r, bool& valid) 
 
 __device__ inline int64_t jp_off(int i) { return (int64_t)TB * TB * i * (i + 1) / 2; }
 
-__device__ inline double sqd(const double* a, const double* b, int d) {
-  double s = 0.0;
-  for (int t = 0; t < d; ++t) {
-    const double df = a[t] - b[t];
-    s += df * df;
-  }
-  return s;
-}
-
 __device__ inline double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
