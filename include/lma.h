@@ -106,6 +106,9 @@ lma_status lma_fit(const lma_problem *p, hipStream_t stream, lma_state **out);
  * exceeds sigma_s^2 + sigma_n^2, and for 0 < B < M-1 it can be negative at a
  * few test points, because the covariance of Eq. (2) over training and test
  * inputs together need not be positive definite there.
+ * The same request gives the same bits.  How many points a request holds decides
+ * the order of some sums, so a point's mean and variance may differ in their last
+ * bits between requests (to rounding: 1e-9 relative to the largest in float64).
  * Errors: LMA_E_ARG, LMA_E_HIP, LMA_E_NOMEM.
  */
 lma_status lma_predict(lma_state *f, int64_t n_u, const double *U, const int64_t *u_block_ptr,
@@ -142,6 +145,10 @@ lma_status lma_predict_cov(lma_state *f, int64_t n_u, const double *U, const int
  * mem_budget_bytes the fitted state leaves (at least 256 MB; 16 GB when
  * mem_budget_bytes is 0).  Synchronises the stream.  Errors as for lma_fit;
  * LMA_E_NOT_PD also for a non-finite gradient.
+ * With grad NULL *lml is, bit for bit, the likelihood of an lma_fit of the same
+ * problem.  With a gradient the factors are formed in one fixed order of sums, so
+ * *lml may differ from that in its last bits (to rounding: 1e-9 relative in
+ * float64, 1e-8 in mixed precision).
  */
 lma_status lma_lml(const lma_problem *p, double *lml, double *grad, hipStream_t stream);
 

@@ -19,12 +19,11 @@
 
 namespace lma {
 
-// k_diag16 (float64 fits).  What bounds it is the serial chain of 128 pivots, so
-// the chain is kept in registers.  The 128 x 128 tile is cut into 16 x 16 blocks
+// k_diag16 (float64 fits).  The serial chain of 128 pivots cannot be shortened, so
+// it is kept in registers.  The 128 x 128 tile is cut into 16 x 16 blocks
 // whose lower half lives in the accumulators of the four waves (block (i, j) with
 // wave j mod 4).  For each block column kb the column goes to LDS as 16-wide rows;
-// every lane then
-// holds one row: lanes 0-15 of every wave the diagonal block (four copies, so the
+// every lane then holds one row: lanes 0-15 of every wave the diagonal block (four copies, so the
 // pivots need no barrier), lanes 16-47 the rows of two other blocks.  One pass over
 // the 16 columns factors the diagonal block and solves all other rows against it,
 // with the pivot row read by v_readlane.  The rows of block kb itself are rows of
@@ -34,8 +33,10 @@ namespace lma {
 // block (j, kb) of L).  The trailing update of both is one MFMA product per slot.
 // Two barriers per block column; they order LDS only, so the stores of the results
 // (from LDS, in whole rows) drain behind the next block column.
-// Measured per launch (one workgroup per diagonal tile): 206 us for k_diag32,
-// 36 us in this form, of which the pivot chain is 10.
+// Measured per launch (one workgroup per diagonal tile): 205 us for 32 x 32 blocks with
+// columns and sums as loops over LDS, 35 us in this form.  Bound: of the 35 us the pivot
+// chain is 10; the rest is the sixteen barriers, the trips of a block column through LDS
+// and the trailing products between them, one after the other.
 constexpr int NB = 16;          // block edge
 constexpr int NBK = TB / NB;    // blocks per tile side
 constexpr int PLD = NB + 2;     // row stride of the panel in LDS (16-byte aligned rows)
@@ -230,8 +231,8 @@ __global__ __launch_bounds__(NT) void k_diag16(StepArgs<double> a, const int32_t
 // it forms those sums exactly as a loop over k does; the columns of a block run in
 // registers, a row per lane (lanes 0-31 of every wave the diagonal block, lanes 32-63
 // rows below it) with the pivot row by v_readlane.  Bound: the chain of 128 roots,
-// reciprocals and divisions.  Measured per launch: 215 us with the columns and sums as
-// loops over LDS, 62 us in this form, with the same bits.
+// reciprocals and divisions.  Measured per launch: 205 us (float32 tiles 220) with the
+// columns and sums as loops over LDS, 60 us (64) in this form, with the same bits.
 constexpr int DLD = TB + 1;      // row stride of the tile in LDS
 constexpr int DB = 32;           // block edge
 constexpr int DNB = TB / DB;     // blocks per tile side

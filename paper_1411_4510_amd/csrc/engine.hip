@@ -709,15 +709,18 @@ static void in_launches(int64_t n, int64_t threads, F&& f) {
 }
 
 // Pieces per tile side (1, 2 or 4) of a launch of n whole tiles with products of
-// length k.  A whole tile gives its products the most reuse but only one workgroup
-// fits on a CU, so n tiles take ceil(n / 256) turns.  Measured (k_update, float64, in
-// units of one turn): 4 pieces per tile take 0.48 per turn of 256 of them (two fit
-// on a CU, each at a lower rate), 16 pieces 0.245.  So cutting pays while the pieces
-// fit in one (n <= 16, 32 .. 64) or two (n <= 128) turns: n = 8 1763 / 864 / 432 us for
-// 1 / 4 / 16 pieces at k = 16000, n = 56 1576 / 751 / 1469, n = 120 1474 / 1406 / 2770,
-// n = 136 1289 / 1853 / 2731.  With k <= 256 the covariance and the stores are most of
-// a tile's time and more workgroups on a CU overlap them: n = 1032, k = 0 150 / 80 / 81 us,
-// k = 128 235 / 195 / 266, k = 256 324 / 310 / 470, k = 384 397 / 427 / 686.
+// length k.  A whole tile gives its products the most reuse; pieces fill CUs that whole
+// tiles leave idle, and overlap the covariance and the stores where products are short.
+// Measured, us for 1 / 4 / 16 pieces a tile (d = 1):
+//   float64, k = 3072: n = 8 384 / 176 / 90, 24 387 / 180 / 177, 64 388 / 186 / 342, 128 398 /
+//   354 / 667, 136 397 / 517 / 751, 512 810 / 1368 / 2663 (two whole tiles share a CU)
+//   mixed, k = 3072: n = 8 218 / 92 / 47, 64 220 / 99 / 179, 128 221 / 184 / 339, 136 222 / 265 / 380
+//   k = 0: float64 n = 256 29 / 21 / 19, 1032 71 / 66 / 56; mixed 1032 93 / 58 / 56
+//   k = 128: float64 n = 136 44 / 41 / 43, 1032 151 / 188 / 260; mixed 1032 144 / 115 / 140
+//   k = 256: float64 n = 128 59 / 43 / 65, 1032 224 / 299 / 459; mixed 1032 194 / 171 / 234
+//   k = 384: mixed n = 136 51 / 49 / 56, 512 99 / 113 / 176
+// The line at k = 256 is right for mixed precision; in float64 it was drawn when a whole tile
+// held a CU alone (n = 1032, k = 256: 324 / 310), and beyond n = 136 lies at 0 now.
 static inline int split_of(int64_t n, int64_t k) {
   if (n <= 16 || (k == 0 && n <= NCU)) return 4;
   return n <= NCU / 2 || k <= 256 ? 2 : 1;
@@ -748,9 +751,10 @@ struct UpdatePlan {
   double us;
 };
 
-// Estimated times in us.  Measured for a turn of whole tiles: 1.75 us per 16 k in
-// float64 and 1.05 in mixed precision (float32 products and their folds); the
-// parts are written and read once (128 KB each, 3.5 TB/s) and need a launch more.
+// Estimated times in us.  A turn of whole tiles is taken as 1.75 us per 16 k in float64
+// (256 tiles alone take 2.1) and 1.05 in mixed precision (float32 products and their folds;
+// 1.0 for half a turn, 1.3 for a full one); the parts are written and read once (128 KB
+// each, 3.5 TB/s) and need a launch more.
 // Measured over all launches (products of k_update, its parts and their sums): full GP
 // n=16384 261 -> 201 ms, n=262144 728 -> 688, n=65536 22.4 -> 21.7, mixed n=50021 36.5 -> 31.3.
 template <bool MIXED>

@@ -5,7 +5,9 @@
 // owns the 64x64 quadrant (wr, wc) as 4x4 MFMA 16x16 sub-tiles.  Where a launch
 // has too few tiles to fill the chip the tile is cut into 64x64 or 32x32 pieces, a
 // workgroup each, and a wave owns 2x2 sub-tiles or one.  Every element sums its
-// products in the same order in these forms (not where parts or waves share k).  Operand
+// products in the same order in these forms (not where parts or waves share k).
+// Whole tiles with float64 products take their operands through LDS (wg_gemm).
+// Elsewhere (wave_gemm: pieces, thin tiles, float32 products) operand
 // fragments are read straight from HBM/L2 in the MFMA 16x16x4 input layout
 // (lane l supplies row l%16 and four consecutive k values starting at
 // 4*(l/16)); the four MFMA k-steps of a 16-wide k chunk consume those four
