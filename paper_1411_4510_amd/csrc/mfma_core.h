@@ -218,7 +218,7 @@ __device__ inline void zero_acc(typename Mfma<Tc>::acc (&acc)[RA][RB]) {
 // Measured with 4096 tiles of k = 4096 (peak 78.6 TFLOP/s): 63.0 for wave_gemm straight
 // from memory with one workgroup per CU, 65.2 for two plain stages in LDS, 66.5 with
 // the barrier between the halves, 71.9 with the LDS writes and loads dealt out among
-// the products (matrix cores busy 92 %).  With 256 tiles, one per CU, both forms take
+// the products (matrix cores busy 92 %; 88 % over the whole-tile launches of an n=524288 step).  With 256 tiles, one per CU, both forms take
 // the same time (668 and 679 us).
 constexpr int SLD = 18;                                          // row stride in LDS: 16 rows touch every bank once
 constexpr size_t WG_GEMM_LDS = 2 * 2 * 128 * SLD * sizeof(double);  // two stages of 128 + 128 rows
