@@ -18,6 +18,7 @@
 // Sigma_ddot solve of k_u - G_u, and the combine of Theorem 2.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdlib>
@@ -698,6 +699,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
   }
   // ---- window table
   int maxTw = 0;
+  std::vector<std::vector<int32_t>> above;  // per chunk of windows, for launch_fwd / launch_bwd
   {
     std::vector<int64_t> tab(10 * M);
     int64_t* t_wstart = tab.data();
@@ -710,6 +712,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
     int64_t* t_rhs = t_vec + M;
     int32_t* t_T = reinterpret_cast<int32_t*>(t_rhs + M);
     int32_t* t_tw = t_T + M;
+    int32_t* t_order = reinterpret_cast<int32_t*>(t_rhs + 2 * M);
     int64_t vec_acc = 0;
     for (int64_t m = 0; m < M; ++m) {
       const WinGeom g = win_geom(f.bp, M, f.B, m);
@@ -725,6 +728,18 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
       t_tw[m] = g.tw;
       vec_acc += (int64_t)g.T * TB;
       maxTw = std::max(maxTw, g.T);
+    }
+    // the windows of a chunk, those of more tiles first, and how many have more than i
+    above.resize(f.chunk.size() - 1);
+    for (size_t c = 0; c + 1 < f.chunk.size(); ++c) {
+      const int64_t m0 = f.chunk[c], nw = f.chunk[c + 1] - m0;
+      std::vector<int32_t>& n = above[c];
+      n.assign(*std::max_element(t_T + m0, t_T + m0 + nw) + 1, 0);
+      for (int64_t m = m0; m < m0 + nw; ++m) n[t_T[m] - 1] += 1;
+      for (size_t i = n.size(); i-- > 1;) n[i - 1] += n[i];
+      std::vector<int32_t> at(n);  // where the next window of i tiles goes
+      for (int64_t m = 0; m < nw; ++m) t_order[m0 + at[t_T[m0 + m]]++] = (int32_t)m;
+      n.pop_back();
     }
     f.wt_host = std::move(tab);
   }
@@ -960,6 +975,7 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
       va.w = sub(c);
       va.panels = panels;
       va.invs = invs;
+      va.order = reinterpret_cast<const int32_t*>(dtab + 9 * M) + f.chunk[c];
       va.sp = (int)sp;
       va.s = (int)s;
       va.g = g;
@@ -972,14 +988,14 @@ lma_status do_fit(const lma_problem* p, hipStream_t st, lma_state** out, bool ke
       auto va = winvec(panels, invs, xJ, xW, c);
       using TT = typename std::remove_const<typename std::remove_pointer<decltype(panels)>::type>::type;
       prof::timed(prof::OTHER, 0.0, st, [&] { launch_ycp<TT>(va, nwin(c), maxTw, st); });
-      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, nwin(c), maxTw, st); });
+      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, above[c].data(), (int)above[c].size(), st); });
       HIPCHK(hipGetLastError());
     };
     auto full_solve = [&](auto* panels, auto* invs, double* vJ, double* vW, int c) {
       auto va = winvec(panels, invs, vJ, vW, c);
       using TT = typename std::remove_const<typename std::remove_pointer<decltype(panels)>::type>::type;
-      prof::timed(prof::OTHER, 0.0, st, [&] { launch_fwd<TT>(va, nwin(c), maxTw, st); });
-      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, nwin(c), maxTw, st); });
+      prof::timed(prof::OTHER, 0.0, st, [&] { launch_fwd<TT>(va, above[c].data(), (int)above[c].size(), st); });
+      prof::timed(prof::OTHER, 0.0, st, [&] { launch_bwd<TT>(va, above[c].data(), (int)above[c].size(), st); });
       HIPCHK(hipGetLastError());
     };
     // x += alpha t over the vector entries of chunk c's windows

@@ -102,6 +102,7 @@ struct WinVecArgs {
   WinTab w;
   const TW* panels;        // window factor storage
   const TW* invs;          // inverted diagonal tiles
+  const int32_t* order;    // windows, those of more column tiles first (k_solve_step)
   int sp, s;
   const double* g;         // [sp] (k_ycp)
   double* vJ;
@@ -135,10 +136,11 @@ struct HArgs {
 
 template <typename TW>
 void launch_ycp(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st);
+// above[i]: windows of more than i column tiles, i = 0 .. maxT - 1
 template <typename TW>
-void launch_fwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st);
+void launch_fwd(const WinVecArgs<TW>& a, const int32_t* above, int maxT, hipStream_t st);
 template <typename TW>
-void launch_bwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st);
+void launch_bwd(const WinVecArgs<TW>& a, const int32_t* above, int maxT, hipStream_t st);
 void launch_gres(const GresArgs& a, hipStream_t st);
 // g += dg and t = L_SS^T dg (one workgroup)
 void launch_gupdate(const double* L, const double* dg, double* g, double* t, int sp, hipStream_t st);

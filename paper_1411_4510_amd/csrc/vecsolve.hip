@@ -45,11 +45,13 @@ __device__ inline double wave_sum(double v) {
 // whose tile is next solves it at once with the inverted diagonal tile.  It alone
 // touches that tile of the vector, so the solution replaces the vector in place.
 // W_m's factor is the leading block of J_m's, so both vectors take part in one
-// read of a tile.  Bound: one read of the factors (HBM), and for few or narrow
-// windows the launches.  Measured against one workgroup per window walking its
-// factor once for each vector: backward at n=16384, M=16, B=15 (6.3 GB of factors)
-// 44.2 -> 2.6 ms, n=2048 92 -> 20 us (4 launches); forward and backward of a mixed
-// fit (n=50021, B=3) 26.7 -> about 4 ms.
+// read of a tile.  A launch holds the windows that have a tile in it: 20000 windows of
+// 2 points beside one of 8000 in mixed precision (B=0) took 95 ms, nearly all of it
+// empty workgroups, with every window in each launch, and take 3.3 ms (the fit 135 -> 40).
+// Bound: one read of the factors (HBM), and for few or narrow windows the launches.
+// Measured against one workgroup per window walking its factor once for each vector:
+// backward at n=16384, M=16, B=15 (6.3 GB of factors) 44.2 -> 2.6 ms, n=2048 92 -> 20 us
+// (4 launches); forward and backward of a mixed fit (n=50021, B=3) 26.7 -> about 4 ms.
 constexpr int SOLVE_NT = 512;
 constexpr int SOLVE_W = SOLVE_NT / 64;
 constexpr int SOLVE_R = TB / SOLVE_W;  // tile rows of a wave
@@ -123,18 +125,19 @@ __device__ inline double mul_n(const typename Vec2<TW>::type (&a)[SOLVE_R], cons
 // Step i of the solves with L^T (BWD, i = maxT .. 1: tile i is solved, tile i - 1
 // comes next) or with L (i = 0 .. maxT - 1: tile i - 1 is solved, tile i comes next).
 template <typename TW, bool BWD>
-__global__ __launch_bounds__(SOLVE_NT) void k_solve_step(WinVecArgs<TW> a, int i) {
+__global__ __launch_bounds__(SOLVE_NT) void k_solve_step(WinVecArgs<TW> a, int i, int y0) {
   __shared__ double xJ[TB], xW[TB];
   __shared__ double red[SOLVE_W * TB];
   typedef typename Vec2<TW>::type V2;
-  const int m = blockIdx.x, tid = threadIdx.x;
+  const int m = a.order[blockIdx.x], tid = threadIdx.x;
   const WinTab& w = a.w;
   const int T = w.T[m], tw = w.tw[m];
   // the tile of the vector this workgroup updates, and whether there is a solved tile to subtract
-  const int tv = BWD ? i - 1 - (int)blockIdx.y : i + (int)blockIdx.y;
+  const int y = y0 + (int)blockIdx.y;
+  const int tv = BWD ? i - 1 - y : i + y;
   const int ts = BWD ? i : i - 1;
   if (tv < 0 || tv >= T) return;
-  const bool upd = BWD ? i < T : i > 0, next = blockIdx.y == 0;
+  const bool upd = BWD ? i < T : i > 0, next = y == 0;
   if (BWD && i > T) return;
   if (!upd && !next) return;
   const bool inW = tv < tw, updW = inW && (BWD ? i < tw : i > 0);
@@ -308,15 +311,31 @@ template <typename TW>
 void launch_ycp(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st) {
   hipLaunchKernelGGL(k_ycp<TW>, dim3(M, (maxT * TB + 255) / 256), dim3(256), 0, st, a);
 }
+// A workgroup without a tile takes 0.48 ns (20000 windows, maxT=63: 195M of them 95 ms),
+// a launch about 4 us: launches are cut where they would hold more empty ones than this.
+constexpr int64_t SOLVE_EMPTY = 8192;
 template <typename TW>
-void launch_fwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st) {
-  for (int i = 0; i < maxT; ++i)
-    hipLaunchKernelGGL((k_solve_step<TW, false>), dim3(M, i > 0 ? maxT - i : 1), dim3(SOLVE_NT), 0, st, a, i);
+void launch_fwd(const WinVecArgs<TW>& a, const int32_t* above, int maxT, hipStream_t st) {
+  for (int i = 0; i < maxT; ++i) {
+    const int ys = i > 0 ? maxT - i : 1;
+    for (int y = 0, ny; y < ys; y += ny) {
+      const int n = above[i + y];
+      int64_t empty = 0;
+      for (ny = 1; y + ny < ys && (empty += n - above[i + y + ny]) <= SOLVE_EMPTY;) ++ny;
+      hipLaunchKernelGGL((k_solve_step<TW, false>), dim3(n, ny), dim3(SOLVE_NT), 0, st, a, i, y);
+    }
+  }
 }
 template <typename TW>
-void launch_bwd(const WinVecArgs<TW>& a, int M, int maxT, hipStream_t st) {
-  for (int i = maxT; i > 0; --i)
-    hipLaunchKernelGGL((k_solve_step<TW, true>), dim3(M, i < maxT ? i : 1), dim3(SOLVE_NT), 0, st, a, i);
+void launch_bwd(const WinVecArgs<TW>& a, const int32_t* above, int maxT, hipStream_t st) {
+  for (int i = maxT; i > 0; --i) {
+    // windows of i tiles start here with their last one; those of more subtract from all i
+    const int n = above[i - 1], more = i < maxT ? above[i] : 0;
+    const bool together = more > 0 && (int64_t)(n - more) * (i - 1) <= SOLVE_EMPTY;
+    hipLaunchKernelGGL((k_solve_step<TW, true>), dim3(n, together ? i : 1), dim3(SOLVE_NT), 0, st, a, i, 0);
+    if (more > 0 && !together)
+      hipLaunchKernelGGL((k_solve_step<TW, true>), dim3(more, i - 1), dim3(SOLVE_NT), 0, st, a, i, 1);
+  }
 }
 void launch_gres(const GresArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(k_gres, dim3(1), dim3(256), sizeof(double) * (size_t)a.sp, st, a);
@@ -341,9 +360,9 @@ void launch_h(const HArgs& a, hipStream_t st) {
 }
 template void launch_ycp<double>(const WinVecArgs<double>&, int, int, hipStream_t);
 template void launch_ycp<float>(const WinVecArgs<float>&, int, int, hipStream_t);
-template void launch_fwd<double>(const WinVecArgs<double>&, int, int, hipStream_t);
-template void launch_fwd<float>(const WinVecArgs<float>&, int, int, hipStream_t);
-template void launch_bwd<double>(const WinVecArgs<double>&, int, int, hipStream_t);
-template void launch_bwd<float>(const WinVecArgs<float>&, int, int, hipStream_t);
+template void launch_fwd<double>(const WinVecArgs<double>&, const int32_t*, int, hipStream_t);
+template void launch_fwd<float>(const WinVecArgs<float>&, const int32_t*, int, hipStream_t);
+template void launch_bwd<double>(const WinVecArgs<double>&, const int32_t*, int, hipStream_t);
+template void launch_bwd<float>(const WinVecArgs<float>&, const int32_t*, int, hipStream_t);
 
 }  // namespace lma

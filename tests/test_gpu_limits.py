@@ -229,3 +229,145 @@ def test_half_a_million_windows(lib):
     for got, ref in ((mean, want_mean), (var, want_var)):
         assert np.abs(got - ref).max() < 1e-4 * np.abs(ref).max()
     assert abs(lml - want) < 1e-4 * abs(want)
+
+
+# Window solves of very unequal windows: launches that hold the windows with a tile in
+# them.  Windows of 1 to 14 tiles in several classes against the oracle, and 20000 windows
+# of two points beside one of 8000: what the launches take (85 ms with every window in each)
+@pytest.mark.parametrize("precision,bar", [("fp64", 1e-9), ("mixed", 1e-5)])
+@pytest.mark.parametrize("B", [0, 1, 3])
+def test_windows_of_very_unequal_sizes(lib, B, precision, bar):
+    from oracle import lma as olma
+    sizes = [5, 3, 400, 7, 1300, 2, 130, 129, 900, 4, 4, 260, 1, 1]
+    p = synth.make_random(seed=8, n=sum(sizes), d=3, M=len(sizes), s=70, n_u=60, B=B, uneven=(1, 1300), sn2=0.05)
+    p.block_ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    ref = olma.fit_predict(p)
+    for budget in (0, 1):
+        state = lib.fit_problem(p, precision=precision)
+        if budget:  # chunks of windows, each with an order of its own
+            full = state.nbytes()
+            state.free()
+            state = lib.fit_problem(p, precision=precision, mem_budget=int(0.75 * full))
+            assert state.chunks() > 1
+        mean, var = state.predict(p.U, p.u_block_ptr)
+        lml = state.lml()
+        state.free()
+        for got, want in ((mean.cpu().numpy(), ref["mean"]), (var.cpu().numpy(), ref["var"])):
+            assert np.linalg.norm(got - want) < bar * np.linalg.norm(want)
+        assert abs(lml - ref["lml"]) < bar * abs(ref["lml"])
+
+
+def test_solves_of_one_large_among_many_small_windows(lib):
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    sizes = np.full(20000, 2)
+    sizes[6000] = 8000
+    rng = np.random.default_rng(2)
+    n = int(sizes.sum())
+    X = np.sort(rng.uniform(size=n))[:, None]
+    y = np.sin(9 * X[:, 0]) + 0.1 * rng.standard_normal(n)
+    bp = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as pf:
+        lib.fit(X, y, bp, X[::500], 0, np.log([0.3, 1.0, 0.05]), precision="mixed").free()
+        torch.cuda.synchronize()
+    ran = [e.time_range.elapsed_us() for e in pf.events()
+           if e.device_type == torch.autograd.DeviceType.CUDA and "k_solve_step" in e.name]
+    if not ran:
+        pytest.skip("the profiler records no kernels here")
+    print(f"  {len(ran)} launches, {sum(ran) / 1e3:.2f} ms", flush=True)
+    assert sum(ran) < 20e3
+
+
+@pytest.mark.parametrize("precision,bar", [("fp64", 1e-9), ("mixed", 1e-5)])
+@pytest.mark.parametrize("sizes", [[2] * 1500 + [1500] + [2] * 1500 + [300], [129] * 8400 + [300]], ids=["12", "3"])
+def test_solves_of_launches_that_are_cut(lib, sizes, precision, bar):
+    # B = 0: PIC in closed form; launches with and without the small windows
+    rng = np.random.default_rng(3)
+    sizes = np.array(sizes)
+    n, ell, sf2, sn2 = int(sizes.sum()), 0.4, 1.3, 0.3
+    bp = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    X = np.sort(rng.uniform(0, 10, size=(n, 1)), axis=0)
+    y = np.sin(2 * X[:, 0]) + np.sqrt(sn2) * rng.standard_normal(n)
+    S = np.linspace(0, 10, 30)[:, None]
+    U = X[bp[:-1]] + 0.01  # one point in each block
+    up = np.arange(len(sizes) + 1, dtype=np.int64)
+
+    def k(a, b):
+        return sf2 * np.exp(-0.5 * (a - np.swapaxes(b, -1, -2)) ** 2 / ell ** 2)
+
+    # Sigma_SS and the blocks' covariances hold the noise, as the fit's do
+    L = np.linalg.cholesky(k(S, S) + sn2 * np.eye(len(S)))
+    dot, rhs, kept = k(S, S) + sn2 * np.eye(len(S)), np.zeros(len(S)), []
+    for nb in np.unique(sizes):
+        ms = np.flatnonzero(sizes == nb)
+        rows = bp[ms][:, None] + np.arange(nb)
+        Xm, KmS = X[rows], k(X[rows], S)
+        V = np.linalg.solve(L, np.swapaxes(KmS, 1, 2))
+        R = k(Xm, Xm) + sn2 * np.eye(nb) - np.swapaxes(V, 1, 2) @ V
+        KuS = k(U[ms][:, None], S)
+        Rum = k(U[ms][:, None], Xm) - np.swapaxes(np.linalg.solve(L, np.swapaxes(KuS, 1, 2)), 1, 2) @ V
+        sol = np.linalg.solve(R, np.concatenate([KmS, y[rows][..., None]], axis=2))
+        G = np.swapaxes(KmS, 1, 2) @ sol
+        dot, rhs = dot + G[:, :, :-1].sum(0), rhs + G[:, :, -1].sum(0)
+        kept.append((ms, KuS[:, 0], (Rum @ sol)[:, 0]))
+    g = np.linalg.solve(dot, rhs)
+    want = np.empty(len(sizes))
+    for ms, KuS, r in kept:
+        want[ms] = KuS @ g + r[:, -1] - r[:, :-1] @ g
+    state = lib.fit(X, y, bp, S, 0, np.log([ell, sf2, sn2]), precision=precision)
+    mean = state.predict(U, up)[0].cpu().numpy()
+    alone = state.predict(U[:1], np.minimum(up, 1))[0].cpu().numpy()
+    state.free()
+    assert np.linalg.norm(mean - want) < bar * np.linalg.norm(want)
+    assert abs(alone[0] - want[0]) < bar * np.linalg.norm(want)
+
+
+def pic_lml(torch, sizes, X, y, S, log_hyp):
+    """Log likelihood of PIC (B = 0, equal sizes together) as a differentiable expression."""
+    ell, sf2, sn2 = log_hyp.exp()
+
+    def k(a, b):
+        return sf2 * torch.exp(-0.5 * (a - b.transpose(-1, -2)) ** 2 / ell ** 2)
+
+    eye = torch.eye(len(S), dtype=X.dtype)
+    Sig = k(S, S) + sn2 * eye
+    L = torch.linalg.cholesky(Sig)
+    start = np.concatenate([[0], np.cumsum(sizes)])
+    dot, rhs, out = Sig, 0.0, -0.5 * len(y) * np.log(2 * np.pi) + L.diagonal().log().sum()
+    for nb in np.unique(sizes):
+        rows = torch.tensor(start[np.flatnonzero(sizes == nb)][:, None] + np.arange(nb))
+        K = k(X[rows], S)
+        V = torch.linalg.solve_triangular(L, K.transpose(1, 2).contiguous(), upper=False)
+        R = k(X[rows], X[rows]) + sn2 * torch.eye(int(nb), dtype=X.dtype)
+        LR = torch.linalg.cholesky(R - V.transpose(1, 2).contiguous() @ V)
+        h = torch.linalg.solve_triangular(LR, torch.cat([K, y[rows][..., None]], 2), upper=False)
+        flat = h.reshape(-1, h.shape[2])
+        G = flat.T.contiguous() @ flat
+        dot, rhs = dot + G[:-1, :-1], rhs + G[:-1, -1]
+        out = out - 0.5 * G[-1, -1] - LR.diagonal(dim1=1, dim2=2).log().sum()
+    Ld = torch.linalg.cholesky(dot)
+    z = torch.linalg.solve_triangular(Ld, rhs[:, None], upper=False)
+    return out + 0.5 * (z * z).sum() - Ld.diagonal().log().sum()
+
+
+def test_gradient_of_one_large_among_many_small_windows(lib):
+    import torch
+    sizes = np.full(20000, 2)
+    sizes[6000] = 8000
+    rng = np.random.default_rng(4)
+    n = int(sizes.sum())
+    bp = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    X = np.sort(rng.uniform(0, 10, size=(n, 1)), axis=0)
+    y = np.sin(2 * X[:, 0]) + 0.5 * rng.standard_normal(n)
+    S = np.linspace(0, 10, 30)[:, None]
+    hyp = np.log([0.4, 1.3, 0.3])
+    h = torch.tensor(hyp, requires_grad=True)
+    want = pic_lml(torch, sizes, *[torch.tensor(a) for a in (X, y, S)], h)
+    want.backward()
+    value, grad = lib.lml(X, y, bp, S, 0, hyp, grad=True)
+    ref = h.grad.numpy()
+    print(f"  {abs(value - want.item()) / abs(want.item()):.1e}, "
+          f"{np.linalg.norm(grad - ref) / np.linalg.norm(ref):.1e}", flush=True)
+    assert abs(value - want.item()) < 1e-9 * abs(want.item())
+    # sums over n points with terms of either sign: 100 times the bar of a value
+    assert np.linalg.norm(grad - ref) < 1e-7 * np.linalg.norm(ref)
