@@ -111,16 +111,16 @@ __global__ __launch_bounds__(NTA) void k_km_assign(const double* __restrict__ P,
 // n=65536, k=64, d=8; the lists take 14 us.
 __global__ __launch_bounds__(256) void k_km_partial(const double* __restrict__ P, int64_t n, int d,
                                                     const int32_t* __restrict__ label, int k, int64_t ch0,
-                                                    int64_t nbx, double* __restrict__ part,
+                                                    int64_t nbx, int64_t b0, double* __restrict__ part,
                                                     int64_t* __restrict__ pcnt) {
   static_assert(CHUNK == 16 * 256 && CU == 8, "16 points per thread, eight 16-bit counters in two words");
   __shared__ __align__(16) uint8_t lab[CHUNK];  // centre of each point relative to c0, 255: another
   __shared__ uint16_t list[CHUNK];              // point offsets, by centre, in increasing order
   __shared__ uint64_t wsum[2][4];
   __shared__ int base[CU + 1];
-  // block b covers chunk ch0 + b / nbx and centres (b % nbx) * CU + 0..7
-  const int64_t g = blockIdx.x / nbx;
-  const int c0 = (int)(blockIdx.x - g * nbx) * CU;
+  // block b (b0 and on) covers chunk ch0 + b / nbx and centres (b % nbx) * CU + 0..7
+  const int64_t b = b0 + blockIdx.x, g = b / nbx;
+  const int c0 = (int)(b - g * nbx) * CU;
   const int nc = k - c0 < CU ? k - c0 : CU;
   const int64_t i0 = (ch0 + g) * CHUNK;
   const int m = (int)(n - i0 < CHUNK ? n - i0 : CHUNK);
@@ -273,9 +273,12 @@ hipError_t update_launch(const double* P, int64_t n, int32_t d, const int32_t* l
   }
   for (int64_t ch0 = 0; ch0 < nch && err == hipSuccess; ch0 += group) {
     const int64_t ng = std::min<int64_t>(group, nch - ch0);
-    hipLaunchKernelGGL(k_km_partial, dim3((unsigned)(ng * nbc)), dim3(256), 0, st, P, n, (int)d, label, (int)k, ch0,
-                       nbc, part, pcnt);
-    err = hipGetLastError();
+    // a launch holds less than 2^32 threads
+    for (int64_t b = 0; b < ng * nbc && err == hipSuccess; b += 0xffffff) {
+      const dim3 blocks((unsigned)std::min<int64_t>(ng * nbc - b, 0xffffff));
+      hipLaunchKernelGGL(k_km_partial, blocks, dim3(256), 0, st, P, n, (int)d, label, (int)k, ch0, nbc, b, part, pcnt);
+      err = hipGetLastError();
+    }
     if (err != hipSuccess) break;
     hipLaunchKernelGGL(k_km_combine, dim3((unsigned)nbx), dim3(NTU), 0, st, part, pcnt, ng, (int)k, (int)d, srun,
                        crun, ch0 == 0 ? 1 : 0, ch0 + ng >= nch ? 1 : 0, C, count);

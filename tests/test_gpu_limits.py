@@ -371,3 +371,24 @@ def test_gradient_of_one_large_among_many_small_windows(lib):
     assert abs(value - want.item()) < 1e-9 * abs(want.item())
     # sums over n points with terms of either sign: 100 times the bar of a value
     assert np.linalg.norm(grad - ref) < 1e-7 * np.linalg.norm(ref)
+
+
+def test_centre_update_of_more_workgroups_than_a_launch_holds(lib, monkeypatch):
+    # all partial sums at once: 262145 chunks of 4096 points x 64 groups of 8 centres, 2^24 + 64
+    # workgroups of 256 threads.  Whole coordinates: the sums are exact in any order.
+    import torch
+    n, k = 2 ** 30 + 4096, 512
+    monkeypatch.setenv("LMA_KMEANS_PART_BYTES", str(4 << 30))
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    label = torch.randint(0, k, (n,), dtype=torch.int32, device="cuda", generator=gen)
+    P = torch.randint(0, 64, (n, 1), dtype=torch.int32, device="cuda", generator=gen).double()
+    C, count = lib.kmeans_update(P, label, torch.zeros(k, 1, dtype=torch.float64, device="cuda"))
+    want = torch.zeros(k, dtype=torch.int64, device="cuda")
+    total = torch.zeros(k, dtype=torch.float64, device="cuda")
+    for i in range(0, n, 2 ** 26):
+        want += torch.bincount(label[i:i + 2 ** 26], minlength=k)
+        total += torch.bincount(label[i:i + 2 ** 26], weights=P[i:i + 2 ** 26, 0], minlength=k)
+    assert torch.equal(count.long(), want)
+    assert torch.equal(C[:, 0], total / want)
+    del P, label
+    torch.cuda.empty_cache()
